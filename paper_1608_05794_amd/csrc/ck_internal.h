@@ -31,7 +31,7 @@ struct RxnRec {
     int sp[3];                  // species of slots 0..5, two 16-bit indices per int (reactants first)
     int nu;                     // stoichiometric coefficient of slot s in bits 2s..2s+1 (1..3)
     int fall;                   // index into the fall-off table, or -1
-    int blk_slots;              // largest slot count among the 64 stored reactions of this one's block
+    int pad;
 };
 
 struct FallRec {                // fall-off parameters (Lindemann / Troe)
@@ -53,19 +53,27 @@ __host__ __device__ inline int rx_neff(int meta) { return meta >> 9; }
 __host__ __device__ inline int rx_sp(const RxnRec &r, int s) { return (r.sp[s >> 1] >> (16 * (s & 1))) & 0xffff; }
 __host__ __device__ inline int rx_nu(const RxnRec &r, int s) { return (r.nu >> (2 * s)) & 3; }
 
+// 64 consecutive pair-form reactions, one per lane of a wavefront, field by field so that each load
+// is contiguous over the lanes.  Pair form: reversible, at most two reactant and two product units
+// (2 A counts as A + A); off holds the byte offsets 8 k of the species of the two reactant and two
+// product slots, 8 nsp (the null species) in an unused second slot.
+struct PairBlock {
+    double lnA[64], beta[64], EaR[64];
+    int4 off[64];
+};
+
 // Device view of a mechanism.
 struct DevMech {
     int nsp, nrxn, N, n_eff;
-    double R;            // J/(mol K)
+    int n_gen;           // stored reactions [0, n_gen) have another form, the rest are pair-form
+    int n_fall;          // pair-form reactions [0, n_fall) are third-body or fall-off reactions
+    double R, invR;      // J/(mol K)
     double ln_p0_R;      // ln(p0 / R), so ln(p0/(R T)) = ln_p0_R - ln T
-    // species block, [3 + kThermoCoef][nsp]: W, 1/W, Tmid, then the NASA-7 derived coefficients;
-    // per range r (0 low, 1 high) at thermo offset 21*r:
-    //   cp/R   : c0..c4           (a1, a2, a3, a4, a5)
-    //   H/(RT) : c5..c10          (a1, a2/2, a3/3, a4/4, a5/5, a6)
-    //   S/R    : c11..c16         (a1 [ln T], a2, a3/2, a4/3, a5/4, a7)
-    //   dcp/dT : c17..c20         (a2, 2 a3, 3 a4, 4 a5)
+    // species block, [3 + kThermoCoef][nsp]: W, 1/W, Tmid, then the NASA-7 coefficients a1..a7 of
+    // the low and of the high range
     const double *spd;
     const RxnRec *rx;
+    const PairBlock *pair;       // stored reactions n_gen.. in pair form
     const FallRec *fall;
     const EffRec *eff;
     const int *orig_index;       // file order of each stored reaction
@@ -75,7 +83,7 @@ struct DevMech {
     __host__ __device__ const double *thermo() const { return spd + 3 * nsp; }
 };
 
-constexpr int kThermoCoef = 42;
+constexpr int kThermoCoef = 14;
 
 struct HostMech {
     int nsp = 0, nrxn = 0, nel = 0;

@@ -20,6 +20,7 @@
 #include "ck_internal.h"
 #include "kinetics.h"
 #include "launch.h"
+#include "reactions.h"
 
 extern "C" __device__ unsigned long long __ockl_wfred_max_u64(unsigned long long);
 extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
@@ -39,37 +40,37 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
     return __hiloint2double(hi, lo);
 }
 
-// LDS layout of one workgroup (doubles); WIN = Jacobian columns staged per window:
-//   C[ns+1] G[ns] H[ns] WD[ns] | IW[128] | VX[128] | RED[16] | PB[2][128] BS[128] XS[128] |
-//   JC[ns * ldj + 128] TB[ns] DWT[ns] TROW[ns + 128]
-struct Lds {
-    double *C, *G, *H, *WD, *IW, *VX, *RED, *PB, *BS, *XS, *JC, *TB, *DWT, *TROW;
+// LDS layout of one workgroup (doubles), ns1 = ns + 1 (a null species closes every array);
+// WIN = Jacobian columns staged per window:
+//   C G H WD [ns1] | IW[128] | VX[128] | RED[16] | PB[2][128] BS[128] XS[128] |
+//   JC[ns1 * ldj + 128] TB DWT HC [ns1] TROW[ns + 128]
+struct Lds : RxArrays {
+    double *IW, *VX, *RED, *PB, *BS, *XS, *TROW;
     double *rows;   // this workgroup's park slice (global memory), or null
     // half-row kernel only: per-row chain-rule scalars and pivot orders, [128] each
-    double *RA, *RB, *RC, *RJ;
+    double *RA, *RB, *RC;
     int *ORD;
-    int ldj;
 };
 
 __host__ __device__ inline int ldj_of(int win) { return win | 1; }
 // JC region: the staged d wdot/dC window, or at least jc_min doubles (the tile kernel reuses the
 // region as scratch of its blocked elimination)
 __host__ __device__ inline size_t jc_doubles(int ns, int win, size_t jc_min) {
-    const size_t j = size_t(ns) * ldj_of(win) + 128;
+    const size_t j = size_t(ns + 1) * ldj_of(win) + 128;
     return j > jc_min ? j : jc_min;
 }
 __host__ __device__ inline size_t lds_doubles(int ns, int win, bool half = false, size_t jc_min = 0) {
-    return size_t(ns + 1) + 3 * size_t(ns) + 128 + 128 + 16 + 2 * 128 + 128 + 128 + jc_doubles(ns, win, jc_min) +
-           2 * size_t(ns) + size_t(ns) + 128 + (half ? 4 * 128 + 64 : 0);
+    return 4 * size_t(ns + 1) + 128 + 128 + 16 + 2 * 128 + 128 + 128 + jc_doubles(ns, win, jc_min) +
+           3 * size_t(ns + 1) + size_t(ns) + 128 + (half ? 3 * 128 + 64 : 0);
 }
 
 __device__ __forceinline__ Lds carve(double *b, int ns, int win, bool half = false, size_t jc_min = 0) {
     Lds L;
     L.ldj = ldj_of(win);
     L.C = b; b += ns + 1;
-    L.G = b; b += ns;
-    L.H = b; b += ns;
-    L.WD = b; b += ns;
+    L.G = b; b += ns + 1;
+    L.H = b; b += ns + 1;
+    L.WD = b; b += ns + 1;
     L.IW = b; b += 128;
     L.VX = b; b += 128;
     L.RED = b; b += 16;
@@ -77,17 +78,17 @@ __device__ __forceinline__ Lds carve(double *b, int ns, int win, bool half = fal
     L.BS = b; b += 128;
     L.XS = b; b += 128;
     L.JC = b; b += jc_doubles(ns, win, jc_min);
-    L.TB = b; b += ns;
-    L.DWT = b; b += ns;
+    L.TB = b; b += ns + 1;
+    L.DWT = b; b += ns + 1;
+    L.HC = b; b += ns + 1;
     L.TROW = b; b += ns + 128;
     L.rows = nullptr;
-    L.RA = L.RB = L.RC = L.RJ = nullptr;
+    L.RA = L.RB = L.RC = nullptr;
     L.ORD = nullptr;
     if (half) {
         L.RA = b; b += 128;
         L.RB = b; b += 128;
         L.RC = b; b += 128;
-        L.RJ = b; b += 128;
         L.ORD = reinterpret_cast<int *>(b);
     }
     return L;
@@ -110,6 +111,25 @@ struct Grp {
         for (int w = 1; w < W; w++) t += red[w];
         __syncthreads();
         return t;
+    }
+    // two sums with one exchange
+    __device__ static __forceinline__ void sum2(double a, double b, double *red, double &sa, double &sb) {
+        sa = __ockl_wfred_add_f64(a);
+        sb = __ockl_wfred_add_f64(b);
+        if (W == 1) return;
+        if (lane() == 0) {
+            red[2 * wave()] = sa;
+            red[2 * wave() + 1] = sb;
+        }
+        __syncthreads();
+        sa = red[0];
+        sb = red[1];
+#pragma unroll
+        for (int w = 1; w < W; w++) {
+            sa += red[2 * w];
+            sb += red[2 * w + 1];
+        }
+        __syncthreads();
     }
     // value of thread src (src uniform)
     __device__ static __forceinline__ double bcast(double v, int src, double *slot) {
@@ -153,12 +173,17 @@ __device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L, int tid
         L.VX[e] = 0.0;
     }
     for (int e = tid; e < M.nsp + 128; e += nthreads) L.TROW[e] = 0.0;
+    if (tid == 0) {
+        L.C[M.nsp] = 1.0;
+        L.G[M.nsp] = 0.0;
+        L.H[M.nsp] = 0.0;
+    }
     __syncthreads();
 }
 
 struct Mix {
     TPow t;
-    double rho, Wbar, Ctot, cpm, cp, h, dcp;
+    double rho, invrho, Wbar, Ctot, cpm, cp, h, dcp, W;
 };
 
 __device__ __forceinline__ int species_of(int tid, int ns) { return (tid >= 1 && tid <= ns) ? tid - 1 : -1; }
@@ -168,126 +193,50 @@ template <int W, bool JAC>
 __device__ __forceinline__ void species_pass(const DevMech &M, double y, double P, const Lds &L, Mix &x) {
     using G = Grp<W>;
     const int ns = M.nsp, tid = G::tid();
-    const int k = species_of(tid, ns);
+    const bool valid = species_of(tid, ns) >= 0;
+    const int k = min(max(tid - 1, 0), ns - 1);
     const double T = G::bcast(y, 0, L.RED + 8);
+    const Nasa co = species_coef(M, k, T);
+    x.W = M.W()[k];
+    const double z = valid ? y * M.invW()[k] : 0.0;
     x.t = tpow(T);
-    const double S = G::sum(k >= 0 ? y * M.invW()[k] : 0.0, L.RED);
-    x.rho = P / (M.R * T * S);
-    x.Wbar = 1.0 / S;
-    x.Ctot = P * x.t.invT / M.R;
-    double cpp = 0.0;
-    if (k >= 0) {
-        L.C[k] = x.rho * y * M.invW()[k];
-        const Thermo th = species_thermo(M, k, x.t);
-        L.G[k] = th.h - th.s;
-        L.H[k] = th.h;
+    const Thermo th = species_thermo(M, co, x.t);
+    double S, cps;
+    G::sum2(z, z * th.cp, L.RED, S, cps);
+    x.cpm = cps * M.R;
+    x.Wbar = ck_rcp(S);
+    x.Ctot = P * x.t.invT * M.invR;
+    x.rho = x.Ctot * x.Wbar;
+    x.invrho = ck_rcp(x.rho);
+    x.cp = valid ? th.cp : 0.0;
+    x.h = valid ? th.h : 0.0;
+    x.dcp = valid ? th.dcp : 0.0;
+    if (valid) {
+        L.C[k] = x.rho * z;
+        L.G[k] = th.g;
         L.WD[k] = 0.0;
-        x.cp = th.cp;
-        x.h = th.h;
-        x.dcp = th.dcp;
-        cpp = y * th.cp * M.invW()[k];
-    } else {
-        x.cp = x.h = x.dcp = 0.0;
-    }
-    x.cpm = G::sum(cpp, L.RED) * M.R;
-    if (JAC)
-        for (int e = tid; e < ns; e += G::T) {
-            L.TB[e] = 0.0;
-            L.DWT[e] = 0.0;
+        if (JAC) {
+            L.H[k] = th.h - 1.0;
+            L.TB[k] = 0.0;
+            L.DWT[k] = 0.0;
+            L.HC[k] = 0.0;
         }
+    }
     __syncthreads();
 }
 
-// Rates of progress into WD (FIRST window only) and d wdot/dC for columns [c0, c0 + win) into JC.
-// The column scatter of a reaction needs c k_f, c k_r and R_net dc/d[M] besides the concentrations:
-// mode 1 stores them in this thread's column of `cache` (entry (3 it + v) * T for the thread's it-th
-// reaction), mode 2 reads them back instead of evaluating the rate constants again.
-template <int W, bool JAC>
-__device__ __forceinline__ void reaction_pass(const DevMech &M, const Lds &L, const TPow &t, double Ctot, int c0, int win,
-                                              bool first, double *cache = nullptr, int mode = 0) {
+// d wdot/dC for the columns [c0, c0 + win) into JC; the first window (mode kRates / kRatesKeep) also
+// fills the per-species accumulators.  Zeroes JC first; the caller's LDS reads of it are done.
+template <int W>
+__device__ __forceinline__ void jacobian_window(const DevMech &M, const Lds &L, const Mix &x, int c0, int win,
+                                                RxMode mode, double *keep) {
     using G = Grp<W>;
-    const int nr = M.nrxn, ns = M.nsp, tid = G::tid();
-    if (JAC) {
-        const int tot = ns * L.ldj;
-        for (int e = tid; e < tot; e += G::T) L.JC[e] = 0.0;
-        __syncthreads();
-    }
-    auto Cg = [&](int k) { return L.C[k]; };
-    auto Gg = [&](int k) { return L.G[k]; };
-    auto Hg = [&](int k) { return L.H[k]; };
-    int it = 0;
-    for (int i = tid; i < nr; i += G::T, it++) {
-        const RxnRec R = M.rx[i];
-        const int nmax = __builtin_amdgcn_readfirstlane(R.blk_slots);
-        Slots S;
-        load_slots(R, Cg, S, nmax);
-        double ckf, ckr, rdm;
-        if (JAC && mode == 2) {
-            ckf = cache[(3 * it) * G::T];
-            ckr = cache[(3 * it + 1) * G::T];
-            rdm = cache[(3 * it + 2) * G::T];
-        } else {
-            Rate q;
-            reaction_rate<JAC>(M, R, S, nmax, t, Ctot, Cg, Gg, Hg, q);
-            const double Rn = q.kf * q.pf - q.kr * q.pr;
-            if (first) {
-                const double qi = q.c * Rn;
-#pragma unroll
-                for (int s = 0; s < kMaxSlots; s++) {
-                    if (s >= nmax) break;
-                    if (S.sgn[s] != 0) atomicAdd(&L.WD[S.sp[s]], (S.sgn[s] * S.nu[s]) * qi);
-                }
-            }
-            ckf = q.c * q.kf;
-            ckr = q.c * q.kr;
-            rdm = JAC ? Rn * q.dcdM : 0.0;
-            if (JAC && first) {
-                const double dqT = q.c * (q.kf * q.dlnkf * q.pf - q.kr * q.dlnkr * q.pr) + Rn * q.dcdT;
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] == 0) continue;
-                    const double v = S.sgn[a] * S.nu[a];
-                    atomicAdd(&L.DWT[S.sp[a]], v * dqT);
-                    if (q.dcdM != 0.0) atomicAdd(&L.TB[S.sp[a]], v * rdm);
-                }
-            }
-            if (JAC && mode == 1) {
-                cache[(3 * it) * G::T] = ckf;
-                cache[(3 * it + 1) * G::T] = ckr;
-                cache[(3 * it + 2) * G::T] = rdm;
-            }
-        }
-        if (JAC) {
-#pragma unroll
-            for (int b = 0; b < kMaxSlots; b++) {
-                if (b >= nmax) break;
-                const int col = S.sp[b] - c0;
-                if (S.sgn[b] == 0 || col < 0 || col >= win) continue;
-                const double d = dprod_slot(S, b, nmax);
-                const double dq = S.sgn[b] < 0 ? ckf * d : -ckr * d;
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] != 0) atomicAdd(&L.JC[S.sp[a] * L.ldj + col], (S.sgn[a] * S.nu[a]) * dq);
-                }
-            }
-            if (rdm != 0.0) {
-                const int eb = R.eff_begin, ec = rx_neff(R.meta);
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] == 0) continue;
-                    const double base = (S.sgn[a] * S.nu[a]) * rdm;
-                    for (int e = 0; e < ec; e++) {
-                        const EffRec E = M.eff[eb + e];
-                        const int col = E.sp - c0;
-                        if (col >= 0 && col < win) atomicAdd(&L.JC[S.sp[a] * L.ldj + col], base * E.am1);
-                    }
-                }
-            }
-        }
-    }
+    const int ns = M.nsp, tid = G::tid();
+    const int tot = ns * L.ldj;
+    for (int e = tid; e < tot; e += G::T) L.JC[e] = 0.0;
+    __syncthreads();
+    const RxScale sc{x.t.invT, x.Wbar * x.invrho, 1.0};
+    ck::reaction_pass<G::T, true>(M, L, x.t, x.Ctot, sc, c0, min(win, ns - c0), mode, keep, tid);
     __syncthreads();
 }
 
@@ -297,95 +246,83 @@ __device__ __forceinline__ double finish_rhs(const DevMech &M, const Lds &L, con
     using G = Grp<W>;
     const int tid = G::tid();
     const int k = species_of(tid, M.nsp);
-    double f = 0.0, qp = 0.0;
-    if (k >= 0) {
-        const double wd = L.WD[k];
-        f = M.W()[k] * wd / x.rho;
-        qp = M.R * x.t.T * x.h * wd;
-    }
-    const double Q = G::sum(qp, L.RED);
-    if (tid == 0) f = -Q / (x.rho * x.cpm);
-    return f;
+    const double wd = k >= 0 ? L.WD[k] : 0.0;
+    const double Q = G::sum(x.h * wd, L.RED) * (M.R * x.t.T);
+    return tid == 0 ? -Q * ck_rcp(x.rho * x.cpm) : x.W * wd * x.invrho;
 }
 
 template <int W>
 __device__ __forceinline__ double rhs(const DevMech &M, const Lds &L, double y, double P) {
     Mix x;
     species_pass<W, false>(M, y, P, L, x);
-    reaction_pass<W, false>(M, L, x.t, x.Ctot, 0, 0, true);
+    ck::reaction_pass<Grp<W>::T, false>(M, L, x.t, x.Ctot, RxScale{0.0, 0.0, 0.0}, 0, 0, kRates, nullptr,
+                                        Grp<W>::tid());
+    __syncthreads();
     const double f = finish_rhs<W>(M, L, x);
     __syncthreads();
     return f;
 }
 
-// f(y) and this thread's row of M = dg I - J in registers (NP columns), d wdot/dC staged in NWIN
-// column windows of width WIN.
-template <int W, int NP, int NWIN, int WIN>
-__device__ __forceinline__ void iteration_rows(const DevMech &M, const Lds &L, double y, double P, double dg, double (&a)[NP],
-                               double &f) {
+// Chain rule from the first window's accumulators: this thread's scalars of its species row and of
+// the temperature row (written to TROW), in the specific mole numbers z = Y / W (ChainIn).
+struct Row {
+    double beta, col0, J00;
+};
+template <int W>
+__device__ __forceinline__ Row chain_rule(const DevMech &M, const Lds &L, const Mix &x, double y, double f) {
     using G = Grp<W>;
+    const int ns = M.nsp, tid = G::tid();
+    const int k = species_of(tid, ns);
+    const bool valid = k >= 0;
+    const double TBk = valid ? L.TB[k] : 0.0, WDk = valid ? L.WD[k] : 0.0, DWTk = valid ? L.DWT[k] : 0.0;
+    ChainIn c;
+    c.rho = x.rho;
+    c.invrho = x.invrho;
+    c.Wbar = x.Wbar;
+    c.invT = x.t.invT;
+    c.R = M.R;
+    c.RT = M.R * x.t.T;
+    c.cpm = x.cpm;
+    double s0, s1, s2, s3;
+    G::sum2(x.h * TBk, x.h * WDk, L.RED, s0, s1);
+    G::sum2(fma(x.cp, WDk, x.h * (x.t.T * DWTk - WDk)), valid ? y * x.dcp * M.invW()[k] : 0.0, L.RED, s2, s3);
+    c.sHB = c.RT * s0;
+    c.sHW = c.RT * s1;
+    c.dQT = M.R * s2;
+    c.sdcp = M.R * s3;
+    c.fT = G::bcast(f, 0, L.RED + 8);
+    if (valid) L.TROW[k] = chain_trow(c, false, L.HC[k], x.cp);
+    Row r;
+    r.beta = TBk;
+    r.col0 = DWTk * x.invrho;
+    r.J00 = chain_J00(c, false);
+    return r;
+}
+
+// f(y) and this thread's row of M = dg I - J in registers (NP columns, one wavefront), d wdot/dC
+// staged whole.
+template <int NP>
+__device__ __forceinline__ void iteration_rows(const DevMech &M, const Lds &L, double y, double P, double dg,
+                                               double (&a)[NP], double &f) {
+    using G = Grp<1>;
     const int ns = M.nsp;
     Mix x;
-    species_pass<W, true>(M, y, P, L, x);
+    species_pass<1, true>(M, y, P, L, x);
     const int tid = G::tid();
     const int k = species_of(tid, ns);
     const bool valid = k >= 0;
-    double jcc = 0.0, colH = 0.0;
-#pragma unroll
-    for (int j = 0; j < NP; j++) a[j] = 0.0;
-#pragma unroll
-    for (int w = 0; w < NWIN; w++) {
-        const int c0 = w * WIN;
-        reaction_pass<W, true>(M, L, x.t, x.Ctot, c0, WIN, w == 0);
-        if (w == 0) f = finish_rhs<W>(M, L, x);
-        if (valid) {
-            const double *row = &L.JC[k * L.ldj];
-#pragma unroll
-            for (int j = 0; j < WIN; j++) {
-                if (c0 + j >= ns) break;
-                const double v = row[j];
-                a[1 + c0 + j] = v;                   // raw d wdot_k / dC_(c0+j) for now
-                jcc += v * L.C[c0 + j];
-            }
-            if (k >= c0 && k < c0 + WIN)
-                for (int r = 0; r < ns; r++) colH += L.H[r] * L.JC[r * L.ldj + (k - c0)];
-        }
-        __syncthreads();
-    }
-    // chain rule (as in the wavefront kernels)
-    const double T = x.t.T, RT = M.R * T;
-    double resid = 0.0, ra = 0.0, col0 = 0.0, TBk = 0.0, WDk = 0.0, DWTk = 0.0;
-    if (valid) {
-        TBk = L.TB[k];
-        WDk = L.WD[k];
-        DWTk = L.DWT[k];
-        jcc += TBk * x.Ctot;
-        colH *= RT;
-        resid = WDk - jcc;
-        ra = M.W()[k] * x.Wbar * resid / x.rho;
-        col0 = (M.W()[k] / x.rho) * (DWTk + resid * x.t.invT);
-    }
-    const double Hk = RT * x.h;
-    const double sumHTB = G::sum(valid ? Hk * TBk : 0.0, L.RED);
-    const double sumHJCC = G::sum(valid ? Hk * jcc : 0.0, L.RED);
-    const double dQT = G::sum(valid ? M.R * x.cp * WDk + Hk * (DWTk - jcc * x.t.invT) : 0.0, L.RED);
-    const double sdcp = G::sum(valid ? y * M.R * x.dcp * M.invW()[k] : 0.0, L.RED);
-    const double fT = G::bcast(f, 0, L.RED + 8);
-    const double D = x.rho * x.cpm;
-    if (valid) {
-        const double dQ = M.invW()[k] * (x.rho * (colH + sumHTB) - x.Wbar * sumHJCC);
-        const double dD = x.rho * M.invW()[k] * (M.R * x.cp - x.cpm * x.Wbar);
-        L.TROW[k] = -(dQ + fT * dD) / D;
-    }
-    const double J00 = -(dQT + fT * (-x.rho * x.cpm * x.t.invT + x.rho * sdcp)) / D;
+    jacobian_window<1>(M, L, x, 0, ns, kRates, nullptr);
+    f = finish_rhs<1>(M, L, x);
+    const Row r = chain_rule<1>(M, L, x, y, f);
     __syncthreads();
-    const double alpha = valid ? M.W()[k] : 0.0;
-    const double beta = valid ? M.W()[k] * TBk + ra : 0.0;
-    a[0] = (tid == 0 ? dg : 0.0) - (tid == 0 ? J00 : col0);
+    const double alpha = valid ? x.W : 0.0;
+    const double beta = alpha * r.beta;
+    const double *row = tid == 0 ? L.TROW : (valid ? &L.JC[k * L.ldj] : L.TROW + ns);
+    a[0] = tid == 0 ? dg - r.J00 : -alpha * r.col0;
 #pragma unroll
     for (int j = 1; j < NP; j++) {
-        const double Jv = tid == 0 ? L.TROW[j - 1] : L.IW[j - 1] * (alpha * a[j] + beta);
-        a[j] = (tid == j ? dg : 0.0) - Jv;
+        const double v = j - 1 < ns ? row[j - 1] : 0.0;
+        a[j] = (tid == j ? dg : 0.0) - L.IW[j - 1] * (tid == 0 ? v : alpha * v + beta);
     }
     __syncthreads();
 }
@@ -470,7 +407,8 @@ struct Ros4Coop {
         double a[NP];
         double f;
         const double dg = 1.0 / (Ros4::gamma * h);
-        iteration_rows<W, NP, NWIN, WIN>(M, L, y, P, dg, a, f);
+        static_assert(W == 1, "larger states take the half-row or the tile form");
+        iteration_rows<NP>(M, L, y, P, dg, a, f);
         int ord;
         const bool ok = gj_invert<W, NP>(a, L, ord);
         const double ih = 1.0 / h;
@@ -512,69 +450,38 @@ __device__ __forceinline__ void iteration_rows_half(const DevMech &M, const Lds 
     const int row = tid >> 1, half = tid & 1;       // row mapping
     const int kr = row - 1;                         // species of the row (row 0 is T)
     const bool rvalid = row >= 1 && row <= ns;
-    double colH = 0.0, jcp = 0.0;                   // jcp: this half's part of sum_l JC[kr][l] C_l
+    double J00 = 0.0;
 #pragma unroll
     for (int j = 0; j < H; j++) a[j] = 0.0;
     // the first window's per-reaction scatter scalars, kept for the second in this workgroup's park
     // slice
-    const bool keep = L.rows != nullptr && 3 * ((M.nrxn + G::T - 1) / G::T) <= H;
+    const bool keep = L.rows != nullptr && 3 * rx_blocks(M, G::T) <= H;
     double *cache = keep ? L.rows + opaque(tid) : nullptr;
 #pragma unroll
     for (int w = 0; w < 2; w++) {
         const int c0 = w * H - 1;                   // window w: matrix columns [w H, w H + H)
-        reaction_pass<W, true>(M, L, x.t, x.Ctot, c0, H, w == 0, cache, keep ? (w == 0 ? 1 : 2) : 0);
-        if (w == 0) f = finish_rhs<W>(M, L, x);
+        jacobian_window<W>(M, L, x, c0, H, w == 0 ? (keep ? kRatesKeep : kRates) : (keep ? kScatterKept : kScatter),
+                           cache);
+        if (w == 0) {
+            f = finish_rhs<W>(M, L, x);
+            const Row r = chain_rule<W>(M, L, x, y, f);
+            J00 = r.J00;
+            if (tid < 128) {
+                L.RA[tid] = valid ? x.W : 0.0;
+                L.RB[tid] = valid ? x.W * r.beta : 0.0;
+                L.RC[tid] = valid ? x.W * r.col0 : 0.0;
+            }
+        }
         if (rvalid && half == w) {
             const double *r = &L.JC[kr * L.ldj];
 #pragma unroll
             for (int j = 0; j < H; j++) {
                 const int jc = c0 + j;              // JC column of matrix column w H + j
-                if (jc >= 0 && jc < ns) {
-                    const double v = r[j];
-                    a[j] = v;                       // raw d wdot_kr / dC_jc until the row scalars are known
-                    jcp += v * L.C[jc];
-                }
+                if (jc >= 0 && jc < ns) a[j] = r[j];
             }
         }
-        if (valid && k + 1 >= w * H && k + 1 < w * H + H)
-            for (int r = 0; r < ns; r++) colH += L.H[r] * L.JC[r * L.ldj + (k + 1 - w * H)];
         __syncthreads();
     }
-    const double jrow = jcp + shfl_pair(jcp);
-    if (half == 0 && rvalid) L.RJ[row] = jrow;
-    __syncthreads();
-    // chain rule in the component mapping (as iteration_rows)
-    const double T = x.t.T, RT = M.R * T;
-    double jcc = 0.0, resid = 0.0, ra = 0.0, col0 = 0.0, TBk = 0.0, WDk = 0.0, DWTk = 0.0;
-    if (valid) {
-        TBk = L.TB[k];
-        WDk = L.WD[k];
-        DWTk = L.DWT[k];
-        jcc = L.RJ[tid] + TBk * x.Ctot;
-        colH *= RT;
-        resid = WDk - jcc;
-        ra = M.W()[k] * x.Wbar * resid / x.rho;
-        col0 = (M.W()[k] / x.rho) * (DWTk + resid * x.t.invT);
-    }
-    const double Hk = RT * x.h;
-    const double sumHTB = G::sum(valid ? Hk * TBk : 0.0, L.RED);
-    const double sumHJCC = G::sum(valid ? Hk * jcc : 0.0, L.RED);
-    const double dQT = G::sum(valid ? M.R * x.cp * WDk + Hk * (DWTk - jcc * x.t.invT) : 0.0, L.RED);
-    const double sdcp = G::sum(valid ? y * M.R * x.dcp * M.invW()[k] : 0.0, L.RED);
-    const double fT = G::bcast(f, 0, L.RED + 8);
-    const double D = x.rho * x.cpm;
-    if (valid) {
-        const double dQ = M.invW()[k] * (x.rho * (colH + sumHTB) - x.Wbar * sumHJCC);
-        const double dD = x.rho * M.invW()[k] * (M.R * x.cp - x.cpm * x.Wbar);
-        L.TROW[k] = -(dQ + fT * dD) / D;
-    }
-    if (tid < 128) {
-        L.RA[tid] = valid ? M.W()[k] : 0.0;
-        L.RB[tid] = valid ? M.W()[k] * TBk + ra : 0.0;
-        L.RC[tid] = valid ? col0 : 0.0;
-    }
-    const double J00 = -(dQT + fT * (-x.rho * x.cpm * x.t.invT + x.rho * sdcp)) / D;
-    __syncthreads();
     const double alpha = row < 128 ? L.RA[row] : 0.0;
     const double beta = row < 128 ? L.RB[row] : 0.0;
     const double c0r = row < 128 ? L.RC[row] : 0.0;
@@ -585,7 +492,7 @@ __device__ __forceinline__ void iteration_rows_half(const DevMech &M, const Lds 
         if (c == 0) {
             v = (row == 0 ? dg : 0.0) - (row == 0 ? J00 : c0r);
         } else {
-            const double Jv = row == 0 ? L.TROW[c - 1] : L.IW[c - 1] * (alpha * a[j] + beta);
+            const double Jv = L.IW[c - 1] * (row == 0 ? L.TROW[c - 1] : alpha * a[j] + beta);
             v = (row == c ? dg : 0.0) - Jv;
         }
         a[j] = v;
@@ -799,7 +706,7 @@ __device__ __forceinline__ double row16_sum(double v) {
 }
 
 // f(y) and this wavefront's tiles of M = dg I - J; d wdot/dC staged in two column windows (as
-// iteration_rows_half, whose row-pair mapping still forms the row sums sum_l JC[k][l] C_l).
+// iteration_rows_half).
 template <int NP, bool F32L = false>
 __device__ __forceinline__ void iteration_tiles(const DevMech &M, const Lds &L, double y, double P, double dg,
                                                 d4 (&m)[TileGeom<NP>::RW][TileGeom<NP>::TR], double &f) {
@@ -811,38 +718,27 @@ __device__ __forceinline__ void iteration_tiles(const DevMech &M, const Lds &L, 
     const int tid = G::tid();
     const int k = species_of(tid, ns);              // component mapping
     const bool valid = k >= 0;
-    const int row = tid >> 1, half = tid & 1;       // row-pair mapping (row sums)
-    const int kr = row - 1;
-    const bool rvalid = row >= 1 && row <= ns;
     const int wv = G::wave(), ln = G::lane(), g = ln >> 4, c16 = ln & 15;
-    double colH = 0.0, jcp = 0.0;
+    double J00 = 0.0;
 #pragma unroll
     for (int i = 0; i < RW; i++)
 #pragma unroll
         for (int J = 0; J < TR; J++) m[i][J] = d4{0.0, 0.0, 0.0, 0.0};
-    const bool keep = L.rows != nullptr && 3 * ((M.nrxn + G::T - 1) / G::T) <= H;
+    const bool keep = L.rows != nullptr && 3 * rx_blocks(M, G::T) <= H;
     double *cache = keep ? L.rows + opaque(tid) : nullptr;
-    // column sums sum_r H_r d wdot_r / dC_col accumulate in VX from the tiles; hr = H of the rows
-    // this lane holds (0 for the temperature row and padding)
-    if (tid < 128) L.VX[tid] = 0.0;
-    double hr[RW][4];
-#pragma unroll
-    for (int i = 0; i < RW; i++)
-#pragma unroll
-        for (int v = 0; v < 4; v++) {
-            const int r = tile_row<F32L>(TileGeom<NP>::tile_of(wv, i), g, v);
-            hr[i][v] = (r >= 1 && r <= ns) ? L.H[r - 1] : 0.0;
-        }
 #pragma unroll
     for (int w = 0; w < 2; w++) {
         const int c0 = w * H - 1;                   // window w: matrix columns [w H, w H + H)
-        reaction_pass<W, true>(M, L, x.t, x.Ctot, c0, H, w == 0, cache, keep ? (w == 0 ? 1 : 2) : 0);
-        if (w == 0) f = finish_rhs<W>(M, L, x);
-        if (rvalid && half == w) {
-            const double *r = &L.JC[kr * L.ldj];
-            for (int j = 0; j < H; j++) {
-                const int jc = c0 + j;
-                if (jc >= 0 && jc < ns) jcp += r[j] * L.C[jc];
+        jacobian_window<W>(M, L, x, c0, H, w == 0 ? (keep ? kRatesKeep : kRates) : (keep ? kScatterKept : kScatter),
+                           cache);
+        if (w == 0) {
+            f = finish_rhs<W>(M, L, x);
+            const Row r = chain_rule<W>(M, L, x, y, f);
+            J00 = r.J00;
+            if (tid < 128) {
+                L.RA[tid] = valid ? x.W : 0.0;
+                L.RB[tid] = valid ? x.W * r.beta : 0.0;
+                L.RC[tid] = valid ? x.W * r.col0 : 0.0;
             }
         }
         // raw window entries d wdot_(r-1) / dC_(col-1) into this wavefront's tiles
@@ -860,52 +756,10 @@ __device__ __forceinline__ void iteration_tiles(const DevMech &M, const Lds &L, 
                     const int r = tile_row<F32L>(I, g, v);
                     if (cin && r >= 1 && r <= ns) m[i][J][v] = L.JC[(r - 1) * L.ldj + (col - w * H)];
                 }
-                if (cin) {
-                    double part = 0.0;
-#pragma unroll
-                    for (int v = 0; v < 4; v++) part = fma(hr[i][v], m[i][J][v], part);
-                    atomicAdd(&L.VX[col], part);
-                }
             }
         }
         __syncthreads();
     }
-    if (valid) colH = L.VX[k + 1];
-    const double jrow = jcp + shfl_pair(jcp);
-    if (half == 0 && rvalid) L.RJ[row] = jrow;
-    __syncthreads();
-    // chain rule in the component mapping (as iteration_rows)
-    const double T = x.t.T, RT = M.R * T;
-    double jcc = 0.0, resid = 0.0, ra = 0.0, col0 = 0.0, TBk = 0.0, WDk = 0.0, DWTk = 0.0;
-    if (valid) {
-        TBk = L.TB[k];
-        WDk = L.WD[k];
-        DWTk = L.DWT[k];
-        jcc = L.RJ[tid] + TBk * x.Ctot;
-        colH *= RT;
-        resid = WDk - jcc;
-        ra = M.W()[k] * x.Wbar * resid / x.rho;
-        col0 = (M.W()[k] / x.rho) * (DWTk + resid * x.t.invT);
-    }
-    const double Hk = RT * x.h;
-    const double sumHTB = G::sum(valid ? Hk * TBk : 0.0, L.RED);
-    const double sumHJCC = G::sum(valid ? Hk * jcc : 0.0, L.RED);
-    const double dQT = G::sum(valid ? M.R * x.cp * WDk + Hk * (DWTk - jcc * x.t.invT) : 0.0, L.RED);
-    const double sdcp = G::sum(valid ? y * M.R * x.dcp * M.invW()[k] : 0.0, L.RED);
-    const double fT = G::bcast(f, 0, L.RED + 8);
-    const double D = x.rho * x.cpm;
-    if (valid) {
-        const double dQ = M.invW()[k] * (x.rho * (colH + sumHTB) - x.Wbar * sumHJCC);
-        const double dD = x.rho * M.invW()[k] * (M.R * x.cp - x.cpm * x.Wbar);
-        L.TROW[k] = -(dQ + fT * dD) / D;
-    }
-    if (tid < 128) {
-        L.RA[tid] = valid ? M.W()[k] : 0.0;
-        L.RB[tid] = valid ? M.W()[k] * TBk + ra : 0.0;
-        L.RC[tid] = valid ? col0 : 0.0;
-    }
-    const double J00 = -(dQT + fT * (-x.rho * x.cpm * x.t.invT + x.rho * sdcp)) / D;
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < RW; i++) {
         const int I = TileGeom<NP>::tile_of(wv, i);
@@ -919,8 +773,7 @@ __device__ __forceinline__ void iteration_tiles(const DevMech &M, const Lds &L, 
                 const int col = 16 * J + c16;
                 double Jv;
                 if (col == 0) Jv = r == 0 ? J00 : c0r;
-                else if (r == 0) Jv = L.TROW[col - 1];
-                else Jv = L.IW[col - 1] * (alpha * m[i][J][v] + beta);
+                else Jv = L.IW[col - 1] * (r == 0 ? L.TROW[col - 1] : alpha * m[i][J][v] + beta);
                 m[i][J][v] = (r == col ? dg : 0.0) - Jv;
             }
         }

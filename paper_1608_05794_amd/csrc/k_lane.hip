@@ -66,7 +66,7 @@ __device__ void rhs_lane(const DevMech &M, const YV &y, double P, SV f, SV w, co
         const double Ck = rho * y[1 + k] * M.invW()[k];
         w[L.C + k] = Ck;
         const Thermo th = species_thermo(M, k, t);
-        w[L.G + k] = th.h - th.s;
+        w[L.G + k] = th.g;
         w[L.H + k] = th.h;
         w[L.CP + k] = th.cp;
         w[L.WD + k] = 0.0;
@@ -75,7 +75,7 @@ __device__ void rhs_lane(const DevMech &M, const YV &y, double P, SV f, SV w, co
     cpm *= M.R;
     auto Cg = [&](int k) { return w[L.C + k]; };
     auto Gg = [&](int k) { return w[L.G + k]; };
-    auto Hg = [&](int k) { return w[L.H + k]; };
+    auto Hg = [&](int k) { return w[L.H + k] - 1.0; };
     for (int i = 0; i < M.nrxn; i++) {
         const RxnRec R = M.rx[i];
         Slots S;
@@ -113,7 +113,7 @@ __device__ void jac_lane(const DevMech &M, const YV &y, double P, SV J, SV f, SV
     for (int k = 0; k < ns; k++) w[L.DWT + k] = 0.0;
     auto Cg = [&](int k) { return w[L.C + k]; };
     auto Gg = [&](int k) { return w[L.G + k]; };
-    auto Hg = [&](int k) { return w[L.H + k]; };
+    auto Hg = [&](int k) { return w[L.H + k] - 1.0; };
     for (int i = 0; i < nr; i++) {
         const RxnRec R = M.rx[i];
         Slots S;

@@ -14,6 +14,7 @@
 #include "ck_internal.h"
 #include "kinetics.h"
 #include "launch.h"
+#include "reactions.h"
 
 extern "C" __device__ unsigned long long __ockl_wfred_max_u64(unsigned long long);
 extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
@@ -44,23 +45,22 @@ __device__ __forceinline__ double bcast(double v, int src) {
 __device__ __forceinline__ bool wave_all(bool v) { return __ballot(!v) == 0ull; }
 
 // ---------------------------------------------------------------------------------------
-// LDS layout of one wavefront (doubles):
-//   C[ns+1] G[ns] H[ns] WD[ns] | IW[64] (1/W_j padded with zeros) | VX[64] (broadcast scratch) |
-//   JC[ns*ldj + 64] TB[ns] DWT[ns] TROW[ns + 64]   (Jacobian kernels only)
+// LDS layout of one wavefront (doubles), ns1 = ns + 1 (a null species closes every array):
+//   C G H WD [ns1] | IW[64] (1/W_j padded with zeros) VX[64] (broadcast scratch): FP32 mode only |
+//   TB DWT HC [ns1] TROW[ns + 64] JC[ns1*ldj + 64]   (Jacobian kernels only)
 // JC holds d wdot / dC for a window of `win` consecutive columns (all ns columns when the
 // Jacobian is staged in one piece), leading dimension ldj = win | 1.
 // ---------------------------------------------------------------------------------------
-struct Lds {
-    double *C, *G, *H, *WD, *IW, *VX, *JC, *TB, *DWT, *TROW;
+struct Lds : RxArrays {
+    double *IW, *VX, *TROW;
     double *park;   // this wavefront's slice of the workspace for parked LU rows ([NP][64]), or null
-    int ldj;
     int cv;         // 0: constant pressure (p = pressure); 1: constant volume (p = density)
 };
 
 __host__ __device__ inline int ldj_of(int win) { return win | 1; }
 __host__ __device__ inline size_t lds_doubles(int ns, bool jac, int win) {
-    size_t d = size_t(ns + 1) + 3 * size_t(ns) + 128;
-    if (jac) d += size_t(ns) * ldj_of(win) + 64 + 2 * size_t(ns) + size_t(ns) + 64;
+    size_t d = 4 * size_t(ns + 1) + 128;
+    if (jac) d += 3 * size_t(ns + 1) + size_t(ns) + 64 + size_t(ns + 1) * ldj_of(win) + 64;
     return d;
 }
 __host__ __device__ inline size_t lds_doubles(int ns, bool jac) { return lds_doubles(ns, jac, ns); }
@@ -69,18 +69,19 @@ __device__ __forceinline__ Lds carve(double *b, int ns, bool jac, int win) {
     Lds L;
     L.ldj = ldj_of(win);
     L.C = b; b += ns + 1;
-    L.G = b; b += ns;
-    L.H = b; b += ns;
-    L.WD = b; b += ns;
+    L.G = b; b += ns + 1;
+    L.H = b; b += ns + 1;
+    L.WD = b; b += ns + 1;
     L.IW = b; b += 64;
     L.VX = b; b += 64;
     if (jac) {
-        L.JC = b; b += size_t(ns) * L.ldj + 64;
-        L.TB = b; b += ns;
-        L.DWT = b; b += ns;
-        L.TROW = b;
+        L.TB = b; b += ns + 1;
+        L.DWT = b; b += ns + 1;
+        L.HC = b; b += ns + 1;
+        L.TROW = b; b += ns + 64;
+        L.JC = b;
     } else {
-        L.JC = L.TB = L.DWT = L.TROW = nullptr;
+        L.JC = L.TB = L.DWT = L.HC = L.TROW = nullptr;
     }
     L.park = nullptr;
     L.cv = 0;
@@ -91,10 +92,15 @@ __device__ __forceinline__ Lds carve(double *b, int ns, bool jac) { return carve
 __device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L) {
     const int l = lane_id();
     L.IW[l] = l < M.nsp ? M.invW()[l] : 0.0;
-    L.C[M.nsp] = 1.0;
+    if (l == 0) {
+        L.C[M.nsp] = 1.0;
+        L.G[M.nsp] = 0.0;
+        L.H[M.nsp] = 0.0;
+    }
     if (L.TROW) {
         for (int e = l; e < M.nsp + 64; e += 64) L.TROW[e] = 0.0;
-        for (int e = M.nsp * L.ldj + l; e < M.nsp * L.ldj + 64; e += 64) L.JC[e] = 0.0;
+        // columns past the staged rows of JC are read (and dropped) by lanes without a species
+        for (int e = (M.nsp + 1) * L.ldj + l; e < (M.nsp + 1) * L.ldj + 64; e += 64) L.JC[e] = 0.0;
     }
     __syncthreads();
 }
@@ -102,198 +108,138 @@ __device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L) {
 template <int RPL>
 struct Mix {
     TPow t;
-    double rho, Wbar, Ctot, cpm;
-    double cp[RPL], h[RPL], dcp[RPL];
+    double rho, invrho, Wbar, Ctot, cpm;
+    double W[RPL], cp[RPL], h[RPL], dcp[RPL];
+    bool valid[RPL];    // this register slot holds a species (slot 0 of lane 0 is T)
+    int k[RPL];         // its index, clamped into range
 };
 
-// Species index held by register slot c of this lane, or -1 (slot 0 of lane 0 is T).
-__device__ __forceinline__ int slot_species(int c, int ns, int lane) {
-    const int i = lane + 64 * c;
-    return (i >= 1 && i <= ns) ? i - 1 : -1;
-}
-
-// Mixture state and per-species thermodynamics (Section 3: ideal gas, Eq. tfits).
-template <int RPL, bool JAC, bool ZERO_JC = true>
+// Mixture state and per-species thermodynamics (Section 3: ideal gas, Eq. tfits).  Every lane reads
+// an in-range species, so the loads are issued together and only the stores are masked.
+template <int RPL, bool JAC>
 __device__ __forceinline__ void species_pass(const DevMech &M, const double (&y)[RPL], double P, const Lds &L, Mix<RPL> &x) {
     const int ns = M.nsp;
     const int lane = lane_fresh();
     const double T = bcast(y[0], 0);
-    x.t = tpow(T);
-    double sy = 0.0;
+    double z[RPL];
+    Nasa co[RPL];
+    double sz = 0.0;
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
-        const int k = slot_species(c, ns, lane);
-        if (k >= 0) sy += y[c] * M.invW()[k];
+        const int i = lane + 64 * c;
+        x.valid[c] = i >= 1 && i <= ns;
+        x.k[c] = min(max(i - 1, 0), ns - 1);
+        co[c] = species_coef(M, x.k[c], T);
+        x.W[c] = M.W()[x.k[c]];
+        z[c] = x.valid[c] ? y[c] * M.invW()[x.k[c]] : 0.0;
+        sz += z[c];
     }
-    const double S = wsum(sy);
+    x.t = tpow(T);
+    const double S = wsum(sz);          // sum_k Y_k / W_k
+    x.Wbar = ck_rcp(S);
     if (L.cv) {   // constant volume: P holds the (fixed) density
         x.rho = P;
         x.Ctot = P * S;
     } else {
-        x.rho = P / (M.R * T * S);
-        x.Ctot = P * x.t.invT / M.R;
+        x.Ctot = P * x.t.invT * M.invR;
+        x.rho = x.Ctot * x.Wbar;
     }
-    x.Wbar = 1.0 / S;
+    x.invrho = ck_rcp(x.rho);
     double cpp = 0.0;
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
-        const int k = slot_species(c, ns, lane);
-        if (k >= 0) {
-            L.C[k] = x.rho * y[c] * M.invW()[k];
-            const Thermo th = species_thermo(M, k, x.t);
-            L.G[k] = th.h - th.s;
-            L.H[k] = th.h;
+        const Thermo th = species_thermo(M, co[c], x.t);
+        x.cp[c] = th.cp;
+        x.h[c] = th.h;
+        if (JAC) x.dcp[c] = th.dcp;
+        if (x.valid[c]) {
+            const int k = x.k[c];
+            L.C[k] = x.rho * z[c];
+            L.G[k] = th.g;
             L.WD[k] = 0.0;
-            x.cp[c] = th.cp;
-            x.h[c] = th.h;
-            x.dcp[c] = th.dcp;
-            cpp += y[c] * th.cp * M.invW()[k];
-        } else {
-            x.cp[c] = x.h[c] = x.dcp[c] = 0.0;
+            if (JAC) {
+                L.H[k] = th.h - 1.0;
+                L.TB[k] = 0.0;
+                L.DWT[k] = 0.0;
+                L.HC[k] = 0.0;
+            }
         }
+        cpp = fma(z[c], th.cp, cpp);
     }
     x.cpm = wsum(cpp) * M.R;
-    if (JAC) {
-        const int l = lane;
-        const int tot = ns * L.ldj;
-        if (ZERO_JC)
-            for (int e = l; e < tot; e += 64) L.JC[e] = 0.0;
-        for (int e = l; e < ns; e += 64) {
-            L.TB[e] = 0.0;
-            L.DWT[e] = 0.0;
-        }
-    }
     __syncthreads();
 }
 
-// Rates of progress (Eqs. wdot, kfor, krev, kc), scattered into WD; with JAC
-// also d wdot / dC (into JC, and the third-body rank-one part into TB) and
-// d wdot / dT at fixed C (into DWT).  With a column window [c0, c0 + win) only
-// those columns of d wdot / dC are accumulated, and WD, TB and DWT only when
-// `first` is set.
-// Column scatter of reaction i needs three scalars besides the concentrations: c k_f, c k_r and
-// R_net dc/d[M].  mode 1 stores them in this lane's column of `cache` (entry (3 it + v) * 64 for
-// the lane's it-th reaction); mode 2 reads them back instead of evaluating the rate constants, so
-// a later column window costs a record load and the scatter only.
-template <bool JAC>
-__device__ __forceinline__ void reaction_pass(const DevMech &M, const Lds &L, const TPow &t, double Ctot, int c0, int win,
-                              bool first, double *cache = nullptr, int mode = 0) {
-    const int nr = M.nrxn;
-    auto Cg = [&](int k) { return L.C[k]; };
-    auto Gg = [&](int k) { return L.G[k]; };
-    auto Hg = [&](int k) { return L.H[k]; };
-    int it = 0;
-    for (int i = lane_fresh(); i < nr; i += 64, it++) {
-        const RxnRec R = M.rx[i];
-        const int nmax = __builtin_amdgcn_readfirstlane(R.blk_slots);
-        Slots S;
-        load_slots(R, Cg, S, nmax);
-        double ckf, ckr, rdm;
-        if (JAC && mode == 2) {
-            ckf = cache[(3 * it) * 64];
-            ckr = cache[(3 * it + 1) * 64];
-            rdm = cache[(3 * it + 2) * 64];
-        } else {
-            Rate q;
-            reaction_rate<JAC>(M, R, S, nmax, t, Ctot, Cg, Gg, Hg, q);
-            const double Rn = q.kf * q.pf - q.kr * q.pr;
-            if (first) {
-                const double qi = q.c * Rn;
-#pragma unroll
-                for (int s = 0; s < kMaxSlots; s++) {
-                    if (s >= nmax) break;
-                    if (S.sgn[s] != 0) atomicAdd(&L.WD[S.sp[s]], (S.sgn[s] * S.nu[s]) * qi);
-                }
-            }
-            ckf = q.c * q.kf;
-            ckr = q.c * q.kr;
-            rdm = JAC ? Rn * q.dcdM : 0.0;
-            if (JAC && first) {
-                const double dqT = q.c * (q.kf * q.dlnkf * q.pf - q.kr * q.dlnkr * q.pr) + Rn * q.dcdT;
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] == 0) continue;
-                    const double v = S.sgn[a] * S.nu[a];
-                    atomicAdd(&L.DWT[S.sp[a]], v * dqT);
-                    if (q.dcdM != 0.0) atomicAdd(&L.TB[S.sp[a]], v * rdm);
-                }
-            }
-            if (JAC && mode == 1) {
-                cache[(3 * it) * 64] = ckf;
-                cache[(3 * it + 1) * 64] = ckr;
-                cache[(3 * it + 2) * 64] = rdm;
-            }
-        }
-        if (JAC) {
-#pragma unroll
-            for (int b = 0; b < kMaxSlots; b++) {
-                if (b >= nmax) break;
-                const int col = S.sp[b] - c0;
-                if (S.sgn[b] == 0 || col < 0 || col >= win) continue;
-                const double d = dprod_slot(S, b, nmax);
-                const double dq = S.sgn[b] < 0 ? ckf * d : -ckr * d;
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] != 0) atomicAdd(&L.JC[S.sp[a] * L.ldj + col], (S.sgn[a] * S.nu[a]) * dq);
-                }
-            }
-            if (rdm != 0.0) {
-                const int eb = R.eff_begin, ec = rx_neff(R.meta);
-#pragma unroll
-                for (int a = 0; a < kMaxSlots; a++) {
-                    if (a >= nmax) break;
-                    if (S.sgn[a] == 0) continue;
-                    const double base = (S.sgn[a] * S.nu[a]) * rdm;
-                    for (int e = 0; e < ec; e++) {
-                        const EffRec E = M.eff[eb + e];
-                        const int col = E.sp - c0;
-                        if (col >= 0 && col < win) atomicAdd(&L.JC[S.sp[a] * L.ldj + col], base * E.am1);
-                    }
-                }
-            }
-        }
-    }
-    __syncthreads();
-}
-
-template <bool JAC>
-__device__ __forceinline__ void reaction_pass(const DevMech &M, const Lds &L, const TPow &t, double Ctot) {
-    reaction_pass<JAC>(M, L, t, Ctot, 0, M.nsp, true);
+__device__ __forceinline__ void zero_jc(const Lds &L, int ns) {
+    const int tot = ns * L.ldj;
+    for (int e = lane_fresh(); e < tot; e += 64) L.JC[e] = 0.0;
 }
 
 // Eqs. ydot and tdot from the accumulated production rates.  Constant volume: internal energies
 // U_k = H_k - R T and c_v = c_p - R / Wbar in place of H_k and c_p.
 template <int RPL>
 __device__ __forceinline__ void finish_rhs(const DevMech &M, const Lds &L, const Mix<RPL> &x, double (&f)[RPL]) {
-    const int ns = M.nsp;
     const int lane = lane_fresh();
     const double shift = L.cv ? 1.0 : 0.0;
     double qp = 0.0;
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
-        const int k = slot_species(c, ns, lane);
-        if (k >= 0) {
-            const double wd = L.WD[k];
-            f[c] = M.W()[k] * wd / x.rho;
-            qp += M.R * x.t.T * (x.h[c] - shift) * wd;
-        } else {
-            f[c] = 0.0;
-        }
+        const double wd = x.valid[c] ? L.WD[x.k[c]] : 0.0;
+        f[c] = x.W[c] * wd * x.invrho;
+        qp = fma(x.h[c] - shift, wd, qp);
     }
-    const double Q = wsum(qp);
-    const double heat_cap = L.cv ? x.cpm - M.R / x.Wbar : x.cpm;
-    if (lane == 0) f[0] = -Q / (x.rho * heat_cap);
+    const double Q = wsum(qp) * (M.R * x.t.T);
+    const double heat_cap = L.cv ? x.cpm - M.R * ck_rcp(x.Wbar) : x.cpm;
+    const double fT = -Q * ck_rcp(x.rho * heat_cap);
+    if (lane == 0) f[0] = fT;
 }
 
 template <int RPL>
 __device__ __forceinline__ void rhs_wave(const DevMech &M, const Lds &L, const double (&y)[RPL], double P, double (&f)[RPL]) {
     Mix<RPL> x;
     species_pass<RPL, false>(M, y, P, L, x);
-    reaction_pass<false>(M, L, x.t, x.Ctot);
+    reaction_pass<64, false>(M, L, x.t, x.Ctot, RxScale{0.0, 0.0, 0.0}, 0, 0, kRates, nullptr, lane_fresh());
+    __syncthreads();
     finish_rhs<RPL>(M, L, x, f);
     __syncthreads();
+}
+
+__device__ __forceinline__ RxScale rx_scale(const Lds &L, const Mix<1> &x) {
+    return L.cv ? RxScale{0.0, 0.0, 0.0} : RxScale{x.t.invT, x.Wbar * x.invrho, 1.0};
+}
+
+// Chain rule for the lane's species row (lane k + 1) and its entry of the temperature row, in the
+// specific mole numbers z = Y / W (J' of ChainIn): J'[k+1][0] = col0, J'[k+1][1+j] = JC[k][j] + beta,
+// J'[0][1+k] = trow, J'[0][0] = J00.
+struct Chain {
+    double beta, col0, trow, J00;
+};
+__device__ __forceinline__ Chain chain_rule(const DevMech &M, const Lds &L, const Mix<1> &x, double y0, double fT) {
+    const bool valid = x.valid[0];
+    const int k = x.k[0];
+    const double TBk = valid ? L.TB[k] : 0.0, WDk = valid ? L.WD[k] : 0.0, DWTk = valid ? L.DWT[k] : 0.0;
+    const bool cv = L.cv != 0;
+    ChainIn c;
+    c.rho = x.rho;
+    c.invrho = x.invrho;
+    c.Wbar = x.Wbar;
+    c.invT = x.t.invT;
+    c.R = M.R;
+    c.RT = M.R * x.t.T;
+    c.cpm = x.cpm;
+    c.fT = fT;
+    const double e = cv ? 1.0 : 0.0;
+    const double Hk = x.h[0] - e;                               // over R T
+    c.sHB = c.RT * wsum(Hk * TBk);
+    c.sHW = c.RT * wsum(Hk * WDk);
+    c.dQT = M.R * wsum(fma(x.cp[0] - e, WDk, Hk * (x.t.T * DWTk - (cv ? 0.0 : WDk))));
+    c.sdcp = M.R * wsum(valid ? y0 * x.dcp[0] * M.invW()[k] : 0.0);
+    Chain o;
+    o.trow = valid ? chain_trow(c, cv, L.HC[k], x.cp[0]) : 0.0;
+    o.J00 = chain_J00(c, cv);
+    o.beta = TBk;
+    o.col0 = DWTk * x.invrho;
+    return o;
 }
 
 // Row of J owned by this lane: J[l][0] = c0, J[l][1 + j] = IW[j] * (alpha * src[j] + beta).
@@ -302,76 +248,11 @@ struct JRow {
     double alpha, beta, c0;
 };
 
-// Chain rule from (d wdot/dC at fixed T, d wdot/dT at fixed C) to J = df/dy, for the lane's
-// species row k (lane k + 1) and the lane's entry of the temperature row.  Inputs: jcc =
-// sum_l JC[k][l] C_l (third-body rank-one part excluded), colH = sum_r h_r JC[r][k] and colJ =
-// sum_r JC[r][k] (h_r = H_r / (R T)).  The species row is J[k+1][0] = col0,
-// J[k+1][1+j] = (alpha JC[k][j] + beta) / W_j; trow is J[0][1+k] and J00 = J[0][0].
-// Constant pressure: C = rho Y / W with rho = P Wbar / (R T); constant volume: rho fixed, U_k and
-// c_v in place of H_k and c_p.
-struct Chain {
-    double alpha, beta, col0, trow, J00;
-};
-__device__ __forceinline__ Chain chain_rule(const DevMech &M, const Lds &L, const Mix<1> &x, bool valid, int k,
-                                            double y0, double fT, double jcc, double colH, double colJ) {
-    const double RT = M.R * x.t.T;
-    double TBk = 0.0, WDk = 0.0, DWTk = 0.0;
-    if (valid) {
-        TBk = L.TB[k];
-        WDk = L.WD[k];
-        DWTk = L.DWT[k];
-    }
-    const double Wk = valid ? M.W()[k] : 0.0, iWk = valid ? M.invW()[k] : 0.0;
-    const double sdcp = wsum(valid ? y0 * M.R * x.dcp[0] * iWk : 0.0);
-    Chain c;
-    if (!L.cv) {
-        jcc += TBk * x.Ctot;
-        const double resid = WDk - jcc;
-        const double Hk = RT * x.h[0];
-        const double sumHTB = wsum(valid ? Hk * TBk : 0.0);
-        const double sumHJCC = wsum(valid ? Hk * jcc : 0.0);
-        const double dQT = wsum(valid ? M.R * x.cp[0] * WDk + Hk * (DWTk - jcc * x.t.invT) : 0.0);
-        const double D = x.rho * x.cpm;
-        const double dQ = iWk * (x.rho * (RT * colH + sumHTB) - x.Wbar * sumHJCC);
-        const double dD = x.rho * iWk * (M.R * x.cp[0] - x.cpm * x.Wbar);
-        c.trow = valid ? -(dQ + fT * dD) / D : 0.0;
-        c.J00 = -(dQT + fT * (-x.rho * x.cpm * x.t.invT + x.rho * sdcp)) / D;
-        c.alpha = Wk;
-        c.beta = valid ? Wk * TBk + Wk * x.Wbar * resid / x.rho : 0.0;
-        c.col0 = valid ? (Wk / x.rho) * (DWTk + resid * x.t.invT) : 0.0;
-    } else {
-        const double Uk = RT * (x.h[0] - 1.0);
-        const double sumUTB = wsum(valid ? Uk * TBk : 0.0);
-        const double dQT = wsum(valid ? M.R * (x.cp[0] - 1.0) * WDk + Uk * DWTk : 0.0);
-        const double D = x.rho * (x.cpm - M.R / x.Wbar);
-        const double dQ = iWk * x.rho * (RT * (colH - colJ) + sumUTB);
-        const double dD = x.rho * iWk * M.R * (x.cp[0] - 1.0);
-        c.trow = valid ? -(dQ + fT * dD) / D : 0.0;
-        c.J00 = -(dQT + fT * x.rho * sdcp) / D;
-        c.alpha = Wk;
-        c.beta = Wk * TBk;
-        c.col0 = valid ? (Wk / x.rho) * DWTk : 0.0;
-    }
-    return c;
-}
-
-// Row descriptor of J for N <= 64, one row per lane (Jacobian pieces staged whole in LDS).
+// Row descriptor of J (mass fractions) for N <= 64, one row per lane, d wdot/dC staged whole in LDS.
 __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, const Mix<1> &x, double y0, double fT) {
-    const int ns = M.nsp, lane = lane_fresh();
-    const int k = slot_species(0, ns, lane);
-    const bool valid = k >= 0;
-    double jcc = 0.0, colH = 0.0, colJ = 0.0;
-    if (valid) {
-        const double *row = &L.JC[k * L.ldj];
-        for (int j = 0; j < ns; j++) {
-            jcc += row[j] * L.C[j];
-            const double v = L.JC[j * L.ldj + k];
-            colH += L.H[j] * v;
-            colJ += v;
-        }
-    }
-    const Chain c = chain_rule(M, L, x, valid, k, y0, fT, jcc, colH, colJ);
-    if (valid) L.TROW[k] = c.trow * M.W()[k];
+    const int lane = lane_fresh();
+    const Chain c = chain_rule(M, L, x, y0, fT);
+    if (x.valid[0]) L.TROW[x.k[0]] = c.trow;
     __syncthreads();
     JRow r;
     if (lane == 0) {
@@ -379,11 +260,11 @@ __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, cons
         r.alpha = 1.0;
         r.beta = 0.0;
         r.c0 = c.J00;
-    } else if (valid) {
-        r.src = &L.JC[k * L.ldj];
-        r.alpha = c.alpha;
-        r.beta = c.beta;
-        r.c0 = c.col0;
+    } else if (x.valid[0]) {
+        r.src = &L.JC[x.k[0] * L.ldj];
+        r.alpha = x.W[0];
+        r.beta = x.W[0] * c.beta;
+        r.c0 = x.W[0] * c.col0;
     } else {
         r.src = L.TROW;
         r.alpha = 0.0;
@@ -393,20 +274,27 @@ __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, cons
     return r;
 }
 
+// f(y) and the Jacobian pieces with d wdot/dC staged whole.
+__device__ __forceinline__ JRow jac_whole(const DevMech &M, const Lds &L, double y, double P, double &f) {
+    Mix<1> x;
+    const double yy[1] = {y};
+    double ff[1];
+    zero_jc(L, M.nsp);
+    species_pass<1, true>(M, yy, P, L, x);
+    reaction_pass<64, true>(M, L, x.t, x.Ctot, rx_scale(L, x), 0, M.nsp, kRates, nullptr, lane_fresh());
+    __syncthreads();
+    finish_rhs<1>(M, L, x, ff);
+    f = ff[0];
+    return jac_prepare(M, L, x, y, bcast(ff[0], 0));
+}
+
 // f(y) and this lane's row of the iteration matrix M = dg I - J (registers, element type T) for
 // N <= NP <= 64.  The row descriptor jr stays valid (with the Jacobian pieces in LDS) until the
 // next Jacobian, so J x products can be formed later without a stored FP64 matrix.
 template <int NP, class T>
 __device__ __forceinline__ void jac_rows(const DevMech &M, const Lds &L, double y, double P, double dg, T (&a)[NP], double &f,
                          JRow &jr) {
-    Mix<1> x;
-    const double yy[1] = {y};
-    double ff[1];
-    species_pass<1, true>(M, yy, P, L, x);
-    reaction_pass<true>(M, L, x.t, x.Ctot);
-    finish_rhs<1>(M, L, x, ff);
-    f = ff[0];
-    jr = jac_prepare(M, L, x, y, bcast(ff[0], 0));
+    jr = jac_whole(M, L, y, P, f);
     const int lane = lane_fresh();
     a[0] = T((lane == 0 ? dg : 0.0) - jr.c0);
 #pragma unroll
@@ -414,71 +302,58 @@ __device__ __forceinline__ void jac_rows(const DevMech &M, const Lds &L, double 
     __syncthreads();
 }
 
-// f(y) and this lane's row of M = dg I - J (FP64 registers) for N <= NP <= 64, with d wdot/dC
-// staged in NWIN column windows of WIN columns (NWIN * WIN >= ns).  The reaction pass runs once
-// per window, which keeps JC at ns * (WIN | 1) doubles of LDS; the second window reuses the first
-// window's rate constants when they fit the park slice (else it recomputes them).  Raw window
-// entries wait in the park slice until the chain-rule scalars of the row are known.
+// f(y) and this lane's row of M' = dg I - J' (FP64 registers; J' the Jacobian in the specific mole
+// numbers, similar to J by diag(1, W)) for N <= NP <= 64, with d wdot/dC staged in NWIN column
+// windows of WIN columns (NWIN * WIN >= ns).  The first window's reaction pass also leaves every
+// per-species sum of the chain rule, so each window's columns are final when they are read.  The
+// second window takes the first one's rate constants from the park slice when they fit (else it
+// evaluates them again).  iw and w: 1/W and W of the lane's component (1 for T, 0 for padding).
 template <int NP, int NWIN, int WIN>
 __device__ __forceinline__ void jac_rows_win(const DevMech &M, const Lds &L, double y, double P, double dg, double (&a)[NP],
-                             double &f) {
+                             double &f, double &iw, double &w) {
     Mix<1> x;
     const double yy[1] = {y};
     double ff[1];
-    species_pass<1, true, false>(M, yy, P, L, x);
     const int ns = M.nsp;
+    zero_jc(L, ns);
+    species_pass<1, true>(M, yy, P, L, x);
+    const RxScale sc = rx_scale(L, x);
+    static_assert(NWIN == 1 || NWIN == 2, "the kept scalars serve one later window");
+    const bool fits = NWIN == 2 && 3 * rx_blocks(M, 64) <= NP;
+    reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, 0, min(WIN, ns), fits ? kRatesKeep : kRates, L.park + lane_fresh(),
+                            lane_fresh());
+    __syncthreads();
+    finish_rhs<1>(M, L, x, ff);
+    f = ff[0];
+    const Chain c = chain_rule(M, L, x, y, bcast(f, 0));
     const int lane = lane_fresh();
-    const int k = lane - 1;
-    const bool valid = lane >= 1 && lane <= ns;
-    double jcc = 0.0, colH = 0.0, colJ = 0.0;
-    // per-reaction scatter scalars of the first window, kept in the park slice for the second
-    static_assert(NWIN <= 2, "the scalar cache serves one later window");
-    const bool keep = NWIN == 2 && 3 * ((M.nrxn + 63) / 64) <= NP;
-    double *cache = L.park + lane_fresh();
+    const bool valid = x.valid[0];
+    if (valid) L.TROW[x.k[0]] = c.trow;
+    w = lane == 0 ? 1.0 : (valid ? x.W[0] : 0.0);
+    iw = lane == 0 ? 1.0 : (valid ? M.invW()[x.k[0]] : 0.0);
+    a[0] = lane == 0 ? dg - c.J00 : (valid ? -c.col0 : 0.0);
+    const double beta = valid ? c.beta : 0.0;
+    __syncthreads();
 #pragma unroll
-    for (int w = 0; w < NWIN; w++) {
-        const int c0 = w * WIN;
-        const int tot = ns * L.ldj;
-        for (int e = lane; e < tot; e += 64) L.JC[e] = 0.0;
-        __syncthreads();
-        reaction_pass<true>(M, L, x.t, x.Ctot, c0, WIN, w == 0, cache, keep ? (w == 0 ? 1 : 2) : 0);
-        if (w == 0) finish_rhs<1>(M, L, x, ff);
-        // raw d wdot_k / dC_(c0+j) into column 1 + c0 + j of the row registers; the chain-rule
-        // scalars of the row are applied once every window is in
-        // (every lane reads an in-range entry and keeps it under a bit mask, so that the reads
-        // are not split into one masked branch each; the column tests use a scalar copy of ns
-        // that the compiler cannot hoist out of the reactor loop, where the tests' results would
-        // occupy and spill scalar registers)
-        const double *row = &L.JC[(valid ? k : 0) * L.ldj];
-        const int vkeep = opaque(valid ? -1 : 0);
+    for (int v = 0; v < NWIN; v++) {
+        const int c0 = v * WIN;
+        if (v > 0) {
+            __syncthreads();
+            zero_jc(L, ns);
+            __syncthreads();
+            reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, c0, min(WIN, ns - c0), fits ? kScatterKept : kScatter,
+                                    L.park + lane_fresh(), lane_fresh());
+            __syncthreads();
+        }
+        // lane 0 reads the temperature row, a lane without a row its zero padding
+        const double *row = lane == 0 ? L.TROW + c0 : (valid ? &L.JC[x.k[0] * L.ldj] : L.TROW + ns);
         const int nsw = opaque_s(ns);
 #pragma unroll
         for (int j = 0; j < WIN; j++) {
             if (1 + c0 + j >= NP) break;
-            const bool in = c0 + j < nsw;
-            const double e = row[j];
-            const double v = __hiloint2double(__double2hiint(e) & vkeep, __double2loint(e) & vkeep);
-            if (in) jcc += v * L.C[c0 + j];
-            a[1 + c0 + j] = in ? v : 0.0;
+            a[1 + c0 + j] = c0 + j < nsw ? (lane == 1 + c0 + j ? dg : 0.0) - (row[j] + beta)
+                                         : (lane == 1 + c0 + j ? dg : 0.0);
         }
-        if (valid && k >= c0 && k < c0 + WIN)
-            for (int r = 0; r < ns; r++) {
-                const double v = L.JC[r * L.ldj + (k - c0)];
-                colH += L.H[r] * v;
-                colJ += v;
-            }
-        __syncthreads();
-    }
-    f = ff[0];
-    const Chain c = chain_rule(M, L, x, valid, k, y, bcast(f, 0), jcc, colH, colJ);
-    if (valid) L.TROW[k] = c.trow;
-    const double J00 = c.J00, col0 = c.col0, alpha = c.alpha, beta = c.beta;
-    __syncthreads();
-    a[0] = (lane == 0 ? dg : 0.0) - (lane == 0 ? J00 : col0);
-#pragma unroll
-    for (int j = 1; j < NP; j++) {
-        const double Jv = lane == 0 ? L.TROW[j - 1] : L.IW[j - 1] * (alpha * a[j] + beta);
-        a[j] = (lane == j ? dg : 0.0) - Jv;
     }
     __syncthreads();
 }
@@ -593,7 +468,8 @@ __device__ __forceinline__ void unpark_rows(const Lds &L, double (&a)[NP]) {
     for (int j = 0; j < NP; j++) a[j] = r[j * 64];
 }
 
-// FULLJC: d wdot/dC staged whole (the FP32-mode LDS layout), no column windows.
+// FULLJC: d wdot/dC staged whole (the FP32-mode LDS layout), no column windows.  The stage systems
+// are solved in the specific mole numbers (iw scales a right-hand side, w a solution).
 template <int NP, bool FULLJC = false>
 struct Ros4Wave {
     using SH = WaveShape<NP>;
@@ -601,26 +477,23 @@ struct Ros4Wave {
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, double y, double P, double h, double &ynew,
                                 double &e) {
         double a[NP];
-        double f;
+        double f, iw, w;
         const double dg = 1.0 / (Ros4::gamma * h);
-        if (SH::NWIN == 1 || FULLJC) {
-            JRow jr;
-            jac_rows<NP, double>(M, L, y, P, dg, a, f, jr);
-        } else {
-            jac_rows_win<NP, SH::NWIN, SH::WIN>(M, L, y, P, dg, a, f);
-        }
+        if (SH::NWIN == 1 || FULLJC) jac_rows_win<NP, 1, NP - 1>(M, L, y, P, dg, a, f, iw, w);
+        else jac_rows_win<NP, SH::NWIN, SH::WIN>(M, L, y, P, dg, a, f, iw, w);
         LU<NP> lu;
         lu_factor<NP>(a, lu);
         const double ih = 1.0 / h;
-        const double u1 = lu_solve<NP>(a, lu, f);
+        const double u1 = w * lu_solve<NP>(a, lu, iw * f);
         // the factored rows stay in registers across the stage source terms (it fits without spills)
         double yt[1] = {y + Ros4::a21 * u1}, ft[1];
         rhs_wave<1>(M, L, yt, P, ft);
-        const double u2 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c21 * u1) * ih);
+        const double u2 = w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c21 * u1) * ih));
         yt[0] = y + Ros4::a31 * u1 + Ros4::a32 * u2;
         rhs_wave<1>(M, L, yt, P, ft);
-        const double u3 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih);
-        const double u4 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih);
+        const double u3 = w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih));
+        const double u4 =
+            w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih));
         ynew = y + Ros4::m1 * u1 + Ros4::m2 * u2 + Ros4::m3 * u3 + Ros4::m4 * u4;
         e = Ros4::e1 * u1 + Ros4::e2 * u2 + Ros4::e3 * u3 + Ros4::e4 * u4;
         return lu.ok;
@@ -1074,8 +947,9 @@ __device__ __forceinline__ int64_t xcd_reactor(int64_t b, int64_t nb) {
 template <int RPL>
 __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
                                                       const double *p, double *dydt, int cv) {
-    extern __shared__ double lds_raw[];
-    Lds L = carve(lds_raw, M.nsp, false);
+    // laid out for the largest species count of the instantiation, so every offset is a constant
+    __shared__ double lds_raw[4 * 64 * RPL + 128];
+    Lds L = carve(lds_raw, 64 * RPL - 1, false, 0);
     L.cv = cv;
     init_lds(M, L);
     const int N = M.N, lane = lane_id();
@@ -1106,13 +980,8 @@ __global__ void __launch_bounds__(64) jac_wave_kernel(DevMech M, int64_t n, cons
     const int64_t r = xcd_reactor(blockIdx.x, int64_t(gridDim.x));
     if (r >= n) return;
     const double yl = lane < N ? y[int64_t(lane) * ld + r] : 0.0;
-    Mix<1> x;
-    const double yy[1] = {yl};
-    double ff[1];
-    species_pass<1, true>(M, yy, p[r], L, x);
-    reaction_pass<true>(M, L, x.t, x.Ctot);
-    finish_rhs<1>(M, L, x, ff);
-    const JRow row = jac_prepare(M, L, x, yl, bcast(ff[0], 0));
+    double f;
+    const JRow row = jac_whole(M, L, yl, p[r], f);
     if (lane < N) {
         double *out = jac + int64_t(lane) * N * ld + r;
         out[0] = row.c0;
@@ -1192,12 +1061,11 @@ size_t wave_ws_bytes(const DevMech &M, int cus) {
 
 int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *dydt,
                     int cv, hipStream_t s) {
-    const size_t lds = lds_doubles(M.nsp, false) * sizeof(double);
     const unsigned grid = unsigned((n + 7) / 8 * 8);
     if (M.N <= 64)
-        rhs_wave_kernel<1><<<dim3(grid), dim3(64), lds, s>>>(M, n, y, ld, p, dydt, cv);
+        rhs_wave_kernel<1><<<dim3(grid), dim3(64), 0, s>>>(M, n, y, ld, p, dydt, cv);
     else
-        rhs_wave_kernel<2><<<dim3(grid), dim3(64), lds, s>>>(M, n, y, ld, p, dydt, cv);
+        rhs_wave_kernel<2><<<dim3(grid), dim3(64), 0, s>>>(M, n, y, ld, p, dydt, cv);
     return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
 }
 

@@ -10,10 +10,66 @@
 
 namespace ck {
 
+// exp(x) = 2^n (1 + r + r^2 P(r)), n = round(x / ln 2), |r| <= ln 2 / 2: P is the degree-9 Chebyshev
+// interpolant of (e^r - 1 - r) / r^2 (relative error 1.6e-17, below the rounding of the last step).
+// 17 operations and no branch; 0 and inf beyond the exponent range, as long as |x| < 1e15 (rate
+// constants at any temperature above 1e-9 K; the loader bounds the Troe temperatures).
+__device__ __forceinline__ double ck_exp(double x) {
+    const double n = __builtin_rint(x * 1.4426950408889634);
+    double r = fma(n, -0.6931471805598903, x);
+    r = fma(n, -5.497923018708371e-14, r);
+    double p = 2.5100397137931663e-08;
+    p = fma(p, r, 2.762010358488696e-07);
+    p = fma(p, r, 2.755726843551756e-06);
+    p = fma(p, r, 2.4801521264122017e-05);
+    p = fma(p, r, 0.00019841269863069374);
+    p = fma(p, r, 0.0013888888917234206);
+    p = fma(p, r, 0.008333333333330058);
+    p = fma(p, r, 0.04166666666662409);
+    p = fma(p, r, 0.16666666666666669);
+    p = fma(p, r, 0.5000000000000001);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return __builtin_amdgcn_ldexp(p, int(n));
+}
+
+// 1 / x: hardware estimate and two Newton-Raphson steps (within an ulp for normal x).
+__device__ __forceinline__ double ck_rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// ln x for x > 0, NaN otherwise: x = 2^e m with m in [sqrt(1/2), sqrt(2)), f = m - 1, s = f / (2 + f),
+// ln m = 2 atanh(s) = f - s (f - z P(z)), z = s^2, P the degree-6 Chebyshev interpolant of
+// (2 atanh(s) / s - 2) / z (relative error 5e-18 of the result).
+__device__ __forceinline__ double ck_log(double x) {
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.7071067811865476;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double f = m - 1.0, d = 2.0 + f;
+    double s = f * ck_rcp(d);
+    s = fma(fma(-d, s, f), ck_rcp(d), s);
+    const double z = s * s;
+    double p = 0.146171283998073;
+    p = fma(p, z, 0.15331666676597175);
+    p = fma(p, z, 0.1818289077802613);
+    p = fma(p, z, 0.22222211112104948);
+    p = fma(p, z, 0.2857142862611452);
+    p = fma(p, z, 0.399999999998992);
+    p = fma(p, z, 0.666666666666667);
+    const double de = double(e);
+    const double v = fma(de, 0.6931471805598903, f - fma(s, fma(-z, p, f), de * -5.497923018708371e-14));
+    return x > 0.0 ? v : __builtin_nan("");
+}
+
 struct Thermo {
-    double cp, h, s, dcp;   // cp/R, H/(RT), S/R, d(cp/R)/dT
+    double cp, h, g, dcp;   // cp/R, H/(RT), H/(RT) - S/R - ln(p0/(RT)), d(cp/R)/dT
 };
 
+// Powers of T and the multiples that the NASA-7 forms need.
 struct TPow {
     double T, invT, lnT, T2, T3, T4;
 };
@@ -21,26 +77,40 @@ struct TPow {
 __device__ __forceinline__ TPow tpow(double T) {
     TPow p;
     p.T = T;
-    p.invT = 1.0 / T;
-    p.lnT = log(T);
+    p.invT = ck_rcp(T);
+    p.lnT = ck_log(T);
     p.T2 = T * T;
     p.T3 = p.T2 * T;
     p.T4 = p.T3 * T;
     return p;
 }
 
-// Species k at temperature t: low range if T < Tmid, else high (per-lane select).
-__device__ __forceinline__ Thermo species_thermo(const DevMech &M, int k, const TPow &t) {
+// NASA-7 coefficients of species k: low range if T < Tmid, else high (per-lane select).
+struct Nasa {
+    double a1, a2, a3, a4, a5, a6, a7;
+};
+__device__ __forceinline__ Nasa species_coef(const DevMech &M, int k, double T) {
     const int ns = M.nsp;
-    const int off = (t.T < M.Tmid()[k]) ? 0 : 21;
-    const double *c = M.thermo() + size_t(off) * ns + k;
-    auto a = [&](int j) { return c[size_t(j) * ns]; };
+    const double *c = M.thermo() + (T < M.Tmid()[k] ? 0 : 7) * ns + k;
+    return Nasa{c[0], c[ns], c[2 * ns], c[3 * ns], c[4 * ns], c[5 * ns], c[6 * ns]};
+}
+
+// The 1/k factors of the integrated polynomials go to the powers of T, which every species shares,
+// so a species costs seven coefficient loads and 16 multiply-adds.  g is formed as one polynomial:
+// a1 (1 - ln T) - a2 T/2 - a3 T^2/6 - a4 T^3/12 - a5 T^4/20 + a6/T - a7, plus ln T - ln(p0/R).
+__device__ __forceinline__ Thermo species_thermo(const DevMech &M, const Nasa &a, const TPow &t) {
+    const double h2 = t.T * (1.0 / 2.0), h3 = t.T2 * (1.0 / 3.0), h4 = t.T3 * (1.0 / 4.0), h5 = t.T4 * (1.0 / 5.0);
+    const double g3 = t.T2 * (-1.0 / 6.0), g4 = t.T3 * (-1.0 / 12.0), g5 = t.T4 * (-1.0 / 20.0);
     Thermo o;
-    o.cp = a(0) + a(1) * t.T + a(2) * t.T2 + a(3) * t.T3 + a(4) * t.T4;
-    o.h = a(5) + a(6) * t.T + a(7) * t.T2 + a(8) * t.T3 + a(9) * t.T4 + a(10) * t.invT;
-    o.s = a(11) * t.lnT + a(12) * t.T + a(13) * t.T2 + a(14) * t.T3 + a(15) * t.T4 + a(16);
-    o.dcp = a(17) + a(18) * t.T + a(19) * t.T2 + a(20) * t.T3;
+    o.cp = fma(a.a5, t.T4, fma(a.a4, t.T3, fma(a.a3, t.T2, fma(a.a2, t.T, a.a1))));
+    o.h = fma(a.a6, t.invT, fma(a.a5, h5, fma(a.a4, h4, fma(a.a3, h3, fma(a.a2, h2, a.a1)))));
+    o.g = fma(a.a6, t.invT, fma(a.a5, g5, fma(a.a4, g4, fma(a.a3, g3, fma(a.a2, -h2, a.a1 * (1.0 - t.lnT)))))) +
+          ((t.lnT - M.ln_p0_R) - a.a7);
+    o.dcp = fma(4.0 * a.a5, t.T3, fma(3.0 * a.a4, t.T2, fma(2.0 * a.a3, t.T, a.a2)));
     return o;
+}
+__device__ __forceinline__ Thermo species_thermo(const DevMech &M, int k, const TPow &t) {
+    return species_thermo(M, species_coef(M, k, t.T), t);
 }
 
 // x^n for n in 0..3
@@ -80,23 +150,89 @@ __device__ __forceinline__ void load_slots(const RxnRec &R, const Cget &C, Slots
     }
 }
 
+// Third-body / fall-off factor c of a reaction, [M], and the derivatives of c.
+struct Factor {
+    double c, Mc, dcdM, dcdT;
+};
+
+// Factor of reaction R (not elementary) whose (high-pressure) rate constant is exp(lnkf).
+template <bool DERIV, class Cget>
+__device__ __forceinline__ void rate_factor(const DevMech &M, const RxnRec &R, const TPow &t, double Ctot,
+                                            double lnkf, double dlnkf, const Cget &C, Factor &o) {
+    const int ty = rx_type(R.meta);
+    double Mc = Ctot;
+    const int eb = R.eff_begin, ec = rx_neff(R.meta);
+    for (int e = 0; e < ec; e++) {
+        const EffRec E = M.eff[eb + e];
+        Mc += E.am1 * C(E.sp);
+    }
+    o.Mc = Mc;
+    o.c = Mc;
+    if (DERIV) {
+        o.dcdM = 1.0;
+        o.dcdT = 0.0;
+    }
+    if (ty == kThirdBody) return;
+    // fall-off: Pr = k0 [M] / k_inf, c = Pr / (1 + Pr) F
+    const FallRec F = M.fall[R.fall];
+    const double lnk0 = fma(-F.Ea0R, t.invT, fma(F.beta0, t.lnT, F.lnA0));
+    const double ratio = ck_exp(lnk0 - lnkf);
+    const double Pr = ratio * Mc;
+    double Fb = 1.0, g = 0.0, dlogF_dL = 0.0, dFc_over_Fc = 0.0;
+    if (ty == kTroe) {
+        constexpr double kLog10e = 0.4342944819032518, kLn10 = 2.302585092994046;
+        const double a = F.a;
+        const double e3 = ck_exp(-t.T * F.invT3);
+        const double e1 = ck_exp(-t.T * F.invT1);
+        const double e2 = ck_exp(-F.T2 * t.invT);
+        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
+        const double L = kLog10e * ck_log(fmax(Fc, 1e-300));
+        const double cc = -0.4 - 0.67 * L;
+        const double nn = 0.75 - 1.27 * L;
+        const double x = fma(kLog10e, ck_log(fmax(Pr, 1e-300)), cc);
+        const double d = nn - 0.14 * x;
+        const double id = ck_rcp(d);
+        const double f1 = x * id;
+        const double iu = ck_rcp(fma(f1, f1, 1.0));
+        Fb = ck_exp(kLn10 * L * iu);
+        if (DERIV) {
+            const double iu2 = iu * iu;
+            const double id2 = id * id;
+            g = L * (-2.0 * f1 * iu2) * (nn * id2);
+            dlogF_dL = iu - L * 2.0 * f1 * iu2 * ((-0.67 * nn + 1.27 * x) * id2);
+            const double dFc = -(1.0 - a) * F.invT3 * e3 - a * F.invT1 * e1 + F.T2 * t.invT * t.invT * e2;
+            dFc_over_Fc = dFc / Fc;
+        }
+    }
+    const double ionep = 1.0 / (1.0 + Pr);
+    o.c = Pr * ionep * Fb;
+    if (DERIV) {
+        const double dc_dPr = Fb * ionep * (ionep + g);
+        const double dlnPr_dT = (F.beta0 + F.Ea0R * t.invT) * t.invT - dlnkf;
+        o.dcdM = dc_dPr * ratio;
+        o.dcdT = dc_dPr * Pr * dlnPr_dT;
+        if (ty == kTroe) o.dcdT += o.c * dlogF_dL * dFc_over_Fc;
+    }
+}
+
 // Everything one reaction contributes at (T, C).
 struct Rate {
     double kf, kr;        // multiply the mass-action products; k_inf for fall-off
     double pf, pr;        // prod C^nu' and prod C^nu''
-    double c;             // third-body / fall-off factor
+    double c, Mc;         // third-body / fall-off factor and its [M] (0 for elementary reactions)
     double dlnkf, dlnkr;  // d ln k / dT            (DERIV only)
     double dcdM, dcdT;    // d c / d[M], d c / dT   (DERIV only)
 };
 
 // Rate constants and factors of reaction R (Eqs. kfor, krev, kc; third-body and
-// fall-off factor c).  Gget(k) returns g_k = H_k/(RT) - S_k/R, Hget(k) H_k/(RT).
+// fall-off factor c).  Gget(k) returns H_k/(RT) - S_k/R - ln(p0/(RT)), Hget(k) H_k/(RT) - 1, so that
+// ln Kc = -sum_j nu_j g_j and d ln Kc / dT = sum_j nu_j h_j / T without the net mole change.
 template <bool DERIV, class Cget, class Gget, class Hget>
 __device__ __forceinline__ void reaction_rate(const DevMech &M, const RxnRec &R, const Slots &S, int nmax,
                                               const TPow &t, double Ctot, const Cget &C, const Gget &G,
                                               const Hget &H, Rate &o) {
-    const double lnkf = R.lnA + R.beta * t.lnT - R.EaR * t.invT;
-    o.kf = exp(lnkf);
+    const double lnkf = fma(-R.EaR, t.invT, fma(R.beta, t.lnT, R.lnA));
+    o.kf = ck_exp(lnkf);
     if (DERIV) o.dlnkf = (R.beta + R.EaR * t.invT) * t.invT;
     o.pf = 1.0;
     o.pr = 1.0;
@@ -114,69 +250,26 @@ __device__ __forceinline__ void reaction_rate(const DevMech &M, const RxnRec &R,
     }
     const int meta = R.meta;
     if (rx_rev(meta)) {
-        // ln Kc = -sum_j nu_j g_j + dnu ln(p0 / (R T)); kr = kf / Kc
-        const double lnKc = -sg + R.dnu * (M.ln_p0_R - t.lnT);
-        o.kr = exp(lnkf - lnKc);
-        if (DERIV) o.dlnkr = o.dlnkf - (sh - R.dnu) * t.invT;
+        o.kr = ck_exp(lnkf + sg);      // kr = kf / Kc
+        if (DERIV) o.dlnkr = o.dlnkf - sh * t.invT;
     } else {
         o.kr = 0.0;
         if (DERIV) o.dlnkr = 0.0;
     }
     o.c = 1.0;
+    o.Mc = 0.0;
     if (DERIV) {
         o.dcdM = 0.0;
         o.dcdT = 0.0;
     }
-    const int ty = rx_type(meta);
-    if (ty == kElementary) return;
-    double Mc = Ctot;
-    const int eb = R.eff_begin, ec = rx_neff(meta);
-    for (int e = 0; e < ec; e++) {
-        const EffRec E = M.eff[eb + e];
-        Mc += E.am1 * C(E.sp);
-    }
-    if (ty == kThirdBody) {
-        o.c = Mc;
-        if (DERIV) o.dcdM = 1.0;
-        return;
-    }
-    // fall-off: Pr = k0 [M] / k_inf, c = Pr / (1 + Pr) F
-    const FallRec F = M.fall[R.fall];
-    const double lnk0 = F.lnA0 + F.beta0 * t.lnT - F.Ea0R * t.invT;
-    const double ratio = exp(lnk0 - lnkf);
-    const double Pr = ratio * Mc;
-    double Fb = 1.0, g = 0.0, dlogF_dL = 0.0, dFc_over_Fc = 0.0;
-    if (ty == kTroe) {
-        const double a = F.a;
-        const double e3 = exp(-t.T * F.invT3);
-        const double e1 = exp(-t.T * F.invT1);
-        const double e2 = exp(-F.T2 * t.invT);
-        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
-        const double L = log10(fmax(Fc, 1e-300));
-        const double cc = -0.4 - 0.67 * L;
-        const double nn = 0.75 - 1.27 * L;
-        const double x = log10(fmax(Pr, 1e-300)) + cc;
-        const double d = nn - 0.14 * x;
-        const double f1 = x / d;
-        const double u = 1.0 + f1 * f1;
-        Fb = exp10(L / u);
-        if (DERIV) {
-            const double iu2 = 1.0 / (u * u);
-            const double id2 = 1.0 / (d * d);
-            g = L * (-2.0 * f1 * iu2) * (nn * id2);
-            dlogF_dL = 1.0 / u - L * 2.0 * f1 * iu2 * ((-0.67 * nn + 1.27 * x) * id2);
-            const double dFc = -(1.0 - a) * F.invT3 * e3 - a * F.invT1 * e1 + F.T2 * t.invT * t.invT * e2;
-            dFc_over_Fc = dFc / Fc;
-        }
-    }
-    const double onep = 1.0 + Pr;
-    o.c = Pr / onep * Fb;
+    if (rx_type(meta) == kElementary) return;
+    Factor f;
+    rate_factor<DERIV>(M, R, t, Ctot, lnkf, o.dlnkf, C, f);
+    o.c = f.c;
+    o.Mc = f.Mc;
     if (DERIV) {
-        const double dc_dPr = Fb / (onep * onep) + Fb * g / onep;
-        const double dlnPr_dT = (F.beta0 + F.Ea0R * t.invT) * t.invT - o.dlnkf;
-        o.dcdM = dc_dPr * ratio;
-        o.dcdT = dc_dPr * Pr * dlnPr_dT;
-        if (ty == kTroe) o.dcdT += Pr / onep * Fb * dlogF_dL * dFc_over_Fc;
+        o.dcdM = f.dcdM;
+        o.dcdT = f.dcdT;
     }
 }
 

@@ -163,33 +163,43 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     const HostMech &hm = m->host;
     const int ns = hm.nsp, nr = hm.nrxn;
 
-    // species block: W, 1/W, Tmid, then the derived NASA-7 coefficients, each [nsp]
+    // species block: W, 1/W, Tmid, then the NASA-7 coefficients, each [nsp]
     std::vector<double> spd(size_t(3 + kThermoCoef) * ns);
     for (int k = 0; k < ns; k++) {
         spd[k] = hm.W[k];
         spd[size_t(ns) + k] = 1.0 / hm.W[k];
         spd[size_t(2) * ns + k] = hm.Tmid[k];
-        for (int rg = 0; rg < 2; rg++) {
-            const double *a = rg == 0 ? &hm.alow[7 * k] : &hm.ahigh[7 * k];
-            double c[21] = {a[0], a[1], a[2], a[3], a[4],
-                            a[0], a[1] / 2.0, a[2] / 3.0, a[3] / 4.0, a[4] / 5.0, a[5],
-                            a[0], a[1], a[2] / 2.0, a[3] / 3.0, a[4] / 4.0, a[6],
-                            a[1], 2.0 * a[2], 3.0 * a[3], 4.0 * a[4]};
-            for (int j = 0; j < 21; j++) spd[size_t(3 + 21 * rg + j) * ns + k] = c[j];
+        for (int j = 0; j < 7; j++) {
+            spd[size_t(3 + j) * ns + k] = hm.alow[7 * k + j];
+            spd[size_t(10 + j) * ns + k] = hm.ahigh[7 * k + j];
         }
     }
-    // Reactions sorted by type (stable), the most complex first, and within a type by species slot
-    // count, the fewest first: the kernels hand consecutive blocks of 64 reactions to the lanes of
-    // a wavefront, and a block pays for the most complex type it holds and loops over its largest
-    // slot count.  So the few third-body and fall-off reactions share the leading blocks, topped up
-    // with the smallest elementary reactions, and the ragged last block holds elementary ones only.
+    // Stored order (stable): reactions that are not pair-form first, then by type, the most complex
+    // first, and within a type by species slot count, the fewest first.  The kernels hand
+    // consecutive blocks of 64 reactions to the lanes of a wavefront, and a block pays for the most
+    // complex type it holds, so the few third-body and fall-off reactions share the leading blocks
+    // and the ragged last block holds elementary ones only.
     std::vector<int> order(nr);
     std::iota(order.begin(), order.end(), 0);
+    auto units = [](const std::vector<int> &nu) { return std::accumulate(nu.begin(), nu.end(), 0); };
+    auto pair_form = [&](int i) {
+        const auto &x = hm.rx[i];
+        const int r = units(x.rnu), p = units(x.pnu);
+        return x.rev && r >= 1 && r <= 2 && p >= 1 && p <= 2;
+    };
     auto slots = [&](int i) { return hm.rx[i].rsp.size() + hm.rx[i].psp.size(); };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        if (pair_form(a) != pair_form(b)) return !pair_form(a);
         if (hm.rx[a].type != hm.rx[b].type) return hm.rx[a].type > hm.rx[b].type;
         return slots(a) < slots(b);
     });
+    int n_gen = 0, n_fall = 0;
+    for (int i = 0; i < nr; i++) {
+        n_gen += !pair_form(i);
+        n_fall += pair_form(i) && hm.rx[i].type != kElementary;
+    }
+    std::vector<PairBlock> pair(std::max((nr - n_gen + 63) / 64, 1));
+    std::memset(pair.data(), 0, pair.size() * sizeof(PairBlock));
     std::vector<RxnRec> rx(std::max(nr, 1));
     std::vector<FallRec> fall;
     std::vector<EffRec> eff;
@@ -228,12 +238,28 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
             F.Ea0R = x.Ea0 / hm.R;
             if (x.type == 3) {
                 F.a = x.ta;
-                F.invT3 = 1.0 / x.T3;
-                F.invT1 = 1.0 / x.T1;
-                F.T2 = x.T2;
+                // exp(-T / T***) and its like are 0 (or inf) long before these bounds, which keep the
+                // arguments within the range of the kernels' exp
+                auto bound = [](double v, double b) { return std::min(std::max(v, -b), b); };
+                F.invT3 = bound(1.0 / x.T3, 1e10);
+                F.invT1 = bound(1.0 / x.T1, 1e10);
+                F.T2 = bound(x.T2, 1e12);
             }
             R.fall = int(fall.size());
             fall.push_back(F);
+        }
+        if (ii >= n_gen) {
+            PairBlock &B = pair[(ii - n_gen) / 64];
+            const int l = (ii - n_gen) % 64;
+            int u[4] = {ns, ns, ns, ns};
+            for (size_t j = 0, c = 0; j < x.rsp.size(); j++)
+                for (int v = 0; v < x.rnu[j]; v++) u[c++] = x.rsp[j];
+            for (size_t j = 0, c = 2; j < x.psp.size(); j++)
+                for (int v = 0; v < x.pnu[j]; v++) u[c++] = x.psp[j];
+            B.lnA[l] = R.lnA;
+            B.beta[l] = R.beta;
+            B.EaR[l] = R.EaR;
+            B.off[l] = make_int4(8 * u[0], 8 * u[1], 8 * u[2], 8 * u[3]);
         }
         for (auto &e : x.eff) {
             EffRec E{};
@@ -242,16 +268,12 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
             eff.push_back(E);
         }
     }
-    for (int b0 = 0; b0 < nr; b0 += 64) {
-        int mx = 0;
-        for (int i = b0; i < std::min(nr, b0 + 64); i++) mx = std::max(mx, rx_nslot(rx[i].meta));
-        for (int i = b0; i < std::min(nr, b0 + 64); i++) rx[i].blk_slots = mx;
-    }
     if (fall.empty()) fall.resize(1);
     if (eff.empty()) eff.resize(1);
 
     Packer pk;
-    const size_t ospd = pk.add(spd), orx = pk.add(rx), ofall = pk.add(fall), oeff = pk.add(eff), oorig = pk.add(orig);
+    const size_t ospd = pk.add(spd), orx = pk.add(rx), ofall = pk.add(fall), oeff = pk.add(eff), oorig = pk.add(orig),
+                 opair = pk.add(pair);
 
     m->device = device;
     int prev = 0;
@@ -284,10 +306,14 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     d.nrxn = nr;
     d.N = ns + 1;
     d.n_eff = int(eff.size());
+    d.n_gen = n_gen;
+    d.n_fall = n_fall;
     d.R = hm.R;
+    d.invR = 1.0 / hm.R;
     d.ln_p0_R = std::log(hm.p0 / hm.R);
     d.spd = reinterpret_cast<const double *>(b + ospd);
     d.rx = reinterpret_cast<const RxnRec *>(b + orx);
+    d.pair = reinterpret_cast<const PairBlock *>(b + opair);
     d.fall = reinterpret_cast<const FallRec *>(b + ofall);
     d.eff = reinterpret_cast<const EffRec *>(b + oeff);
     d.orig_index = reinterpret_cast<const int *>(b + oorig);
