@@ -4,8 +4,9 @@
 //     component l + 64 when N > 64);
 //   - reaction phases run lane-per-reaction, scattering rates of progress
 //     into per-species accumulators in LDS with FP64 LDS atomics;
-//   - the Rosenbrock matrix (I/(gamma h) - J) lives in registers, one row
-//     per lane, and is factored by a fully unrolled partial-pivoting LU.
+//   - the Rosenbrock matrix (I/(gamma h) - J) lives in 16 x 16 register tiles
+//     and is inverted by a blocked Gauss-Jordan elimination on the FP64 matrix
+//     cores (wtile.h).
 // This is the deep-vectorisation design of Section 4 applied to a 64-wide
 // wavefront.  Integrators pull reactors from a device work queue (the
 // paper's global atomic counter, Section 5.2) one reactor per wavefront, so
@@ -15,6 +16,7 @@
 #include "kinetics.h"
 #include "launch.h"
 #include "reactions.h"
+#include "wtile.h"
 
 extern "C" __device__ unsigned long long __ockl_wfred_max_u64(unsigned long long);
 extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
@@ -46,61 +48,83 @@ __device__ __forceinline__ bool wave_all(bool v) { return __ballot(!v) == 0ull; 
 
 // ---------------------------------------------------------------------------------------
 // LDS layout of one wavefront (doubles), ns1 = ns + 1 (a null species closes every array):
-//   C G H WD [ns1] | IW[64] (1/W_j padded with zeros) VX[64] (broadcast scratch): FP32 mode only |
-//   TB DWT HC [ns1] TROW[ns + 64] JC[ns1*ldj + 64]   (Jacobian kernels only)
-// JC holds d wdot / dC for a window of `win` consecutive columns (all ns columns when the
-// Jacobian is staged in one piece), leading dimension ldj = win | 1.
+//   C G H WD [ns1]                                   every kernel
+//   | scratch of the tiles                           kLdsTiles (ROS4 with another Jacobian)
+//   | TB DWT HC [ns1] TROW[96] JC                    kLdsJac (ROS4): JC holds d wdot / dC for a window
+//                                                    of columns, then the scratch of the tiles
+//   | TB DWT HC [ns1] TROW[ns + 96] JC IW[64] VX[64] kLdsWhole: d wdot / dC staged in one piece
 // ---------------------------------------------------------------------------------------
+enum LdsKind { kLdsRhs, kLdsTiles, kLdsJac, kLdsWhole };
+
 struct Lds : RxArrays {
     double *IW, *VX, *TROW;
-    double *park;   // this wavefront's slice of the workspace for parked LU rows ([NP][64]), or null
+    double *park;   // this wavefront's slice of the workspace, or null
     int cv;         // 0: constant pressure (p = pressure); 1: constant volume (p = density)
 };
 
-__host__ __device__ inline int ldj_of(int win) { return win | 1; }
-__host__ __device__ inline size_t lds_doubles(int ns, bool jac, int win) {
-    size_t d = 4 * size_t(ns + 1) + 128;
-    if (jac) d += 3 * size_t(ns + 1) + size_t(ns) + 64 + size_t(ns + 1) * ldj_of(win) + 64;
+// Column windows of the staged d wdot/dC for a padded size NP: matrix columns [32 w, 32 w + 32), the
+// temperature column being matrix column 0, so that a window is whole tile columns.
+template <int NP>
+struct WaveShape {
+    static constexpr int TR = WTile<NP>::TR;
+    static constexpr int NWIN = TR > 2 ? 2 : 1;
+    static constexpr int WIN = TR > 2 ? 32 : 16 * TR;
+    static constexpr int LDJ = WIN | 1;
+    static constexpr bool PARK = NWIN == 2;    // the first window's rate scalars wait for the second
+};
+
+__host__ __device__ inline int whole_ldj(int ns) { return ns | 1; }
+// jc: doubles of the JC region (kLdsTiles, kLdsJac)
+__host__ __device__ inline size_t lds_doubles(LdsKind kind, int ns, size_t jc) {
+    size_t d = 4 * size_t(ns + 1);
+    if (kind == kLdsTiles) d += jc;
+    if (kind == kLdsJac) d += 3 * size_t(ns + 1) + 96 + jc;
+    if (kind == kLdsWhole) {
+        const size_t whole = size_t(ns + 1) * whole_ldj(ns) + 64;
+        d += 3 * size_t(ns + 1) + size_t(ns) + 96 + 128 + (whole > jc ? whole : jc);
+    }
     return d;
 }
-__host__ __device__ inline size_t lds_doubles(int ns, bool jac) { return lds_doubles(ns, jac, ns); }
 
-__device__ __forceinline__ Lds carve(double *b, int ns, bool jac, int win) {
+__device__ __forceinline__ Lds carve(double *b, LdsKind kind, int ns, int ldj) {
     Lds L;
-    L.ldj = ldj_of(win);
+    L.JC = L.TB = L.DWT = L.HC = L.TROW = L.IW = L.VX = nullptr;
+    L.ldj = ldj;
     L.C = b; b += ns + 1;
     L.G = b; b += ns + 1;
     L.H = b; b += ns + 1;
     L.WD = b; b += ns + 1;
-    L.IW = b; b += 64;
-    L.VX = b; b += 64;
-    if (jac) {
+    if (kind == kLdsTiles) L.JC = b;
+    if (kind == kLdsJac || kind == kLdsWhole) {
         L.TB = b; b += ns + 1;
         L.DWT = b; b += ns + 1;
         L.HC = b; b += ns + 1;
-        L.TROW = b; b += ns + 64;
+        L.TROW = b; b += kind == kLdsJac ? 96 : ns + 96;
+        if (kind == kLdsWhole) {
+            L.IW = b; b += 64;
+            L.VX = b; b += 64;
+        }
         L.JC = b;
-    } else {
-        L.JC = L.TB = L.DWT = L.HC = L.TROW = nullptr;
     }
     L.park = nullptr;
     L.cv = 0;
     return L;
 }
-__device__ __forceinline__ Lds carve(double *b, int ns, bool jac) { return carve(b, ns, jac, ns); }
 
-__device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L) {
-    const int l = lane_id();
-    L.IW[l] = l < M.nsp ? M.invW()[l] : 0.0;
+__device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L, LdsKind kind) {
+    const int l = lane_id(), ns = M.nsp;
     if (l == 0) {
-        L.C[M.nsp] = 1.0;
-        L.G[M.nsp] = 0.0;
-        L.H[M.nsp] = 0.0;
+        L.C[ns] = 1.0;
+        L.G[ns] = 0.0;
+        L.H[ns] = 0.0;
     }
-    if (L.TROW) {
-        for (int e = l; e < M.nsp + 64; e += 64) L.TROW[e] = 0.0;
-        // columns past the staged rows of JC are read (and dropped) by lanes without a species
-        for (int e = (M.nsp + 1) * L.ldj + l; e < (M.nsp + 1) * L.ldj + 64; e += 64) L.JC[e] = 0.0;
+    if (kind == kLdsJac)
+        for (int e = l; e < 96; e += 64) L.TROW[e] = 0.0;
+    if (kind == kLdsWhole) {
+        for (int e = l; e < ns + 96; e += 64) L.TROW[e] = 0.0;
+        L.IW[l] = l < ns ? M.invW()[l] : 0.0;
+        // read (and multiplied by zero) past the last staged row
+        for (int e = (ns + 1) * L.ldj + l; e < (ns + 1) * L.ldj + 64; e += 64) L.JC[e] = 0.0;
     }
     __syncthreads();
 }
@@ -253,6 +277,7 @@ __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, cons
     const int lane = lane_fresh();
     const Chain c = chain_rule(M, L, x, y0, fT);
     if (x.valid[0]) L.TROW[x.k[0]] = c.trow;
+    if (lane == 0) L.TROW[M.nsp] = 0.0;     // an FP64 step may have used it
     __syncthreads();
     JRow r;
     if (lane == 0) {
@@ -302,15 +327,18 @@ __device__ __forceinline__ void jac_rows(const DevMech &M, const Lds &L, double 
     __syncthreads();
 }
 
-// f(y) and this lane's row of M' = dg I - J' (FP64 registers; J' the Jacobian in the specific mole
-// numbers, similar to J by diag(1, W)) for N <= NP <= 64, with d wdot/dC staged in NWIN column
-// windows of WIN columns (NWIN * WIN >= ns).  The first window's reaction pass also leaves every
-// per-species sum of the chain rule, so each window's columns are final when they are read.  The
-// second window takes the first one's rate constants from the park slice when they fit (else it
-// evaluates them again).  iw and w: 1/W and W of the lane's component (1 for T, 0 for padding).
-template <int NP, int NWIN, int WIN>
-__device__ __forceinline__ void jac_rows_win(const DevMech &M, const Lds &L, double y, double P, double dg, double (&a)[NP],
-                             double &f, double &iw, double &w) {
+// f(y) and the tiles of M' = dg I - J' (J' the Jacobian in the specific mole numbers, similar to J by
+// diag(1, W)) for N <= NP <= 64.  The first window's reaction pass also leaves every per-species sum
+// of the chain rule, so each window's columns are final when they are read.  The second window takes
+// the first one's rate constants from the park slice when they fit (else it evaluates them again).
+// iw and w: 1/W and W of the lane's component (1 for T, 0 for padding).
+template <int NP>
+__device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L0, double y, double P, double dg,
+                                          wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], double &f, double &iw, double &w) {
+    using SH = WaveShape<NP>;
+    constexpr int TR = SH::TR, NWIN = SH::NWIN, WIN = SH::WIN;
+    Lds L = L0;
+    L.ldj = SH::LDJ;
     Mix<1> x;
     const double yy[1] = {y};
     double ff[1];
@@ -318,41 +346,57 @@ __device__ __forceinline__ void jac_rows_win(const DevMech &M, const Lds &L, dou
     zero_jc(L, ns);
     species_pass<1, true>(M, yy, P, L, x);
     const RxScale sc = rx_scale(L, x);
-    static_assert(NWIN == 1 || NWIN == 2, "the kept scalars serve one later window");
     const bool fits = NWIN == 2 && 3 * rx_blocks(M, 64) <= NP;
-    reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, 0, min(WIN, ns), fits ? kRatesKeep : kRates, L.park + lane_fresh(),
-                            lane_fresh());
+    reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, -1, min(WIN, ns + 1), fits ? kRatesKeep : kRates,
+                            L.park + lane_fresh(), lane_fresh());
     __syncthreads();
     finish_rhs<1>(M, L, x, ff);
     f = ff[0];
-    const Chain c = chain_rule(M, L, x, y, bcast(f, 0));
+    const Chain ch = chain_rule(M, L, x, y, bcast(f, 0));
     const int lane = lane_fresh();
-    const bool valid = x.valid[0];
-    if (valid) L.TROW[x.k[0]] = c.trow;
-    w = lane == 0 ? 1.0 : (valid ? x.W[0] : 0.0);
-    iw = lane == 0 ? 1.0 : (valid ? M.invW()[x.k[0]] : 0.0);
-    a[0] = lane == 0 ? dg - c.J00 : (valid ? -c.col0 : 0.0);
-    const double beta = valid ? c.beta : 0.0;
+    const int g = lane >> 4, c16 = lane & 15;
+    if (x.valid[0]) {
+        L.TROW[1 + x.k[0]] = ch.trow;
+        L.JC[x.k[0] * SH::LDJ] = ch.col0;
+    }
+    if (lane == 0) L.TROW[0] = ch.J00;
+    w = lane == 0 ? 1.0 : (x.valid[0] ? x.W[0] : 0.0);
+    iw = lane == 0 ? 1.0 : (x.valid[0] ? M.invW()[x.k[0]] : 0.0);
     __syncthreads();
+    double dgm[4];
 #pragma unroll
-    for (int v = 0; v < NWIN; v++) {
-        const int c0 = v * WIN;
-        if (v > 0) {
+    for (int v = 0; v < 4; v++) dgm[v] = c16 == g + 4 * v ? dg : 0.0;
+    const int nsw = opaque_s(ns);
+#pragma unroll
+    for (int wnd = 0; wnd < NWIN; wnd++) {
+        if (wnd > 0) {
             __syncthreads();
             zero_jc(L, ns);
             __syncthreads();
-            reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, c0, min(WIN, ns - c0), fits ? kScatterKept : kScatter,
-                                    L.park + lane_fresh(), lane_fresh());
+            reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, WIN - 1, min(WIN, ns + 1 - WIN),
+                                    fits ? kScatterKept : kScatter, L.park + lane_fresh(), lane_fresh());
             __syncthreads();
         }
-        // lane 0 reads the temperature row, a lane without a row its zero padding
-        const double *row = lane == 0 ? L.TROW + c0 : (valid ? &L.JC[x.k[0] * L.ldj] : L.TROW + ns);
-        const int nsw = opaque_s(ns);
 #pragma unroll
-        for (int j = 0; j < WIN; j++) {
-            if (1 + c0 + j >= NP) break;
-            a[1 + c0 + j] = c0 + j < nsw ? (lane == 1 + c0 + j ? dg : 0.0) - (row[j] + beta)
-                                         : (lane == 1 + c0 + j ? dg : 0.0);
+        for (int I = 0; I < TR; I++) {
+            // matrix row 16 I + c: the temperature row, a species row or padding (zeros)
+            const int r = 16 * I + c16;
+            const bool sp = r >= 1 && r <= nsw;
+            const double *row = sp ? &L.JC[(r - 1) * SH::LDJ] : (r == 0 ? L.TROW + WIN * wnd : L.TROW + 64);
+            const double beta = sp ? L.TB[sp ? r - 1 : 0] : 0.0;
+#pragma unroll
+            for (int J = WIN / 16 * wnd; J < TR && J < WIN / 16 * (wnd + 1); J++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int c0 = 16 * J + 4 * v;      // matrix columns c0 + g
+                    if (c0 >= NP) {
+                        X[J][I][v] = 0.0;
+                        continue;
+                    }
+                    // beta on species columns: all but the temperature's and the padding's
+                    const double b = c0 == 0 ? (g == 0 ? 0.0 : beta) : (c0 + 3 < NP - 8 || c0 + g <= nsw ? beta : 0.0);
+                    X[J][I][v] = (I == J ? dgm[v] : 0.0) - (row[c0 - WIN * wnd + g] + b);
+                }
         }
     }
     __syncthreads();
@@ -375,128 +419,42 @@ __device__ __forceinline__ double jac_times(const DevMech &M, const Lds &L, cons
 }
 
 // ---------------------------------------------------------------------------------------
-// dense LU with partial pivoting, one row per lane, fully unrolled over NP columns
-// ---------------------------------------------------------------------------------------
-template <int NP>
-struct LU {
-    int pivv;         // lane k holds the lane of the pivot row of column k
-    int ord;          // this lane's pivot order
-    double dinv;      // 1 / U[ord][ord]
-    bool ok;
-};
-
-template <int NP>
-__device__ __forceinline__ void lu_factor(double (&a)[NP], LU<NP> &f) {
-    const int lane = lane_id();
-    bool done = false;
-    f.ord = NP;
-    f.dinv = 0.0;
-    f.ok = true;
-    f.pivv = 0;
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        // pivot search on the high word of |a| (ordered like |a|; candidates within a relative 2^-20
-        // of the largest may tie, and the first lane is taken)
-        const unsigned key = done ? 0u : unsigned(__double2hiint(fabs(a[k])));
-        const unsigned mx = __ockl_wfred_max_u32(key);
-        const int p = __builtin_ctzll(__ballot(!done && key == mx));
-        if (lane == k) f.pivv = p;
-        f.ok = f.ok && (mx != 0u);
-        // 1 / pivot: hardware reciprocal estimate refined by two Newton-Raphson steps (within an
-        // ulp; a shorter dependency chain than the correctly rounded division)
-        const double piv = bcast(a[k], p);
-        double inv = __builtin_amdgcn_rcp(piv);
-        inv = fma(fma(-piv, inv, 1.0), inv, inv);
-        inv = fma(fma(-piv, inv, 1.0), inv, inv);
-        if (lane == p) {
-            done = true;
-            f.ord = k;
-            f.dinv = inv;
-        }
-        const double l = done ? 0.0 : a[k] * inv;
-        if (!done) a[k] = l;
-#pragma unroll
-        for (int j = k + 1; j < NP; j++) a[j] = fma(-l, bcast(a[j], p), a[j]);
-    }
-}
-
-// Solve (L U) x = P b; b and x distributed one component per lane.
-template <int NP>
-__device__ __forceinline__ double lu_solve(const double (&a)[NP], const LU<NP> &f, double b) {
-    const int lane = lane_fresh();
-    const int pivv = opaque(f.pivv);
-    const int ord = opaque(f.ord);
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        const double yk = bcast(b, __builtin_amdgcn_readlane(pivv, k));
-        if (ord > k) b = fma(-a[k], yk, b);
-    }
-    double x = 0.0;
-#pragma unroll
-    for (int k = NP - 1; k >= 0; k--) {
-        const double xk = bcast(b * f.dinv, __builtin_amdgcn_readlane(pivv, k));
-        if (lane == k) x = xk;
-        if (ord < k) b = fma(-a[k], xk, b);
-    }
-    return x;
-}
-
-// ---------------------------------------------------------------------------------------
 // one steps
 // ---------------------------------------------------------------------------------------
-// Window count and width of the staged d wdot/dC for a padded size NP, and whether the kernel
-// uses a parking slice in the workspace (raw Jacobian window entries and the first window's
-// per-reaction rate scalars; the forward-difference step also parks its Jacobian columns and
-// its LU rows there).
+// Stages of a ROS4 step with the inverted matrix in tiles; iw scales a right-hand side, w a solution
+// (the tiles are those of M in the variables z = y / w).
 template <int NP>
-struct WaveShape {
-    static constexpr int NWIN = NP > 32 ? 2 : 1;
-    static constexpr int WIN = NWIN == 1 ? 0 : (NP - 1 + NWIN - 1) / NWIN;   // 0: all ns columns
-    static constexpr bool PARK = NP > 32;
-};
-
-template <int NP>
-__device__ __forceinline__ void park_rows(const Lds &L, const double (&a)[NP]) {
-    double *r = L.park + lane_fresh();
-#pragma unroll
-    for (int j = 0; j < NP; j++) r[j * 64] = a[j];
-}
-template <int NP>
-__device__ __forceinline__ void unpark_rows(const Lds &L, double (&a)[NP]) {
-    const double *r = L.park + lane_fresh();
-#pragma unroll
-    for (int j = 0; j < NP; j++) a[j] = r[j * 64];
+__device__ __forceinline__ void ros4_stages(const DevMech &M, const Lds &L, double y, double P, double h,
+                                            const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int ord,
+                                            double f, double iw, double w, double &ynew, double &e) {
+    const int lane = lane_fresh();
+    auto solve = [&](double b) { return w * wt_solve<NP>(X, s, lane, ord, iw * b); };
+    const double ih = 1.0 / h;
+    const double u1 = solve(f);
+    // the inverse stays in registers across the stage source terms
+    double yt[1] = {y + Ros4::a21 * u1}, ft[1];
+    rhs_wave<1>(M, L, yt, P, ft);
+    const double u2 = solve(ft[0] + (Ros4::c21 * u1) * ih);
+    yt[0] = y + Ros4::a31 * u1 + Ros4::a32 * u2;
+    rhs_wave<1>(M, L, yt, P, ft);
+    const double u3 = solve(ft[0] + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih);
+    const double u4 = solve(ft[0] + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih);
+    ynew = y + Ros4::m1 * u1 + Ros4::m2 * u2 + Ros4::m3 * u3 + Ros4::m4 * u4;
+    e = Ros4::e1 * u1 + Ros4::e2 * u2 + Ros4::e3 * u3 + Ros4::e4 * u4;
 }
 
-// FULLJC: d wdot/dC staged whole (the FP32-mode LDS layout), no column windows.  The stage systems
-// are solved in the specific mole numbers (iw scales a right-hand side, w a solution).
-template <int NP, bool FULLJC = false>
+template <int NP>
 struct Ros4Wave {
-    using SH = WaveShape<NP>;
-    static constexpr double qinv = 0.25;
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, double y, double P, double h, double &ynew,
                                 double &e) {
-        double a[NP];
+        wd4 X[WTile<NP>::TR][WTile<NP>::TR];
         double f, iw, w;
-        const double dg = 1.0 / (Ros4::gamma * h);
-        if (SH::NWIN == 1 || FULLJC) jac_rows_win<NP, 1, NP - 1>(M, L, y, P, dg, a, f, iw, w);
-        else jac_rows_win<NP, SH::NWIN, SH::WIN>(M, L, y, P, dg, a, f, iw, w);
-        LU<NP> lu;
-        lu_factor<NP>(a, lu);
-        const double ih = 1.0 / h;
-        const double u1 = w * lu_solve<NP>(a, lu, iw * f);
-        // the factored rows stay in registers across the stage source terms (it fits without spills)
-        double yt[1] = {y + Ros4::a21 * u1}, ft[1];
-        rhs_wave<1>(M, L, yt, P, ft);
-        const double u2 = w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c21 * u1) * ih));
-        yt[0] = y + Ros4::a31 * u1 + Ros4::a32 * u2;
-        rhs_wave<1>(M, L, yt, P, ft);
-        const double u3 = w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih));
-        const double u4 =
-            w * lu_solve<NP>(a, lu, iw * (ft[0] + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih));
-        ynew = y + Ros4::m1 * u1 + Ros4::m2 * u2 + Ros4::m3 * u3 + Ros4::m4 * u4;
-        e = Ros4::e1 * u1 + Ros4::e2 * u2 + Ros4::e3 * u3 + Ros4::e4 * u4;
-        return lu.ok;
+        jac_tiles<NP>(M, L, y, P, 1.0 / (Ros4::gamma * h), X, f, iw, w);
+        const WScratch s = wt_scratch<NP>(L.JC);
+        int ord;
+        const bool ok = wt_invert<NP>(X, s, lane_fresh(), ord);
+        ros4_stages<NP>(M, L, y, P, h, X, s, ord, f, iw, w, ynew, e);
+        return ok;
     }
 };
 
@@ -505,12 +463,13 @@ struct Ros4Wave {
 //   inc_j = max(sqrt(eps) |y_j|, min_inc (rtol |y_j| + atol)),
 //   min_inc = 1000 |h| eps N ||f(y)||_w (1 if that norm is 0), w_i = 1 / (rtol |y_i| + atol),
 // as CVODE's dense difference quotient.  Columns are written to the parking slice (lane i holds
-// row i), then loaded as the lane's row; f(y) doubles as the first stage's right-hand side.
+// row i), then loaded as tiles; f(y) doubles as the first stage's right-hand side.
 template <int NP>
 struct Ros4WaveFD {
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, double y, double P, double h,
                                                 double &ynew, double &e, const IntOpts &o) {
         constexpr double eps = 2.220446049250313e-16;
+        constexpr int TR = WTile<NP>::TR;
         const int N = M.N;
         const int lane = lane_fresh();
         const bool comp = lane < N;
@@ -530,30 +489,25 @@ struct Ros4WaveFD {
                 pk[j * 64] = comp ? (fj[0] - f0[0]) / inc : 0.0;   // J[lane][j]
             }
         }
+        __syncthreads();      // lanes read each other's columns below
         const double dg = 1.0 / (Ros4::gamma * h);
-        double a[NP];
-        {
-            const double *pk = L.park + lane_fresh();
+        wd4 X[TR][TR];
+        const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
-            for (int j = 0; j < NP; j++) a[j] = (lane == j ? dg : 0.0) - (j < N ? pk[j * 64] : 0.0);
-        }
-        LU<NP> lu;
-        lu_factor<NP>(a, lu);
-        const double ih = 1.0 / h;
-        const double u1 = lu_solve<NP>(a, lu, f0[0]);
-        park_rows<NP>(L, a);
-        double yt[1] = {y + Ros4::a21 * u1}, ft[1];
-        rhs_wave<1>(M, L, yt, P, ft);
-        unpark_rows<NP>(L, a);
-        const double u2 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c21 * u1) * ih);
-        yt[0] = y + Ros4::a31 * u1 + Ros4::a32 * u2;
-        rhs_wave<1>(M, L, yt, P, ft);
-        unpark_rows<NP>(L, a);
-        const double u3 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih);
-        const double u4 = lu_solve<NP>(a, lu, ft[0] + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih);
-        ynew = y + Ros4::m1 * u1 + Ros4::m2 * u2 + Ros4::m3 * u3 + Ros4::m4 * u4;
-        e = Ros4::e1 * u1 + Ros4::e2 * u2 + Ros4::e3 * u3 + Ros4::e4 * u4;
-        return lu.ok;
+        for (int J = 0; J < TR; J++)
+#pragma unroll
+            for (int I = 0; I < TR; I++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int row = 16 * I + c16, col = 16 * J + g + 4 * v;
+                    const double d = (I == J && c16 == g + 4 * v && col < NP) ? dg : 0.0;
+                    X[J][I][v] = d - (row < N && col < N ? L.park[col * 64 + row] : 0.0);
+                }
+        const WScratch s = wt_scratch<NP>(L.JC);
+        int ord;
+        const bool ok = wt_invert<NP>(X, s, lane_fresh(), ord);
+        ros4_stages<NP>(M, L, y, P, h, X, s, ord, f0[0], 1.0, 1.0, ynew, e);
+        return ok;
     }
 };
 
@@ -680,7 +634,7 @@ struct Ros4Wave32 {
         const bool ok = step32(M, L, y, P, h, ynew, e, sweeps, conv);
         if (conv) return ok;
         fb++;
-        return Ros4Wave<NP, true>::step(M, L, y, P, h, ynew, e);
+        return Ros4Wave<NP>::step(M, L, y, P, h, ynew, e);
     }
 };
 
@@ -756,8 +710,9 @@ template <int NP>
 struct Ros4Adapter {
     static constexpr int RPL = 1;
     static constexpr int NSMAX = NP - 1;
-    static constexpr bool JAC = true;
-    static constexpr int WIN = WaveShape<NP>::WIN;
+    static constexpr LdsKind LDS = kLdsJac;
+    static constexpr int LDJ = WaveShape<NP>::LDJ;
+    static constexpr int kJc = NP * LDJ > WTile<NP>::kScratch ? NP * LDJ : WTile<NP>::kScratch;
     static constexpr bool PARK = WaveShape<NP>::PARK;
     static constexpr int PARK_ROWS = NP;
     static constexpr double qinv = 0.25;
@@ -771,8 +726,9 @@ template <int NP>
 struct Ros4AdapterFD {
     static constexpr int RPL = 1;
     static constexpr int NSMAX = NP - 1;
-    static constexpr bool JAC = false;      // no d wdot/dC staging: only source-term evaluations
-    static constexpr int WIN = 0;
+    static constexpr LdsKind LDS = kLdsTiles;      // no d wdot/dC staging: only source-term evaluations
+    static constexpr int LDJ = 0;
+    static constexpr int kJc = WTile<NP>::kScratch;
     static constexpr bool PARK = true;
     static constexpr int PARK_ROWS = NP;
     static constexpr double qinv = 0.25;
@@ -786,10 +742,11 @@ template <int NP>
 struct Ros4Adapter32 {
     static constexpr int RPL = 1;
     static constexpr int NSMAX = NP - 1;
-    static constexpr bool JAC = true;
-    static constexpr int WIN = 0;
-    static constexpr bool PARK = false;
-    static constexpr int PARK_ROWS = 0;
+    static constexpr LdsKind LDS = kLdsWhole;
+    static constexpr int LDJ = NSMAX | 1;
+    static constexpr int kJc = Ros4Adapter<NP>::kJc;      // the FP64 step of a refactored solve
+    static constexpr bool PARK = WaveShape<NP>::PARK;
+    static constexpr int PARK_ROWS = NP;
     static constexpr double qinv = 0.25;
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, const double (&y)[1], double P, double h,
                                 double (&yn)[1], double (&e)[1], const IntOpts &o, int &fb) {
@@ -919,8 +876,9 @@ template <int R>
 struct Rkf45S {
     static constexpr int RPL = R;
     static constexpr int NSMAX = 64 * R - 1;
-    static constexpr bool JAC = false;
-    static constexpr int WIN = 0;
+    static constexpr LdsKind LDS = kLdsRhs;
+    static constexpr int LDJ = 0;
+    static constexpr int kJc = 0;
     static constexpr bool PARK = false;
     static constexpr int PARK_ROWS = 0;
     static constexpr double qinv = 0.2;
@@ -948,10 +906,10 @@ template <int RPL>
 __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
                                                       const double *p, double *dydt, int cv) {
     // laid out for the largest species count of the instantiation, so every offset is a constant
-    __shared__ double lds_raw[4 * 64 * RPL + 128];
-    Lds L = carve(lds_raw, 64 * RPL - 1, false, 0);
+    __shared__ double lds_raw[4 * 64 * RPL];
+    Lds L = carve(lds_raw, kLdsRhs, 64 * RPL - 1, 0);
     L.cv = cv;
-    init_lds(M, L);
+    init_lds(M, L, kLdsRhs);
     const int N = M.N, lane = lane_id();
     const int64_t nb = int64_t(gridDim.x);
     const int64_t r = xcd_reactor(blockIdx.x, nb);
@@ -973,9 +931,9 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
 __global__ void __launch_bounds__(64) jac_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
                                                       const double *p, double *jac, int cv) {
     extern __shared__ double lds_raw[];
-    Lds L = carve(lds_raw, M.nsp, true);
+    Lds L = carve(lds_raw, kLdsWhole, M.nsp, whole_ldj(M.nsp));
     L.cv = cv;
-    init_lds(M, L);
+    init_lds(M, L, kLdsWhole);
     const int N = M.N, lane = lane_id();
     const int64_t r = xcd_reactor(blockIdx.x, int64_t(gridDim.x));
     if (r >= n) return;
@@ -998,10 +956,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // LDS laid out for the largest species count of the instantiation: every offset is a
     // compile-time constant, so LDS addresses need no scalar registers
     extern __shared__ double lds_raw[];
-    Lds L = carve(lds_raw, S::NSMAX, S::JAC, S::WIN > 0 ? S::WIN : S::NSMAX);
+    Lds L = carve(lds_raw, S::LDS, S::NSMAX, S::LDJ);
     L.cv = o.reactor;
     if (S::PARK) L.park = park + size_t(blockIdx.x) * (size_t(S::PARK_ROWS) * 64);
-    init_lds(M, L);
+    init_lds(M, L, S::LDS);
     for (;;) {
         unsigned v = 0;
         if (lane_id() == 0) v = atomicAdd(queue, 1u);
@@ -1028,7 +986,7 @@ int launch_int(const DevMech &M, int64_t n, double *y, int64_t ld, const double 
                double *h, const IntOpts &o, unsigned *queue, int32_t *status, int32_t *nacc, int32_t *nrej,
                hipStream_t s) {
     if (M.nsp > S::NSMAX) return CK_EUNSUPPORTED;
-    const size_t lds = lds_doubles(S::NSMAX, S::JAC, S::WIN > 0 ? S::WIN : S::NSMAX) * sizeof(double);
+    const size_t lds = lds_doubles(S::LDS, S::NSMAX, S::kJc) * sizeof(double);
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return CK_EHIP;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return CK_EHIP;
@@ -1072,7 +1030,7 @@ int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, co
 int launch_jac_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac,
                     int cv, hipStream_t s) {
     if (M.N > 64) return cv ? CK_EUNSUPPORTED : launch_jac_coop(M, n, y, ld, p, jac, s);
-    const size_t lds = lds_doubles(M.nsp, true) * sizeof(double);
+    const size_t lds = lds_doubles(kLdsWhole, M.nsp, 0) * sizeof(double);
     const unsigned grid = unsigned((n + 7) / 8 * 8);
     jac_wave_kernel<<<dim3(grid), dim3(64), lds, s>>>(M, n, y, ld, p, jac, cv);
     return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;

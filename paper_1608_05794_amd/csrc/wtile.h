@@ -1,0 +1,225 @@
+// Dense linear algebra of one wavefront (N <= 64): the iteration matrix in 16 x 16 register tiles and
+// its inverse by blocked Gauss-Jordan elimination with partial pivoting, rank-16 updates on the FP64
+// matrix cores; stage solves are matrix-vector products.
+//
+// Layout.  Lane l = 16 g + c.  Tile X[J][I] holds the TRANSPOSE of the matrix block (I, J) in the
+// accumulator layout of the 16x16x4 instruction: register v of lane (g, c) is
+//     A[16 I + c][16 J + g + 4 v]     (FP64 instruction: rows of the accumulator interleave over g).
+// Transposed, an update A[:, J] += T U[:, J] is X[J][I] += U^T T^T, whose B operand (lane (g, c) holds
+// T[16 I + c][4 s + g]) is register s of the eliminated panel's own tile, so the panel is not loaded a
+// second time; the A operand is the panel's pivot rows, read from LDS.  A matrix-vector product is
+// 16 TR multiply-adds per lane and row block and a sum over the four lane groups that leaves row
+// 16 g + c on lane (g, c), i.e. one component per lane.
+//
+// Why this form (measured at N = 54, M53, 16384 reactors to 1e-13 s): the register LU with one row per
+// lane spent about 6300 vector instructions on the factorisation (two lane reads and a hazard wait per
+// multiply-add, in a serial chain per column) and 900 on each of the four substitutions, of 17.2 k a
+// step.  Here a panel costs one pivot search and 15 broadcast columns per pivot, the other columns go
+// to the matrix cores, and a solve is about 80 instructions.
+#pragma once
+
+#include "kinetics.h"
+
+extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
+
+namespace ck {
+
+typedef double wd4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double wt_readlane(double v, int src) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
+    return __hiloint2double(hi, lo);
+}
+
+// Halves of two registers exchanged between the lane halves (32) or between even and odd rows of 16
+// lanes (16), then added: lanes of the lower half (even rows) get the sum of a over the pair, the
+// others that of b.
+__device__ __forceinline__ double wt_fold32(double a, double b) {
+    auto lo = __builtin_amdgcn_permlane32_swap(unsigned(__double2loint(a)), unsigned(__double2loint(b)), false, false);
+    auto hi = __builtin_amdgcn_permlane32_swap(unsigned(__double2hiint(a)), unsigned(__double2hiint(b)), false, false);
+    return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+}
+__device__ __forceinline__ double wt_fold16(double a, double b) {
+    auto lo = __builtin_amdgcn_permlane16_swap(unsigned(__double2loint(a)), unsigned(__double2loint(b)), false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap(unsigned(__double2hiint(a)), unsigned(__double2hiint(b)), false, false);
+    return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+}
+
+template <int NP>
+struct WTile {
+    static_assert(NP % 8 == 0 && NP <= 64, "one wavefront: up to 64 rows");
+    static constexpr int TR = (NP + 15) / 16;     // tiles per side
+    // column stride of the panel buffer and row stride of the pivot rows (doubles): 4 over a multiple
+    // of 16, so the four lane groups of an access start in different banks
+    static constexpr int PLD = 16 * TR + 4;
+    static constexpr int kScratch = 16 * PLD + 64 + 64 + 32;   // panel / pivot rows, vectors, pivot orders
+    using Mat = wd4[TR][TR];
+};
+
+// Scratch in LDS (WTile::kScratch doubles): PNL and the pivot rows UB share one buffer.
+struct WScratch {
+    double *PNL, *BS, *XS;
+    int *ORD;
+};
+template <int NP>
+__device__ __forceinline__ WScratch wt_scratch(double *b) {
+    WScratch s;
+    s.PNL = b;
+    s.BS = b + 16 * WTile<NP>::PLD;
+    s.XS = s.BS + 64;
+    s.ORD = reinterpret_cast<int *>(s.XS + 64);
+    return s;
+}
+
+// In-place inverse of the leading NP x NP block (the caller pads rows and columns N..NP-1 with a
+// nonzero diagonal and the rest with zeros).  On return lane r holds in `ord` the pivot order of row
+// r: row r of the tiles is row ord of the inverse, its column 16 J + j the one that belongs to the
+// row of pivot order 16 J + j.  False if a pivot column was zero.
+template <int NP>
+__device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane, int &ord) {
+    constexpr int TR = WTile<NP>::TR, PLD = WTile<NP>::PLD;
+    const int g = lane >> 4, c16 = lane & 15;
+    bool done = lane >= NP, ok = true;
+    ord = NP;
+#pragma unroll 1
+    for (int p = 0; p < TR; p++) {
+        // the panel (tile column 0; tile columns rotate) with one row per lane
+        double R[16];
+#pragma unroll
+        for (int I = 0; I < TR; I++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) s.PNL[(g + 4 * v) * PLD + 16 * I + c16] = X[0][I][v];
+        __syncthreads();
+        const int lr = TR == 4 ? lane : min(lane, 16 * TR - 1);
+#pragma unroll
+        for (int j = 0; j < 16; j++) R[j] = s.PNL[j * PLD + lr];
+        __syncthreads();
+        // Gauss-Jordan in the panel, columns rotating so that the pivot column is R[0].  A pivot row
+        // stays unscaled (its multiplier is 0, its own entry 1) and takes the factor 1 / pivot once
+        // at the end: every later step is linear in the row.
+        const int npv = (NP % 16 != 0 && p == TR - 1) ? NP % 16 : 16;
+        double scale = 1.0;
+#pragma unroll 1
+        for (int c = 0; c < npv; c++) {
+            // pivot search on the high word of |a| (ordered like |a|; values within a relative 2^-20
+            // of the largest may tie, and then the first lane is taken)
+            const unsigned key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
+            const unsigned mx = __ockl_wfred_max_u32(key);
+            ok = ok && mx != 0u;
+            const int src = __builtin_ctzll(__ballot(!done && key == mx));
+            const double rp = ck_rcp(wt_readlane(R[0], src));
+            const bool me = lane == src;
+            const double gm = me ? 0.0 : -R[0] * rp;
+            const double last = me ? 1.0 : gm;
+#pragma unroll
+            for (int j = 1; j < 16; j++) R[j - 1] = fma(gm, wt_readlane(R[j], src), R[j]);
+            R[15] = last;
+            done = done || me;
+            scale = me ? rp : scale;
+            ord = me ? 16 * p + c : ord;
+        }
+        // npv rotations leave column j in R[(j - npv) mod 16]
+        const int rot = npv & 15;
+#pragma unroll
+        for (int j = 0; j < 16; j++)
+            if (lane < 16 * TR) s.PNL[((j + rot) & 15) * PLD + lane] = R[j] * scale;
+        s.ORD[lane] = ord;
+        __syncthreads();
+#pragma unroll
+        for (int I = 0; I < TR; I++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) X[0][I][v] = s.PNL[(g + 4 * v) * PLD + 16 * I + c16];
+        if (TR > 1) {
+            int o[TR];
+#pragma unroll
+            for (int I = 0; I < TR; I++) o[I] = s.ORD[16 * I + c16] - 16 * p;
+            __syncthreads();
+            // pivot rows of the other columns into UB (= PNL, the panel is in registers) by pivot
+            // order, and out of the tiles
+#pragma unroll
+            for (int I = 0; I < TR; I++)
+                if (o[I] >= 0 && o[I] < 16) {
+#pragma unroll
+                    for (int J = 1; J < TR; J++)
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            s.PNL[o[I] * PLD + 16 * J + g + 4 * v] = X[J][I][v];
+                            X[J][I][v] = 0.0;
+                        }
+                }
+            __syncthreads();
+#pragma unroll
+            for (int J = 1; J < TR; J++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    if (NP % 16 != 0 && 4 * k >= npv) break;     // no pivots of these orders
+                    const double u = s.PNL[(4 * k + g) * PLD + 16 * J + c16];
+#pragma unroll
+                    for (int I = 0; I < TR; I++)
+                        X[J][I] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, X[0][I][k], X[J][I], 0, 0, 0);
+                }
+            __syncthreads();
+            // the next panel becomes tile column 0
+            wd4 t[TR];
+#pragma unroll
+            for (int I = 0; I < TR; I++) t[I] = X[0][I];
+#pragma unroll
+            for (int J = 0; J + 1 < TR; J++)
+#pragma unroll
+                for (int I = 0; I < TR; I++) X[J][I] = X[J + 1][I];
+#pragma unroll
+            for (int I = 0; I < TR; I++) X[TR - 1][I] = t[I];
+        }
+    }
+    return ok;
+}
+
+// x = A^-1 b from the inverted tiles; b and x one component per lane.
+template <int NP>
+__device__ __forceinline__ double wt_solve(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane,
+                                           int ord, double b) {
+    constexpr int TR = WTile<NP>::TR;
+    const int g = lane >> 4;
+    // b by pivot order, permuted so that the values a lane needs (orders 16 J + g + 4 v) are contiguous:
+    // order o at 16 (o % 4) + o / 4
+    if (ord < NP) s.BS[16 * (ord & 3) + (ord >> 2)] = b;
+    __syncthreads();
+    double bs[4 * TR];
+#pragma unroll
+    for (int k = 0; k < 4 * TR; k++) bs[k] = 4 * k < NP ? s.BS[16 * g + k] : 0.0;
+    double z[4];
+#pragma unroll
+    for (int I = 0; I < TR; I++) {
+        double a = 0.0, b2 = 0.0;     // two chains
+#pragma unroll
+        for (int J = 0; J < TR; J++) {
+            a = fma(X[J][I][0], bs[4 * J], a);
+            b2 = fma(X[J][I][1], bs[4 * J + 1], b2);
+            if (16 * J + 8 < NP) {
+                a = fma(X[J][I][2], bs[4 * J + 2], a);
+                b2 = fma(X[J][I][3], bs[4 * J + 3], b2);
+            }
+        }
+        z[I] = a + b2;
+    }
+    // sum over the lane groups; group g keeps row block I = g
+    double r;
+    if (TR == 1) {
+        const double h = wt_fold32(z[0], z[0]);
+        r = wt_fold16(h, h);
+    } else if (TR == 2) {
+        const double h0 = wt_fold32(z[0], z[0]), h1 = wt_fold32(z[1], z[1]);
+        r = wt_fold16(h0, h1);
+    } else {
+        const double h0 = wt_fold32(z[0], z[2]), h1 = wt_fold32(z[1], TR == 4 ? z[TR - 1] : z[1]);
+        r = wt_fold16(h0, h1);
+    }
+    if (ord < NP) s.XS[ord] = r;
+    __syncthreads();
+    const double x = lane < NP ? s.XS[lane] : 0.0;
+    __syncthreads();
+    return x;
+}
+
+}  // namespace ck
