@@ -148,6 +148,93 @@ struct Packer {
     size_t add(const std::vector<T> &v) { return add(v.data(), v.size() * sizeof(T)); }
 };
 
+// A pair-form reaction in the order of storage: its stored index and the species of its four slots
+// (nsp: the null species).
+struct PairUnits {
+    int id;
+    int sp[4];
+    int type;
+};
+
+// Cost of the LDS atomics of 16 consecutive lanes.  An FP64 LDS atomic is served 16 lanes at a time,
+// two cycles per pass over 16 banks of 8 bytes, and lanes that meet in a bank take turns (measured:
+// 8.4 cycles for 64 lanes without a conflict, 16.5 / 32 / 129 with 2 / 4 / 16 lanes per bank, 30 for
+// random species).  The cost is the largest bank load, summed over the accesses of a ROS4 step: six
+// per slot to the per-species arrays (four in the Jacobian pass, one in each stage source term) and
+// the d wdot/dC entries of the two column windows of width `win`.
+int bank_cost(const PairUnits *r, int n, int nsp, int win) {
+    auto heaviest = [](const int *bank, int k) {
+        unsigned char load[16] = {0};
+        int m = 0;
+        for (int i = 0; i < k; i++) m = std::max(m, int(++load[bank[i] & 15]));
+        return m;
+    };
+    int cost = 0, bank[16], id[16];
+    for (int b = 0; b < 4; b++) {
+        int k = 0;
+        for (int i = 0; i < n; i++)
+            if (r[i].sp[b] != nsp) bank[k++] = r[i].sp[b];
+        cost += 6 * heaviest(bank, k);
+        for (int w = 0; w < 2; w++) {
+            k = 0;
+            for (int i = 0; i < n; i++) {
+                const int col = r[i].sp[b] + 1;
+                if (r[i].sp[b] != nsp && col / win == w) id[k++] = i;
+            }
+            if (k < 2) {
+                cost += 4 * k;
+                continue;
+            }
+            for (int a = 0; a < 4; a++) {
+                for (int j = 0; j < k; j++) bank[j] = r[id[j]].sp[a] * (win | 1) + r[id[j]].sp[b] + 1 - win * w;
+                cost += heaviest(bank, k);
+            }
+        }
+    }
+    return cost;
+}
+
+// Rearranges pair-form reactions over the lanes (within their type, so that the leading blocks keep
+// the fall-off reactions) and the two species of a side over their slots, to keep the lanes of a
+// group apart in the LDS banks: first-improvement descent over random exchanges, 60 per reaction
+// (M53: largest bank load 3.1 -> 2.0 per species access, 2.1 -> 1.6 per Jacobian entry; 30 ms, once
+// per loaded mechanism).
+void spread_over_banks(std::vector<PairUnits> &v, int nsp) {
+    const int n = int(v.size()), N = nsp + 1;
+    if (n < 2) return;
+    const int win = N > 64 ? (N + 15) / 16 * 8 : (N > 32 ? 32 : (N + 15) / 16 * 16);
+    auto count = [&](int g) { return std::min(16, n - 16 * g); };
+    std::vector<int> cost((n + 15) / 16);
+    for (size_t g = 0; g < cost.size(); g++) cost[g] = bank_cost(&v[16 * g], count(int(g)), nsp, win);
+    uint32_t seed = 12345;
+    auto draw = [&](int m) {
+        seed = seed * 1664525u + 1013904223u;
+        return int((uint64_t(seed >> 8) * uint64_t(m)) >> 24);
+    };
+    for (int move = 0; move < 60 * n; move++) {
+        const int i = draw(n), gi = i / 16, kind = draw(6);
+        if (kind < 2) {
+            int &a = v[i].sp[2 * kind], &b = v[i].sp[2 * kind + 1];
+            if (a == b || b == nsp) continue;
+            std::swap(a, b);
+            const int c = bank_cost(&v[16 * gi], count(gi), nsp, win);
+            if (c <= cost[gi]) cost[gi] = c;
+            else std::swap(a, b);
+        } else {
+            const int j = draw(n), gj = j / 16;
+            if (gi == gj || v[i].type != v[j].type) continue;
+            std::swap(v[i], v[j]);
+            const int ci = bank_cost(&v[16 * gi], count(gi), nsp, win), cj = bank_cost(&v[16 * gj], count(gj), nsp, win);
+            if (ci + cj <= cost[gi] + cost[gj]) {
+                cost[gi] = ci;
+                cost[gj] = cj;
+            } else {
+                std::swap(v[i], v[j]);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
@@ -174,11 +261,11 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
             spd[size_t(10 + j) * ns + k] = hm.ahigh[7 * k + j];
         }
     }
-    // Stored order (stable): reactions that are not pair-form first, then by type, the most complex
-    // first, and within a type by species slot count, the fewest first.  The kernels hand
-    // consecutive blocks of 64 reactions to the lanes of a wavefront, and a block pays for the most
-    // complex type it holds, so the few third-body and fall-off reactions share the leading blocks
-    // and the ragged last block holds elementary ones only.
+    // Stored order: reactions that are not pair-form first, then by type, the most complex first.  The
+    // kernels hand consecutive blocks of 64 reactions to the lanes of a wavefront, and a block pays
+    // for the most complex type it holds, so the few third-body and fall-off reactions share the
+    // leading blocks and the ragged last block holds elementary ones only.  Within a type the lanes
+    // of pair-form reactions are chosen by their LDS banks.
     std::vector<int> order(nr);
     std::iota(order.begin(), order.end(), 0);
     auto units = [](const std::vector<int> &nu) { return std::accumulate(nu.begin(), nu.end(), 0); };
@@ -187,17 +274,29 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
         const int r = units(x.rnu), p = units(x.pnu);
         return x.rev && r >= 1 && r <= 2 && p >= 1 && p <= 2;
     };
-    auto slots = [&](int i) { return hm.rx[i].rsp.size() + hm.rx[i].psp.size(); };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         if (pair_form(a) != pair_form(b)) return !pair_form(a);
-        if (hm.rx[a].type != hm.rx[b].type) return hm.rx[a].type > hm.rx[b].type;
-        return slots(a) < slots(b);
+        return hm.rx[a].type > hm.rx[b].type;
     });
     int n_gen = 0, n_fall = 0;
     for (int i = 0; i < nr; i++) {
         n_gen += !pair_form(i);
         n_fall += pair_form(i) && hm.rx[i].type != kElementary;
     }
+    std::vector<PairUnits> units_of(nr - n_gen);
+    for (int ii = n_gen; ii < nr; ii++) {
+        const auto &x = hm.rx[order[ii]];
+        PairUnits &u = units_of[ii - n_gen];
+        u.id = order[ii];
+        u.type = x.type;
+        std::fill(u.sp, u.sp + 4, ns);
+        for (size_t j = 0, c = 0; j < x.rsp.size(); j++)
+            for (int v = 0; v < x.rnu[j]; v++) u.sp[c++] = x.rsp[j];
+        for (size_t j = 0, c = 2; j < x.psp.size(); j++)
+            for (int v = 0; v < x.pnu[j]; v++) u.sp[c++] = x.psp[j];
+    }
+    spread_over_banks(units_of, ns);
+    for (int ii = n_gen; ii < nr; ii++) order[ii] = units_of[ii - n_gen].id;
     std::vector<PairBlock> pair(std::max((nr - n_gen + 63) / 64, 1));
     std::memset(pair.data(), 0, pair.size() * sizeof(PairBlock));
     std::vector<RxnRec> rx(std::max(nr, 1));
@@ -251,11 +350,7 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
         if (ii >= n_gen) {
             PairBlock &B = pair[(ii - n_gen) / 64];
             const int l = (ii - n_gen) % 64;
-            int u[4] = {ns, ns, ns, ns};
-            for (size_t j = 0, c = 0; j < x.rsp.size(); j++)
-                for (int v = 0; v < x.rnu[j]; v++) u[c++] = x.rsp[j];
-            for (size_t j = 0, c = 2; j < x.psp.size(); j++)
-                for (int v = 0; v < x.pnu[j]; v++) u[c++] = x.psp[j];
+            const int *u = units_of[ii - n_gen].sp;
             B.lnA[l] = R.lnA;
             B.beta[l] = R.beta;
             B.EaR[l] = R.EaR;

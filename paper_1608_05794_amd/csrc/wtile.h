@@ -18,9 +18,9 @@
 // to the matrix cores, and a solve is about 80 instructions.
 #pragma once
 
-#include "kinetics.h"
+#include <type_traits>
 
-extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
+#include "kinetics.h"
 
 namespace ck {
 
@@ -31,6 +31,49 @@ __device__ __forceinline__ double wt_readlane(double v, int src) {
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
     return __hiloint2double(hi, lo);
 }
+
+// f(integral_constant<i>) for i in [B, E).
+template <int B, int E, class F>
+__device__ __forceinline__ void wt_for(F &&f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        wt_for<B + 1, E>(static_cast<F &&>(f));
+    }
+}
+
+// Search for the next pivot and its reciprocal, cut into short stages of one dependency chain.  The
+// pivot is the lane with the largest high word of |a| (ordered like |a|; values within a relative
+// 2^-20 of the largest may tie, and then the first lane is taken); key is 0 for rows already used.
+// Stages 0..5: largest key (rows of 16 lanes, then each row's last lane into the next row and row 1's
+// into the upper half); 6, 7: lane; 8, 9: 1 / pivot estimate; 10..13: two Newton-Raphson steps.
+struct PivotSearch {
+    unsigned key, m;
+    int src;
+    bool any;
+    double piv, rp, t;
+    template <int CTRL, int ROWS>
+    __device__ __forceinline__ void fold() {
+        m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), CTRL, ROWS, 0xf, true)));
+    }
+    template <int S>
+    __device__ __forceinline__ void stage(double col) {
+        if constexpr (S == 0) fold<0x111, 0xf>();      // row_shr 1
+        if constexpr (S == 1) fold<0x112, 0xf>();      // row_shr 2
+        if constexpr (S == 2) fold<0x114, 0xf>();      // row_shr 4
+        if constexpr (S == 3) fold<0x118, 0xf>();      // row_shr 8
+        if constexpr (S == 4) fold<0x142, 0xa>();      // row_bcast 15
+        if constexpr (S == 5) fold<0x143, 0xc>();      // row_bcast 31
+        if constexpr (S == 6) {
+            m = unsigned(__builtin_amdgcn_readlane(int(m), 63));
+            any = m != 0u;
+        }
+        if constexpr (S == 7) src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m));
+        if constexpr (S == 8) piv = wt_readlane(col, src);
+        if constexpr (S == 9) rp = __builtin_amdgcn_rcp(piv);
+        if constexpr (S == 10 || S == 12) t = fma(-piv, rp, 1.0);
+        if constexpr (S == 11 || S == 13) rp = fma(t, rp, rp);
+    }
+};
 
 // Halves of two registers exchanged between the lane halves (32) or between even and odd rows of 16
 // lanes (16), then added: lanes of the lower half (even rows) get the sum of a over the pair, the
@@ -100,24 +143,48 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
         // at the end: every later step is linear in the row.
         const int npv = (NP % 16 != 0 && p == TR - 1) ? NP % 16 : 16;
         double scale = 1.0;
+        PivotSearch ps;
+        ps.key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
+        ps.m = ps.key;
+        wt_for<0, 14>([&](auto i) { ps.template stage<decltype(i)::value>(R[0]); });
 #pragma unroll 1
-        for (int c = 0; c < npv; c++) {
-            // pivot search on the high word of |a| (ordered like |a|; values within a relative 2^-20
-            // of the largest may tie, and then the first lane is taken)
-            const unsigned key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
-            const unsigned mx = __ockl_wfred_max_u32(key);
-            ok = ok && mx != 0u;
-            const int src = __builtin_ctzll(__ballot(!done && key == mx));
-            const double rp = ck_rcp(wt_readlane(R[0], src));
-            const bool me = lane == src;
-            const double gm = me ? 0.0 : -R[0] * rp;
-            const double last = me ? 1.0 : gm;
+        for (int c8 = 0; c8 < npv; c8 += 8) {
+            // eight pivots of straight-line code, so that the rotation is register renaming
 #pragma unroll
-            for (int j = 1; j < 16; j++) R[j - 1] = fma(gm, wt_readlane(R[j], src), R[j]);
-            R[15] = last;
-            done = done || me;
-            scale = me ? rp : scale;
-            ord = me ? 16 * p + c : ord;
+            for (int c = 0; c < 8; c++) {
+                ok = ok && ps.any;
+                const int src = ps.src;
+                const bool me = lane == src;
+                const double gm = me ? 0.0 : -R[0] * ps.rp;
+                const double last = me ? 1.0 : gm;
+                done = done || me;
+                scale = me ? ps.rp : scale;
+                ord = me ? 16 * p + c8 + c : ord;
+                // the next pivot's column first, then its search and reciprocal (a chain of about 20
+                // dependent instructions) one stage per updated column: the chain's latency is spent
+                // on the other columns' lane reads and multiply-adds.  The order is fixed by hand;
+                // left to itself the compiler puts most of the chain behind the last column.
+                // Each column's lane reads are issued one column early, which covers the wait between a
+                // lane read and the vector instruction that takes its scalar result.
+                PivotSearch nx;
+                double pj = wt_readlane(R[1], src);
+                wt_for<1, 16>([&](auto i) {
+                    constexpr int j = decltype(i)::value;
+                    const double pn = j < 15 ? wt_readlane(R[j < 15 ? j + 1 : 15], src) : 0.0;
+                    __builtin_amdgcn_sched_barrier(0);
+                    R[j - 1] = fma(gm, pj, R[j]);
+                    pj = pn;
+                    if (j == 2) {
+                        nx.key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
+                        nx.m = nx.key;
+                    }
+                    if (j > 2) nx.template stage<(j > 2 ? j - 3 : 0)>(R[0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                nx.template stage<13>(R[0]);
+                R[15] = last;
+                ps = nx;
+            }
         }
         // npv rotations leave column j in R[(j - npv) mod 16]
         const int rot = npv & 15;
