@@ -62,6 +62,18 @@ struct PairBlock {
     int4 off[64];
 };
 
+// Third-body and fall-off data of 64 consecutive pair-form reactions (the leading ones), laid out like
+// PairBlock so that all of it is requested at once: low-pressure limit, Troe parameters (1/T*** and
+// 1/T* stored), the first three third-body efficiencies (alpha - 1 and the byte offset 8 k of the
+// species; 0 and the null species when there are fewer) and the reaction's type, number of
+// efficiencies and first entry in the efficiency table.
+struct FactorBlock {
+    double lnA0[64], beta0[64], Ea0R[64], a[64], invT3[64], invT1[64], T2[64];
+    double am1[3][64];
+    int4 eff[64];               // offsets of the three species; type | number of efficiencies << 2
+    int eff_begin[64];
+};
+
 // Device view of a mechanism.
 struct DevMech {
     int nsp, nrxn, N, n_eff;
@@ -74,6 +86,7 @@ struct DevMech {
     const double *spd;
     const RxnRec *rx;
     const PairBlock *pair;       // stored reactions n_gen.. in pair form
+    const FactorBlock *factor;   // pair-form reactions [0, n_fall)
     const FallRec *fall;
     const EffRec *eff;
     const int *orig_index;       // file order of each stored reaction

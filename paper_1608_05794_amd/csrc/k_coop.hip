@@ -196,7 +196,7 @@ __device__ __forceinline__ void species_pass(const DevMech &M, double y, double 
     const bool valid = species_of(tid, ns) >= 0;
     const int k = min(max(tid - 1, 0), ns - 1);
     const double T = G::bcast(y, 0, L.RED + 8);
-    const Nasa co = species_coef(M, k, T);
+    const Nasa co = species_coef(M, k, T < M.Tmid()[k]);
     x.W = M.W()[k];
     const double z = valid ? y * M.invW()[k] : 0.0;
     x.t = tpow(T);
@@ -233,10 +233,11 @@ __device__ __forceinline__ void jacobian_window(const DevMech &M, const Lds &L, 
     using G = Grp<W>;
     const int ns = M.nsp, tid = G::tid();
     const int tot = ns * L.ldj;
+    const PairRec first = first_pair<G::T>(M, tid);
     for (int e = tid; e < tot; e += G::T) L.JC[e] = 0.0;
     __syncthreads();
     const RxScale sc{x.t.invT, x.Wbar * x.invrho, 1.0};
-    ck::reaction_pass<G::T, true>(M, L, x.t, x.Ctot, sc, c0, min(win, ns - c0), mode, keep, tid);
+    ck::reaction_pass<G::T, true>(M, L, x.t, x.Ctot, sc, c0, min(win, ns - c0), mode, keep, tid, first);
     __syncthreads();
 }
 
@@ -254,9 +255,10 @@ __device__ __forceinline__ double finish_rhs(const DevMech &M, const Lds &L, con
 template <int W>
 __device__ __forceinline__ double rhs(const DevMech &M, const Lds &L, double y, double P) {
     Mix x;
+    const PairRec first = first_pair<Grp<W>::T>(M, Grp<W>::tid());
     species_pass<W, false>(M, y, P, L, x);
     ck::reaction_pass<Grp<W>::T, false>(M, L, x.t, x.Ctot, RxScale{0.0, 0.0, 0.0}, 0, 0, kRates, nullptr,
-                                        Grp<W>::tid());
+                                        Grp<W>::tid(), first);
     __syncthreads();
     const double f = finish_rhs<W>(M, L, x);
     __syncthreads();

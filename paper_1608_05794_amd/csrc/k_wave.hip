@@ -56,7 +56,16 @@ __device__ __forceinline__ bool wave_all(bool v) { return __ballot(!v) == 0ull; 
 // ---------------------------------------------------------------------------------------
 enum LdsKind { kLdsRhs, kLdsTiles, kLdsJac, kLdsWhole };
 
+// Constants of the species that a register slot of this lane holds (slot 0 of lane 0 is T), read once
+// per kernel: an out-of-range slot takes a neighbour's values and `valid` masks what it stores.
+struct SpeciesLane {
+    double W, iW, Tmid;
+    int k;
+    bool valid;
+};
+
 struct Lds : RxArrays {
+    SpeciesLane sl[2];
     double *IW, *VX, *TROW;
     double *park;   // this wavefront's slice of the workspace, or null
     int cv;         // 0: constant pressure (p = pressure); 1: constant volume (p = density)
@@ -111,8 +120,19 @@ __device__ __forceinline__ Lds carve(double *b, LdsKind kind, int ns, int ldj) {
     return L;
 }
 
-__device__ __forceinline__ void init_lds(const DevMech &M, const Lds &L, LdsKind kind) {
+template <int RPL>
+__device__ __forceinline__ void init_lds(const DevMech &M, Lds &L, LdsKind kind) {
     const int l = lane_id(), ns = M.nsp;
+#pragma unroll
+    for (int c = 0; c < RPL; c++) {
+        const int i = l + 64 * c;
+        SpeciesLane &s = L.sl[c];
+        s.valid = i >= 1 && i <= ns;
+        s.k = min(max(i - 1, 0), ns - 1);
+        s.W = M.W()[s.k];
+        s.iW = M.invW()[s.k];
+        s.Tmid = M.Tmid()[s.k];
+    }
     if (l == 0) {
         L.C[ns] = 1.0;
         L.G[ns] = 0.0;
@@ -133,29 +153,21 @@ template <int RPL>
 struct Mix {
     TPow t;
     double rho, invrho, Wbar, Ctot, cpm;
-    double W[RPL], cp[RPL], h[RPL], dcp[RPL];
-    bool valid[RPL];    // this register slot holds a species (slot 0 of lane 0 is T)
-    int k[RPL];         // its index, clamped into range
+    double cp[RPL], h[RPL], dcp[RPL];
 };
 
 // Mixture state and per-species thermodynamics (Section 3: ideal gas, Eq. tfits).  Every lane reads
 // an in-range species, so the loads are issued together and only the stores are masked.
 template <int RPL, bool JAC>
 __device__ __forceinline__ void species_pass(const DevMech &M, const double (&y)[RPL], double P, const Lds &L, Mix<RPL> &x) {
-    const int ns = M.nsp;
-    const int lane = lane_fresh();
     const double T = bcast(y[0], 0);
     double z[RPL];
     Nasa co[RPL];
     double sz = 0.0;
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
-        const int i = lane + 64 * c;
-        x.valid[c] = i >= 1 && i <= ns;
-        x.k[c] = min(max(i - 1, 0), ns - 1);
-        co[c] = species_coef(M, x.k[c], T);
-        x.W[c] = M.W()[x.k[c]];
-        z[c] = x.valid[c] ? y[c] * M.invW()[x.k[c]] : 0.0;
+        co[c] = species_coef(M, L.sl[c].k, T < L.sl[c].Tmid);
+        z[c] = L.sl[c].valid ? y[c] * L.sl[c].iW : 0.0;
         sz += z[c];
     }
     x.t = tpow(T);
@@ -176,8 +188,8 @@ __device__ __forceinline__ void species_pass(const DevMech &M, const double (&y)
         x.cp[c] = th.cp;
         x.h[c] = th.h;
         if (JAC) x.dcp[c] = th.dcp;
-        if (x.valid[c]) {
-            const int k = x.k[c];
+        if (L.sl[c].valid) {
+            const int k = L.sl[c].k;
             L.C[k] = x.rho * z[c];
             L.G[k] = th.g;
             L.WD[k] = 0.0;
@@ -208,8 +220,8 @@ __device__ __forceinline__ void finish_rhs(const DevMech &M, const Lds &L, const
     double qp = 0.0;
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
-        const double wd = x.valid[c] ? L.WD[x.k[c]] : 0.0;
-        f[c] = x.W[c] * wd * x.invrho;
+        const double wd = L.sl[c].valid ? L.WD[L.sl[c].k] : 0.0;
+        f[c] = L.sl[c].W * wd * x.invrho;
         qp = fma(x.h[c] - shift, wd, qp);
     }
     const double Q = wsum(qp) * (M.R * x.t.T);
@@ -218,11 +230,12 @@ __device__ __forceinline__ void finish_rhs(const DevMech &M, const Lds &L, const
     if (lane == 0) f[0] = fT;
 }
 
-template <int RPL>
+template <int RPL, bool GEN = true>
 __device__ __forceinline__ void rhs_wave(const DevMech &M, const Lds &L, const double (&y)[RPL], double P, double (&f)[RPL]) {
     Mix<RPL> x;
+    const PairRec first = first_pair<64>(M, lane_fresh());
     species_pass<RPL, false>(M, y, P, L, x);
-    reaction_pass<64, false>(M, L, x.t, x.Ctot, RxScale{0.0, 0.0, 0.0}, 0, 0, kRates, nullptr, lane_fresh());
+    reaction_pass<64, false, GEN>(M, L, x.t, x.Ctot, RxScale{0.0, 0.0, 0.0}, 0, 0, kRates, nullptr, lane_fresh(), first);
     __syncthreads();
     finish_rhs<RPL>(M, L, x, f);
     __syncthreads();
@@ -239,8 +252,8 @@ struct Chain {
     double beta, col0, trow, J00;
 };
 __device__ __forceinline__ Chain chain_rule(const DevMech &M, const Lds &L, const Mix<1> &x, double y0, double fT) {
-    const bool valid = x.valid[0];
-    const int k = x.k[0];
+    const bool valid = L.sl[0].valid;
+    const int k = L.sl[0].k;
     const double TBk = valid ? L.TB[k] : 0.0, WDk = valid ? L.WD[k] : 0.0, DWTk = valid ? L.DWT[k] : 0.0;
     const bool cv = L.cv != 0;
     ChainIn c;
@@ -257,7 +270,7 @@ __device__ __forceinline__ Chain chain_rule(const DevMech &M, const Lds &L, cons
     c.sHB = c.RT * wsum(Hk * TBk);
     c.sHW = c.RT * wsum(Hk * WDk);
     c.dQT = M.R * wsum(fma(x.cp[0] - e, WDk, Hk * (x.t.T * DWTk - (cv ? 0.0 : WDk))));
-    c.sdcp = M.R * wsum(valid ? y0 * x.dcp[0] * M.invW()[k] : 0.0);
+    c.sdcp = M.R * wsum(valid ? y0 * x.dcp[0] * L.sl[0].iW : 0.0);
     Chain o;
     o.trow = valid ? chain_trow(c, cv, L.HC[k], x.cp[0]) : 0.0;
     o.J00 = chain_J00(c, cv);
@@ -276,7 +289,7 @@ struct JRow {
 __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, const Mix<1> &x, double y0, double fT) {
     const int lane = lane_fresh();
     const Chain c = chain_rule(M, L, x, y0, fT);
-    if (x.valid[0]) L.TROW[x.k[0]] = c.trow;
+    if (L.sl[0].valid) L.TROW[L.sl[0].k] = c.trow;
     if (lane == 0) L.TROW[M.nsp] = 0.0;     // an FP64 step may have used it
     __syncthreads();
     JRow r;
@@ -285,11 +298,11 @@ __device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, cons
         r.alpha = 1.0;
         r.beta = 0.0;
         r.c0 = c.J00;
-    } else if (x.valid[0]) {
-        r.src = &L.JC[x.k[0] * L.ldj];
-        r.alpha = x.W[0];
-        r.beta = x.W[0] * c.beta;
-        r.c0 = x.W[0] * c.col0;
+    } else if (L.sl[0].valid) {
+        r.src = &L.JC[L.sl[0].k * L.ldj];
+        r.alpha = L.sl[0].W;
+        r.beta = L.sl[0].W * c.beta;
+        r.c0 = L.sl[0].W * c.col0;
     } else {
         r.src = L.TROW;
         r.alpha = 0.0;
@@ -304,9 +317,10 @@ __device__ __forceinline__ JRow jac_whole(const DevMech &M, const Lds &L, double
     Mix<1> x;
     const double yy[1] = {y};
     double ff[1];
+    const PairRec first = first_pair<64>(M, lane_fresh());
     zero_jc(L, M.nsp);
     species_pass<1, true>(M, yy, P, L, x);
-    reaction_pass<64, true>(M, L, x.t, x.Ctot, rx_scale(L, x), 0, M.nsp, kRates, nullptr, lane_fresh());
+    reaction_pass<64, true>(M, L, x.t, x.Ctot, rx_scale(L, x), 0, M.nsp, kRates, nullptr, lane_fresh(), first);
     __syncthreads();
     finish_rhs<1>(M, L, x, ff);
     f = ff[0];
@@ -343,25 +357,26 @@ __device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L0, doubl
     const double yy[1] = {y};
     double ff[1];
     const int ns = M.nsp;
+    const PairRec first = first_pair<64>(M, lane_fresh());
     zero_jc(L, ns);
     species_pass<1, true>(M, yy, P, L, x);
     const RxScale sc = rx_scale(L, x);
     const bool fits = NWIN == 2 && 3 * rx_blocks(M, 64) <= NP;
     reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, -1, min(WIN, ns + 1), fits ? kRatesKeep : kRates,
-                            L.park + lane_fresh(), lane_fresh());
+                            L.park + lane_fresh(), lane_fresh(), first);
     __syncthreads();
     finish_rhs<1>(M, L, x, ff);
     f = ff[0];
     const Chain ch = chain_rule(M, L, x, y, bcast(f, 0));
     const int lane = lane_fresh();
     const int g = lane >> 4, c16 = lane & 15;
-    if (x.valid[0]) {
-        L.TROW[1 + x.k[0]] = ch.trow;
-        L.JC[x.k[0] * SH::LDJ] = ch.col0;
+    if (L.sl[0].valid) {
+        L.TROW[1 + L.sl[0].k] = ch.trow;
+        L.JC[L.sl[0].k * SH::LDJ] = ch.col0;
     }
     if (lane == 0) L.TROW[0] = ch.J00;
-    w = lane == 0 ? 1.0 : (x.valid[0] ? x.W[0] : 0.0);
-    iw = lane == 0 ? 1.0 : (x.valid[0] ? M.invW()[x.k[0]] : 0.0);
+    w = lane == 0 ? 1.0 : (L.sl[0].valid ? L.sl[0].W : 0.0);
+    iw = lane == 0 ? 1.0 : (L.sl[0].valid ? L.sl[0].iW : 0.0);
     __syncthreads();
     double dgm[4];
 #pragma unroll
@@ -370,11 +385,12 @@ __device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L0, doubl
 #pragma unroll
     for (int wnd = 0; wnd < NWIN; wnd++) {
         if (wnd > 0) {
+            const PairRec again = first_pair<64>(M, lane_fresh());
             __syncthreads();
             zero_jc(L, ns);
             __syncthreads();
             reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, WIN - 1, min(WIN, ns + 1 - WIN),
-                                    fits ? kScatterKept : kScatter, L.park + lane_fresh(), lane_fresh());
+                                    fits ? kScatterKept : kScatter, L.park + lane_fresh(), lane_fresh(), again);
             __syncthreads();
         }
 #pragma unroll
@@ -902,14 +918,14 @@ __device__ __forceinline__ int64_t xcd_reactor(int64_t b, int64_t nb) {
 // ---------------------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------------------
-template <int RPL>
+template <int RPL, bool GEN>
 __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
                                                       const double *p, double *dydt, int cv) {
     // laid out for the largest species count of the instantiation, so every offset is a constant
     __shared__ double lds_raw[4 * 64 * RPL];
     Lds L = carve(lds_raw, kLdsRhs, 64 * RPL - 1, 0);
     L.cv = cv;
-    init_lds(M, L, kLdsRhs);
+    init_lds<RPL>(M, L, kLdsRhs);
     const int N = M.N, lane = lane_id();
     const int64_t nb = int64_t(gridDim.x);
     const int64_t r = xcd_reactor(blockIdx.x, nb);
@@ -920,7 +936,7 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
         const int i = lane + 64 * c;
         yv[c] = i < N ? y[int64_t(i) * ld + r] : 0.0;
     }
-    rhs_wave<RPL>(M, L, yv, p[r], f);
+    rhs_wave<RPL, GEN>(M, L, yv, p[r], f);
 #pragma unroll
     for (int c = 0; c < RPL; c++) {
         const int i = lane + 64 * c;
@@ -933,7 +949,7 @@ __global__ void __launch_bounds__(64) jac_wave_kernel(DevMech M, int64_t n, cons
     extern __shared__ double lds_raw[];
     Lds L = carve(lds_raw, kLdsWhole, M.nsp, whole_ldj(M.nsp));
     L.cv = cv;
-    init_lds(M, L, kLdsWhole);
+    init_lds<1>(M, L, kLdsWhole);
     const int N = M.N, lane = lane_id();
     const int64_t r = xcd_reactor(blockIdx.x, int64_t(gridDim.x));
     if (r >= n) return;
@@ -959,7 +975,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     Lds L = carve(lds_raw, S::LDS, S::NSMAX, S::LDJ);
     L.cv = o.reactor;
     if (S::PARK) L.park = park + size_t(blockIdx.x) * (size_t(S::PARK_ROWS) * 64);
-    init_lds(M, L, S::LDS);
+    init_lds<S::RPL>(M, L, S::LDS);
     for (;;) {
         unsigned v = 0;
         if (lane_id() == 0) v = atomicAdd(queue, 1u);
@@ -1020,10 +1036,10 @@ size_t wave_ws_bytes(const DevMech &M, int cus) {
 int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *dydt,
                     int cv, hipStream_t s) {
     const unsigned grid = unsigned((n + 7) / 8 * 8);
-    if (M.N <= 64)
-        rhs_wave_kernel<1><<<dim3(grid), dim3(64), 0, s>>>(M, n, y, ld, p, dydt, cv);
-    else
-        rhs_wave_kernel<2><<<dim3(grid), dim3(64), 0, s>>>(M, n, y, ld, p, dydt, cv);
+    // the general-form code needs 20 more registers than the rest: a kernel of its own
+    auto kern = M.N <= 64 ? (M.n_gen > 0 ? rhs_wave_kernel<1, true> : rhs_wave_kernel<1, false>)
+                          : (M.n_gen > 0 ? rhs_wave_kernel<2, true> : rhs_wave_kernel<2, false>);
+    kern<<<dim3(grid), dim3(64), 0, s>>>(M, n, y, ld, p, dydt, cv);
     return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
 }
 

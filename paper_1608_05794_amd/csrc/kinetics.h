@@ -85,13 +85,13 @@ __device__ __forceinline__ TPow tpow(double T) {
     return p;
 }
 
-// NASA-7 coefficients of species k: low range if T < Tmid, else high (per-lane select).
+// NASA-7 coefficients of species k: the low range (T < Tmid) or the high one (per-lane select).
 struct Nasa {
     double a1, a2, a3, a4, a5, a6, a7;
 };
-__device__ __forceinline__ Nasa species_coef(const DevMech &M, int k, double T) {
+__device__ __forceinline__ Nasa species_coef(const DevMech &M, int k, bool low) {
     const int ns = M.nsp;
-    const double *c = M.thermo() + (T < M.Tmid()[k] ? 0 : 7) * ns + k;
+    const double *c = M.thermo() + (low ? 0 : 7) * ns + k;
     return Nasa{c[0], c[ns], c[2 * ns], c[3 * ns], c[4 * ns], c[5 * ns], c[6 * ns]};
 }
 
@@ -110,7 +110,7 @@ __device__ __forceinline__ Thermo species_thermo(const DevMech &M, const Nasa &a
     return o;
 }
 __device__ __forceinline__ Thermo species_thermo(const DevMech &M, int k, const TPow &t) {
-    return species_thermo(M, species_coef(M, k, t.T), t);
+    return species_thermo(M, species_coef(M, k, t.T < M.Tmid()[k]), t);
 }
 
 // x^n for n in 0..3
@@ -155,17 +155,17 @@ struct Factor {
     double c, Mc, dcdM, dcdT;
 };
 
-// Factor of reaction R (not elementary) whose (high-pressure) rate constant is exp(lnkf).
-template <bool DERIV, class Cget>
-__device__ __forceinline__ void rate_factor(const DevMech &M, const RxnRec &R, const TPow &t, double Ctot,
-                                            double lnkf, double dlnkf, const Cget &C, Factor &o) {
-    const int ty = rx_type(R.meta);
-    double Mc = Ctot;
-    const int eb = R.eff_begin, ec = rx_neff(R.meta);
-    for (int e = 0; e < ec; e++) {
-        const EffRec E = M.eff[eb + e];
-        Mc += E.am1 * C(E.sp);
-    }
+// Parameters of a factor: type, low-pressure limit and Troe data.
+struct FactorIn {
+    int type;
+    double lnA0, beta0, Ea0R, a, invT3, invT1, T2;
+};
+
+// Factor at [M] = Mc of a reaction whose (high-pressure) rate constant is exp(lnkf).
+template <bool DERIV>
+__device__ __forceinline__ void rate_factor(const FactorIn &F, const TPow &t, double Mc, double lnkf, double dlnkf,
+                                            Factor &o) {
+    const int ty = F.type;
     o.Mc = Mc;
     o.c = Mc;
     if (DERIV) {
@@ -174,7 +174,6 @@ __device__ __forceinline__ void rate_factor(const DevMech &M, const RxnRec &R, c
     }
     if (ty == kThirdBody) return;
     // fall-off: Pr = k0 [M] / k_inf, c = Pr / (1 + Pr) F
-    const FallRec F = M.fall[R.fall];
     const double lnk0 = fma(-F.Ea0R, t.invT, fma(F.beta0, t.lnT, F.lnA0));
     const double ratio = ck_exp(lnk0 - lnkf);
     const double Pr = ratio * Mc;
@@ -263,8 +262,19 @@ __device__ __forceinline__ void reaction_rate(const DevMech &M, const RxnRec &R,
         o.dcdT = 0.0;
     }
     if (rx_type(meta) == kElementary) return;
+    double Mc = Ctot;
+    const int eb = R.eff_begin, ec = rx_neff(meta);
+    for (int e = 0; e < ec; e++) {
+        const EffRec E = M.eff[eb + e];
+        Mc += E.am1 * C(E.sp);
+    }
+    FactorIn in{rx_type(meta), 0, 0, 0, 0, 0, 0, 0};
+    if (in.type != kThirdBody) {
+        const FallRec F = M.fall[R.fall];
+        in = FactorIn{in.type, F.lnA0, F.beta0, F.Ea0R, F.a, F.invT3, F.invT1, F.T2};
+    }
     Factor f;
-    rate_factor<DERIV>(M, R, t, Ctot, lnkf, o.dlnkf, C, f);
+    rate_factor<DERIV>(in, t, Mc, lnkf, o.dlnkf, f);
     o.c = f.c;
     o.Mc = f.Mc;
     if (DERIV) {

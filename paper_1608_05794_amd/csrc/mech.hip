@@ -299,6 +299,8 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     for (int ii = n_gen; ii < nr; ii++) order[ii] = units_of[ii - n_gen].id;
     std::vector<PairBlock> pair(std::max((nr - n_gen + 63) / 64, 1));
     std::memset(pair.data(), 0, pair.size() * sizeof(PairBlock));
+    std::vector<FactorBlock> factor(std::max((n_fall + 63) / 64, 1));
+    std::memset(factor.data(), 0, factor.size() * sizeof(FactorBlock));
     std::vector<RxnRec> rx(std::max(nr, 1));
     std::vector<FallRec> fall;
     std::vector<EffRec> eff;
@@ -355,6 +357,26 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
             B.beta[l] = R.beta;
             B.EaR[l] = R.EaR;
             B.off[l] = make_int4(8 * u[0], 8 * u[1], 8 * u[2], 8 * u[3]);
+            if (ii - n_gen < n_fall) {
+                FactorBlock &F = factor[(ii - n_gen) / 64];
+                if (R.fall >= 0) {
+                    const FallRec &r = fall[R.fall];
+                    F.lnA0[l] = r.lnA0;
+                    F.beta0[l] = r.beta0;
+                    F.Ea0R[l] = r.Ea0R;
+                    F.a[l] = r.a;
+                    F.invT3[l] = r.invT3;
+                    F.invT1[l] = r.invT1;
+                    F.T2[l] = r.T2;
+                }
+                int o[3] = {8 * ns, 8 * ns, 8 * ns};
+                for (size_t j = 0; j < std::min<size_t>(3, x.eff.size()); j++) {
+                    o[j] = 8 * x.eff[j].first;
+                    F.am1[j][l] = x.eff[j].second - 1.0;
+                }
+                F.eff[l] = make_int4(o[0], o[1], o[2], x.type | (int(x.eff.size()) << 2));
+                F.eff_begin[l] = R.eff_begin;
+            }
         }
         for (auto &e : x.eff) {
             EffRec E{};
@@ -368,7 +390,7 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
 
     Packer pk;
     const size_t ospd = pk.add(spd), orx = pk.add(rx), ofall = pk.add(fall), oeff = pk.add(eff), oorig = pk.add(orig),
-                 opair = pk.add(pair);
+                 opair = pk.add(pair), ofactor = pk.add(factor);
 
     m->device = device;
     int prev = 0;
@@ -409,6 +431,7 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     d.spd = reinterpret_cast<const double *>(b + ospd);
     d.rx = reinterpret_cast<const RxnRec *>(b + orx);
     d.pair = reinterpret_cast<const PairBlock *>(b + opair);
+    d.factor = reinterpret_cast<const FactorBlock *>(b + ofactor);
     d.fall = reinterpret_cast<const FallRec *>(b + ofall);
     d.eff = reinterpret_cast<const EffRec *>(b + oeff);
     d.orig_index = reinterpret_cast<const int *>(b + oorig);

@@ -52,19 +52,50 @@ __host__ __device__ inline int rx_blocks(const DevMech &M, int T) {
     return (M.n_gen + T - 1) / T + (M.nrxn - M.n_gen + T - 1) / T;
 }
 
+// One pair-form reaction in registers.
+struct PairRec {
+    double lnA, beta, EaR;
+    int4 off;
+};
+__device__ __forceinline__ PairRec pair_rec(const DevMech &M, int i) {
+    const PairBlock &b = M.pair[i >> 6];
+    const int l = i & 63;
+    return PairRec{b.lnA[l], b.beta[l], b.EaR[l], b.off[l]};
+}
+// The first reaction of thread tid: requested ahead of the species pass, whose result it waits for.
+template <int T>
+__device__ __forceinline__ PairRec first_pair(const DevMech &M, int tid) {
+    if (T != 64) return PairRec{};
+    return pair_rec(M, min(tid, max(M.nrxn - M.n_gen - 1, 0)));
+}
+
+// f(byte offset of the species, alpha - 1) for the third-body efficiencies of pair-form reaction i.
+template <class F>
+__device__ __forceinline__ void for_efficiencies(const DevMech &M, int i, F &&f) {
+    const FactorBlock &fb = M.factor[i >> 6];
+    const int l = i & 63, n = fb.eff[l].w >> 2;
+    if (n > 0) f(fb.eff[l].x, fb.am1[0][l]);
+    if (n > 1) f(fb.eff[l].y, fb.am1[1][l]);
+    if (n > 2) f(fb.eff[l].z, fb.am1[2][l]);
+    for (int j = 3; j < n; j++) f(8 * M.eff[fb.eff_begin[l] + j].sp, M.eff[fb.eff_begin[l] + j].am1);
+}
+
 // Pair-form reactions (at most two reactant and two product units, 2 A counting as A + A, and
 // reversible): straight-line code with four slots of coefficient one, no stoichiometric powers and
 // no sign selects.  Slots 1 and 3 may be the null species.
 template <int T, bool JAC>
 __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                                const RxScale &sc, int c0, int win, RxMode mode, double *keep,
-                                               int tid) {
+                                               int tid, PairRec next) {
     const int nf = M.nrxn - M.n_gen;
     const int null_off = 8 * M.nsp;
     for (int i = tid; i < nf; i += T) {
-        const PairBlock &blk = M.pair[i >> 6];
-        const int l = i & 63;
-        const int4 o = blk.off[l];
+        // One wavefront per reactor: the next block's records are requested while this one is evaluated
+        // (M53: RHS stage 10.7 -> 9.5 k cycles).  The workgroup kernels have four wavefronts to cover the
+        // load and no registers for it (M111 ROS4: 406 ms without, 431 ms with).
+        const PairRec R = T == 64 ? next : pair_rec(M, i);
+        if (T == 64 && i + T < nf) next = pair_rec(M, i + T);
+        const int4 o = R.off;
         const double cA = lds_at(A.C, o.x), cB = lds_at(A.C, o.y), cC = lds_at(A.C, o.z), cD = lds_at(A.C, o.w);
         const bool has1 = o.y != null_off, has3 = o.w != null_off;
         const bool factor = i < M.n_fall;        // third-body or fall-off (the leading reactions)
@@ -74,18 +105,29 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
             ckr = keep[T];
             if (factor) rdm = keep[2 * T];
         } else {
-            const double lnkf = fma(-blk.EaR[l], t.invT, fma(blk.beta[l], t.lnT, blk.lnA[l]));
+            const double lnkf = fma(-R.EaR, t.invT, fma(R.beta, t.lnT, R.lnA));
             const double sg = (lds_at(A.G, o.z) + lds_at(A.G, o.w)) - (lds_at(A.G, o.x) + lds_at(A.G, o.y));
             ckf = ck_exp(lnkf);
             ckr = ck_exp(lnkf + sg);             // kr = kf / Kc, ln Kc = -sum_k nu_k g_k
             const double pf = cA * cB, pr = cC * cD;
             double dlnkf = 0.0, rdT = 0.0, rdMc = 0.0;
-            if (JAC) dlnkf = fma(blk.EaR[l], t.invT, blk.beta[l]) * t.invT;
+            if (JAC) dlnkf = fma(R.EaR, t.invT, R.beta) * t.invT;
             if (factor) {
-                const RxnRec R = M.rx[M.n_gen + i];
-                auto Cg = [&](int k) { return A.C[k]; };
+                const FactorBlock &fb = M.factor[i >> 6];
+                const int l = i & 63;
+                const int4 e = fb.eff[l];
+                const FactorIn in{e.w & 3,     fb.lnA0[l],  fb.beta0[l], fb.Ea0R[l],
+                                  fb.a[l],     fb.invT3[l], fb.invT1[l], fb.T2[l]};
+                double Mc = Ctot;
+                Mc = fma(fb.am1[0][l], lds_at(A.C, e.x), Mc);
+                Mc = fma(fb.am1[1][l], lds_at(A.C, e.y), Mc);
+                Mc = fma(fb.am1[2][l], lds_at(A.C, e.z), Mc);
+                for (int j = 3; j < e.w >> 2; j++) {
+                    const EffRec E = M.eff[fb.eff_begin[l] + j];
+                    Mc = fma(E.am1, A.C[E.sp], Mc);
+                }
                 Factor c;
-                rate_factor<JAC>(M, R, t, Ctot, lnkf, dlnkf, Cg, c);
+                rate_factor<JAC>(in, t, Mc, lnkf, dlnkf, c);
                 const double Rn = ckf * pf - ckr * pr;
                 ckf *= c.c;
                 ckr *= c.c;
@@ -132,11 +174,8 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
                         lds_add(A.HC, o.w, -ckr * cC * shx);
                     }
                 }
-                if (JAC && factor && rdm != 0.0) {
-                    const RxnRec &R = M.rx[M.n_gen + i];
-                    const int eb = R.eff_begin, ec = rx_neff(R.meta);
-                    for (int e = 0; e < ec; e++) lds_add(A.HC, 8 * M.eff[eb + e].sp, rdm * M.eff[eb + e].am1 * shx);
-                }
+                if (JAC && factor && rdm != 0.0)
+                    for_efficiencies(M, i, [&](int off, double am1) { lds_add(A.HC, off, rdm * am1 * shx); });
             }
             if (JAC && mode == kRatesKeep) {
                 keep[0] = ckf;
@@ -160,11 +199,7 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
             column(o.y, ckf * cA);
             column(o.z, -ckr * cD);
             column(o.w, -ckr * cC);
-            if (factor && rdm != 0.0) {
-                const RxnRec &R = M.rx[M.n_gen + i];
-                const int eb = R.eff_begin, ec = rx_neff(R.meta);
-                for (int e = 0; e < ec; e++) column(8 * M.eff[eb + e].sp, rdm * M.eff[eb + e].am1);
-            }
+            if (factor && rdm != 0.0) for_efficiencies(M, i, [&](int off, double am1) { column(off, rdm * am1); });
             if (mode == kRatesKeep || mode == kScatterKept) keep += 3 * T;
         }
     }
@@ -257,16 +292,17 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
 }
 
 // Every reaction of the mechanism.  Window: columns [c0, c0 + win) of JC, win already cut to the
-// species count.  The caller synchronises before and after.
-template <int T, bool JAC>
+// species count.  first: first_pair(M, tid).  The caller synchronises before and after.  GEN = false
+// leaves the general form out (the caller knows that the mechanism has none).
+template <int T, bool JAC, bool GEN = true>
 __device__ __forceinline__ void reaction_pass(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                               const RxScale &sc, int c0, int win, RxMode mode, double *keep,
-                                              int tid) {
-    if (M.n_gen > 0) {
+                                              int tid, const PairRec &first) {
+    if (GEN && M.n_gen > 0) {
         general_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
         if (JAC && (mode == kRatesKeep || mode == kScatterKept)) keep += 3 * T * ((M.n_gen + T - 1) / T);
     }
-    pair_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
+    pair_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid, first);
 }
 
 // Chain rule from the accumulators to J = df/dy for the lane's species k, shared by the kernels.
