@@ -944,22 +944,97 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
     }
 }
 
-__global__ void __launch_bounds__(64) jac_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
-                                                      const double *p, double *jac, int cv) {
+// Standalone Jacobian for N <= 64: workgroups of eight wavefronts, one reactor each, d wdot/dC staged
+// in windows of WIN matrix columns (the temperature column is column 0).  Bound by the stores: an entry
+// of a reactor is eight bytes of a line that it shares with fifteen neighbours, so the eight staged
+// windows are written out together, eight neighbouring reactors by one store (64 bytes), instead of
+// one reactor at a time (a line per lane).  Rates are evaluated again for a later window.
+template <int NSMAX, int WIN>
+struct JacShape {
+    static constexpr int R = 8;                     // reactors of a workgroup
+    static constexpr int LDJ = WIN | 1;
+    static constexpr int NWIN = (NSMAX + 1 + WIN - 1) / WIN;
+    static constexpr int kSlab0 = 8 * (NSMAX + 1) + (NSMAX + 1) * LDJ;
+    // slab stride 8 modulo 32 doubles: the eight reactors of a store read different banks
+    static constexpr int kSlab = kSlab0 + (8 - kSlab0 % 32 + 32) % 32;
+    static constexpr size_t kLds = size_t(R) * kSlab + 2 * (NSMAX + 1);
+};
+template <int NSMAX, int WIN>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) jac_wave_kernel(DevMech M, int64_t n, const double *y,
+                                                       int64_t ld, const double *p, double *jac, int cv) {
+    using SH = JacShape<NSMAX, WIN>;
     extern __shared__ double lds_raw[];
-    Lds L = carve(lds_raw, kLdsWhole, M.nsp, whole_ldj(M.nsp));
+    const int N = M.N, ns = M.nsp, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int64_t r0 = xcd_reactor(blockIdx.x, int64_t(gridDim.x)) * SH::R;
+    if (r0 >= n) return;
+    double *W = lds_raw + SH::R * SH::kSlab, *IW = W + NSMAX + 1;
+    // null species, W by matrix row (1 for the temperature row) and 1/W by matrix column
+    Lds L;
+    double *b = lds_raw + wave * SH::kSlab;
+    double *const fields[7] = {b, b + (NSMAX + 1), b + 2 * (NSMAX + 1), b + 3 * (NSMAX + 1), b + 4 * (NSMAX + 1),
+                               b + 5 * (NSMAX + 1), b + 6 * (NSMAX + 1)};
+    L.C = fields[0];
+    L.G = fields[1];
+    L.H = fields[2];
+    L.WD = fields[3];
+    L.TB = fields[4];
+    L.DWT = fields[5];
+    L.HC = fields[6];
+    L.TROW = b + 7 * (NSMAX + 1);
+    L.JC = b + 8 * (NSMAX + 1);
+    L.ldj = SH::LDJ;
     L.cv = cv;
-    init_lds<1>(M, L, kLdsWhole);
-    const int N = M.N, lane = lane_id();
-    const int64_t r = xcd_reactor(blockIdx.x, int64_t(gridDim.x));
-    if (r >= n) return;
+    init_lds<1>(M, L, kLdsRhs);
+    for (int e = int(threadIdx.x); e < N; e += 512) {
+        W[e] = e == 0 ? 1.0 : M.W()[e - 1];
+        IW[e] = e == 0 ? 1.0 : M.invW()[e - 1];
+    }
+    const int64_t r = min(r0 + wave, n - 1);         // the last workgroup's idle wavefronts repeat a reactor
     const double yl = lane < N ? y[int64_t(lane) * ld + r] : 0.0;
-    double f;
-    const JRow row = jac_whole(M, L, yl, p[r], f);
-    if (lane < N) {
-        double *out = jac + int64_t(lane) * N * ld + r;
-        out[0] = row.c0;
-        for (int j = 1; j < N; j++) out[int64_t(j) * ld] = L.IW[j - 1] * (row.alpha * row.src[j - 1] + row.beta);
+    const double yy[1] = {yl};
+    double ff[1];
+    Mix<1> x;
+    const PairRec first = first_pair<64>(M, lane);
+    zero_jc(L, ns);
+    species_pass<1, true>(M, yy, p[r], L, x);
+    const RxScale sc = rx_scale(L, x);
+    reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, -1, min(WIN, N), kRates, nullptr, lane, first);
+    __syncthreads();
+    finish_rhs<1>(M, L, x, ff);
+    const Chain c = chain_rule(M, L, x, yl, bcast(ff[0], 0));
+    __syncthreads();
+    // per-row scalars in place of the sums: W beta in TB, W col0 in DWT, by species; the temperature row
+    if (L.sl[0].valid) {
+        const int k = L.sl[0].k;
+        L.TB[k] = L.sl[0].W * c.beta;
+        L.DWT[k] = L.sl[0].W * c.col0;
+        L.TROW[1 + k] = c.trow;
+    }
+    if (lane == 0) L.TROW[0] = c.J00;
+    for (int w = 0; w < SH::NWIN; w++) {
+        if (w > 0) {
+            if (w * WIN >= N) break;
+            zero_jc(L, ns);
+            __syncthreads();
+            const PairRec again = first_pair<64>(M, lane);
+            reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, w * WIN - 1, min(WIN, N - w * WIN), kScatter, nullptr, lane,
+                                    again);
+        }
+        __syncthreads();
+        const int s = int(threadIdx.x) & 7;
+        const double *slab = lds_raw + s * SH::kSlab;
+        const int cols = min(WIN, N - w * WIN);
+        if (r0 + s < n)
+            for (int e = int(threadIdx.x) >> 3; e < N * WIN; e += 64) {
+                const int i = e / WIN, jj = e % WIN, j = w * WIN + jj;
+                if (jj >= cols) continue;
+                double v;
+                if (i == 0) v = IW[j] * slab[7 * (NSMAX + 1) + j];
+                else if (j == 0) v = slab[5 * (NSMAX + 1) + i - 1];
+                else v = IW[j] * fma(W[i], slab[8 * (NSMAX + 1) + (i - 1) * SH::LDJ + jj], slab[4 * (NSMAX + 1) + i - 1]);
+                jac[(int64_t(i) * N + j) * ld + r0 + s] = v;
+            }
+        __syncthreads();
     }
 }
 
@@ -1020,6 +1095,23 @@ int launch_int(const DevMech &M, int64_t n, double *y, int64_t ld, const double 
 }
 }  // namespace
 
+namespace {
+template <int NSMAX, int WIN>
+int launch_jac(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac, int cv,
+               hipStream_t s) {
+    using SH = JacShape<NSMAX, WIN>;
+    if (M.nsp > NSMAX) return CK_EUNSUPPORTED;
+    const size_t lds = SH::kLds * sizeof(double);
+    auto kern = jac_wave_kernel<NSMAX, WIN>;
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
+        return CK_EHIP;
+    const int64_t groups = (n + SH::R - 1) / SH::R;
+    kern<<<dim3(unsigned((groups + 7) / 8 * 8)), dim3(512), lds, s>>>(M, n, y, ld, p, jac, cv);
+    return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
+}
+}  // namespace
+
 bool wave_supported(const DevMech &M, int method, int precision) {
     if (method == 0) return M.N <= 64;
     return precision == CK_PREC_FP64 && M.N <= 128;
@@ -1046,10 +1138,10 @@ int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, co
 int launch_jac_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac,
                     int cv, hipStream_t s) {
     if (M.N > 64) return cv ? CK_EUNSUPPORTED : launch_jac_coop(M, n, y, ld, p, jac, s);
-    const size_t lds = lds_doubles(kLdsWhole, M.nsp, 0) * sizeof(double);
-    const unsigned grid = unsigned((n + 7) / 8 * 8);
-    jac_wave_kernel<<<dim3(grid), dim3(64), lds, s>>>(M, n, y, ld, p, jac, cv);
-    return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
+    if (M.N <= 16) return launch_jac<15, 16>(M, n, y, ld, p, jac, cv, s);
+    if (M.N <= 32) return launch_jac<31, 32>(M, n, y, ld, p, jac, cv, s);
+    if (M.N <= 56) return launch_jac<55, 32>(M, n, y, ld, p, jac, cv, s);
+    return launch_jac<63, 24>(M, n, y, ld, p, jac, cv, s);      // eight windows of 32 columns exceed the LDS
 }
 
 int launch_integrate_wave(int method, const DevMech &M, int64_t n, double *y, int64_t ld, const double *p,
