@@ -52,9 +52,8 @@ __device__ __forceinline__ bool wave_all(bool v) { return __ballot(!v) == 0ull; 
 //   | scratch of the tiles                           kLdsTiles (ROS4 with another Jacobian)
 //   | TB DWT HC [ns1] TROW[96] JC                    kLdsJac (ROS4): JC holds d wdot / dC for a window
 //                                                    of columns, then the scratch of the tiles
-//   | TB DWT HC [ns1] TROW[ns + 96] JC IW[64] VX[64] kLdsWhole: d wdot / dC staged in one piece
 // ---------------------------------------------------------------------------------------
-enum LdsKind { kLdsRhs, kLdsTiles, kLdsJac, kLdsWhole };
+enum LdsKind { kLdsRhs, kLdsTiles, kLdsJac };
 
 // Constants of the species that a register slot of this lane holds (slot 0 of lane 0 is T), read once
 // per kernel: an out-of-range slot takes a neighbour's values and `valid` masks what it stores.
@@ -66,7 +65,7 @@ struct SpeciesLane {
 
 struct Lds : RxArrays {
     SpeciesLane sl[2];
-    double *IW, *VX, *TROW;
+    double *TROW;   // temperature row of the matrix, by column, and 32 zeros
     double *park;   // this wavefront's slice of the workspace, or null
     int cv;         // 0: constant pressure (p = pressure); 1: constant volume (p = density)
 };
@@ -82,37 +81,28 @@ struct WaveShape {
     static constexpr bool PARK = NWIN == 2;    // the first window's rate scalars wait for the second
 };
 
-__host__ __device__ inline int whole_ldj(int ns) { return ns | 1; }
 // jc: doubles of the JC region (kLdsTiles, kLdsJac)
 __host__ __device__ inline size_t lds_doubles(LdsKind kind, int ns, size_t jc) {
     size_t d = 4 * size_t(ns + 1);
     if (kind == kLdsTiles) d += jc;
     if (kind == kLdsJac) d += 3 * size_t(ns + 1) + 96 + jc;
-    if (kind == kLdsWhole) {
-        const size_t whole = size_t(ns + 1) * whole_ldj(ns) + 64;
-        d += 3 * size_t(ns + 1) + size_t(ns) + 96 + 128 + (whole > jc ? whole : jc);
-    }
     return d;
 }
 
 __device__ __forceinline__ Lds carve(double *b, LdsKind kind, int ns, int ldj) {
     Lds L;
-    L.JC = L.TB = L.DWT = L.HC = L.TROW = L.IW = L.VX = nullptr;
+    L.JC = L.TB = L.DWT = L.HC = L.TROW = nullptr;
     L.ldj = ldj;
     L.C = b; b += ns + 1;
     L.G = b; b += ns + 1;
     L.H = b; b += ns + 1;
     L.WD = b; b += ns + 1;
     if (kind == kLdsTiles) L.JC = b;
-    if (kind == kLdsJac || kind == kLdsWhole) {
+    if (kind == kLdsJac) {
         L.TB = b; b += ns + 1;
         L.DWT = b; b += ns + 1;
         L.HC = b; b += ns + 1;
-        L.TROW = b; b += kind == kLdsJac ? 96 : ns + 96;
-        if (kind == kLdsWhole) {
-            L.IW = b; b += 64;
-            L.VX = b; b += 64;
-        }
+        L.TROW = b; b += 96;
         L.JC = b;
     }
     L.park = nullptr;
@@ -140,12 +130,6 @@ __device__ __forceinline__ void init_lds(const DevMech &M, Lds &L, LdsKind kind)
     }
     if (kind == kLdsJac)
         for (int e = l; e < 96; e += 64) L.TROW[e] = 0.0;
-    if (kind == kLdsWhole) {
-        for (int e = l; e < ns + 96; e += 64) L.TROW[e] = 0.0;
-        L.IW[l] = l < ns ? M.invW()[l] : 0.0;
-        // read (and multiplied by zero) past the last staged row
-        for (int e = (ns + 1) * L.ldj + l; e < (ns + 1) * L.ldj + 64; e += 64) L.JC[e] = 0.0;
-    }
     __syncthreads();
 }
 
@@ -279,80 +263,16 @@ __device__ __forceinline__ Chain chain_rule(const DevMech &M, const Lds &L, cons
     return o;
 }
 
-// Row of J owned by this lane: J[l][0] = c0, J[l][1 + j] = IW[j] * (alpha * src[j] + beta).
-struct JRow {
-    const double *src;
-    double alpha, beta, c0;
-};
-
-// Row descriptor of J (mass fractions) for N <= 64, one row per lane, d wdot/dC staged whole in LDS.
-__device__ __forceinline__ JRow jac_prepare(const DevMech &M, const Lds &L, const Mix<1> &x, double y0, double fT) {
-    const int lane = lane_fresh();
-    const Chain c = chain_rule(M, L, x, y0, fT);
-    if (L.sl[0].valid) L.TROW[L.sl[0].k] = c.trow;
-    if (lane == 0) L.TROW[M.nsp] = 0.0;     // an FP64 step may have used it
-    __syncthreads();
-    JRow r;
-    if (lane == 0) {
-        r.src = L.TROW;
-        r.alpha = 1.0;
-        r.beta = 0.0;
-        r.c0 = c.J00;
-    } else if (L.sl[0].valid) {
-        r.src = &L.JC[L.sl[0].k * L.ldj];
-        r.alpha = L.sl[0].W;
-        r.beta = L.sl[0].W * c.beta;
-        r.c0 = L.sl[0].W * c.col0;
-    } else {
-        r.src = L.TROW;
-        r.alpha = 0.0;
-        r.beta = 0.0;
-        r.c0 = 0.0;
-    }
-    return r;
-}
-
-// f(y) and the Jacobian pieces with d wdot/dC staged whole.
-__device__ __forceinline__ JRow jac_whole(const DevMech &M, const Lds &L, double y, double P, double &f) {
-    Mix<1> x;
-    const double yy[1] = {y};
-    double ff[1];
-    const PairRec first = first_pair<64>(M, lane_fresh());
-    zero_jc(L, M.nsp);
-    species_pass<1, true>(M, yy, P, L, x);
-    reaction_pass<64, true>(M, L, x.t, x.Ctot, rx_scale(L, x), 0, M.nsp, kRates, nullptr, lane_fresh(), first);
-    __syncthreads();
-    finish_rhs<1>(M, L, x, ff);
-    f = ff[0];
-    return jac_prepare(M, L, x, y, bcast(ff[0], 0));
-}
-
-// f(y) and this lane's row of the iteration matrix M = dg I - J (registers, element type T) for
-// N <= NP <= 64.  The row descriptor jr stays valid (with the Jacobian pieces in LDS) until the
-// next Jacobian, so J x products can be formed later without a stored FP64 matrix.
-template <int NP, class T>
-__device__ __forceinline__ void jac_rows(const DevMech &M, const Lds &L, double y, double P, double dg, T (&a)[NP], double &f,
-                         JRow &jr) {
-    jr = jac_whole(M, L, y, P, f);
-    const int lane = lane_fresh();
-    a[0] = T((lane == 0 ? dg : 0.0) - jr.c0);
-#pragma unroll
-    for (int j = 1; j < NP; j++) a[j] = T((lane == j ? dg : 0.0) - L.IW[j - 1] * (jr.alpha * jr.src[j - 1] + jr.beta));
-    __syncthreads();
-}
-
 // f(y) and the tiles of M' = dg I - J' (J' the Jacobian in the specific mole numbers, similar to J by
 // diag(1, W)) for N <= NP <= 64.  The first window's reaction pass also leaves every per-species sum
 // of the chain rule, so each window's columns are final when they are read.  The second window takes
 // the first one's rate constants from the park slice when they fit (else it evaluates them again).
 // iw and w: 1/W and W of the lane's component (1 for T, 0 for padding).
 template <int NP>
-__device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L0, double y, double P, double dg,
+__device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L, double y, double P, double dg,
                                           wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], double &f, double &iw, double &w) {
     using SH = WaveShape<NP>;
     constexpr int TR = SH::TR, NWIN = SH::NWIN, WIN = SH::WIN;
-    Lds L = L0;
-    L.ldj = SH::LDJ;
     Mix<1> x;
     const double yy[1] = {y};
     double ff[1];
@@ -418,22 +338,6 @@ __device__ __forceinline__ void jac_tiles(const DevMech &M, const Lds &L0, doubl
     __syncthreads();
 }
 
-// (J x) for x distributed one component per lane, from the Jacobian pieces in LDS.
-__device__ __forceinline__ double jac_times(const DevMech &M, const Lds &L, const JRow &r, double x) {
-    const int lane = lane_fresh();
-    const int ns = M.nsp;
-    const bool sp = lane >= 1 && lane <= ns;
-    const double v = sp ? x * L.IW[lane - 1] : 0.0;      // x_{j+1} / W_j
-    if (sp) L.VX[lane - 1] = v;
-    const double Sv = wsum(v);
-    const double x0 = bcast(x, 0);
-    __syncthreads();
-    double dot = 0.0;
-    for (int j = 0; j < ns; j++) dot += r.src[j] * L.VX[j];
-    __syncthreads();
-    return r.c0 * x0 + r.alpha * dot + r.beta * Sv;
-}
-
 // ---------------------------------------------------------------------------------------
 // one steps
 // ---------------------------------------------------------------------------------------
@@ -444,7 +348,7 @@ __device__ __forceinline__ void ros4_stages(const DevMech &M, const Lds &L, doub
                                             const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int ord,
                                             double f, double iw, double w, double &ynew, double &e) {
     const int lane = lane_fresh();
-    auto solve = [&](double b) { return w * wt_solve<NP>(X, s, lane, ord, iw * b); };
+    auto solve = [&](double b) { return w * wt_solve<NP, double>(X, s, lane, ord, iw * b); };
     const double ih = 1.0 / h;
     const double u1 = solve(f);
     // the inverse stays in registers across the stage source terms
@@ -468,7 +372,7 @@ struct Ros4Wave {
         jac_tiles<NP>(M, L, y, P, 1.0 / (Ros4::gamma * h), X, f, iw, w);
         const WScratch s = wt_scratch<NP>(L.JC);
         int ord;
-        const bool ok = wt_invert<NP>(X, s, lane_fresh(), ord);
+        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord);
         ros4_stages<NP>(M, L, y, P, h, X, s, ord, f, iw, w, ynew, e);
         return ok;
     }
@@ -521,7 +425,7 @@ struct Ros4WaveFD {
                 }
         const WScratch s = wt_scratch<NP>(L.JC);
         int ord;
-        const bool ok = wt_invert<NP>(X, s, lane_fresh(), ord);
+        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord);
         ros4_stages<NP>(M, L, y, P, h, X, s, ord, f0[0], 1.0, 1.0, ynew, e);
         return ok;
     }
@@ -530,102 +434,53 @@ struct Ros4WaveFD {
 // ---------------------------------------------------------------------------------------
 // FP32 factorisation with FP64 residual refinement
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ float bcastf(float v, int src) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
-}
 __device__ __forceinline__ double wmax_abs(double v) {
     return __longlong_as_double((long long)__ockl_wfred_max_u64((unsigned long long)__double_as_longlong(fabs(v))));
 }
 
-template <int NP>
-struct LU32 {
-    int pivv, ord;
-    float dinv;
-    bool ok;
-};
-
-template <int NP>
-__device__ __forceinline__ void lu_factor32(float (&a)[NP], LU32<NP> &f) {
-    const int lane = lane_id();
-    bool done = false;
-    f.ord = NP;
-    f.dinv = 0.0f;
-    f.ok = true;
-    f.pivv = 0;
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        const unsigned key = done ? 0u : __float_as_uint(fabsf(a[k]));
-        const unsigned mx = __ockl_wfred_max_u32(key);
-        const int p = __builtin_ctzll(__ballot(!done && key == mx));
-        if (lane == k) f.pivv = p;
-        f.ok = f.ok && (mx != 0u);
-        const float inv = 1.0f / bcastf(a[k], p);
-        if (lane == p) {
-            done = true;
-            f.ord = k;
-            f.dinv = inv;
-        }
-        const float l = done ? 0.0f : a[k] * inv;
-        if (!done) a[k] = l;
-#pragma unroll
-        for (int j = k + 1; j < NP; j++) a[j] = fmaf(-l, bcastf(a[j], p), a[j]);
-    }
-}
-
-template <int NP>
-__device__ __forceinline__ float lu_solve32(const float (&a)[NP], const LU32<NP> &f, float b) {
-    const int lane = lane_fresh();
-    const int pivv = opaque(f.pivv);
-    const int ord = opaque(f.ord);
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        const float yk = bcastf(b, __builtin_amdgcn_readlane(pivv, k));
-        if (ord > k) b = fmaf(-a[k], yk, b);
-    }
-    float x = 0.0f;
-#pragma unroll
-    for (int k = NP - 1; k >= 0; k--) {
-        const float xk = bcastf(b * f.dinv, __builtin_amdgcn_readlane(pivv, k));
-        if (lane == k) x = xk;
-        if (ord < k) b = fmaf(-a[k], xk, b);
-    }
-    return x;
-}
-
-// ROS4 step whose linear solves use an FP32 LU of M = I/(gamma h) - J, refined with FP64
-// residuals r = b - M x (M x formed from the FP64 Jacobian pieces).  A solve is done once the
-// correction is below 2^-48 of the solution.  If a correction fails to halve the previous one, or
-// the allowed sweeps run out first, the FP32 step is abandoned and the reactor-step is done again
-// in FP64 (rows formed in FP64 from the full staged d wdot/dC, FP64 LU); `fb` counts such steps.
-// With zero sweeps the FP32 solutions are used as they are.
+// ROS4 step whose linear solves use an FP32 inverse of M = I/(gamma h) - J (tiles, FP32 matrix cores),
+// refined with FP64 residuals r = b - M x (M's FP64 tiles stay in registers beside it).  A solve is
+// done once the correction is below 2^-48 of the solution (max norms over T and Y).  If a correction
+// fails to halve the previous one, or the allowed sweeps run out first, the FP32 step is abandoned and
+// the reactor-step is done again in FP64; `fb` counts such steps.  With zero sweeps the FP32 solutions
+// are used as they are.
 template <int NP>
 struct Ros4Wave32 {
     __device__ static __forceinline__ bool step32(const DevMech &M, const Lds &L, double y, double P, double h,
                                                   double &ynew, double &e, int sweeps, bool &conv) {
-        float a[NP];
-        double f;
-        JRow jr;
-        const double dg = 1.0 / (Ros4::gamma * h);
-        jac_rows<NP, float>(M, L, y, P, dg, a, f, jr);
-        LU32<NP> lu;
-        lu_factor32<NP>(a, lu);
-        const bool ok = lu.ok;
+        constexpr int TR = WTile<NP>::TR;
+        wd4 X[TR][TR];
+        wf4 F[TR][TR];
+        double f, iw, w;
+        jac_tiles<NP>(M, L, y, P, 1.0 / (Ros4::gamma * h), X, f, iw, w);
+#pragma unroll
+        for (int J = 0; J < TR; J++)
+#pragma unroll
+            for (int I = 0; I < TR; I++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) F[J][I][v] = float(X[J][I][v]);
+        const WScratch s = wt_scratch<NP>(L.JC);
+        const int lane = lane_fresh();
+        int ord;
+        const bool ok = wt_invert<NP, float>(F, s, lane, ord);
         conv = true;
-        auto solve = [&](double b) -> double {
-            double x = double(lu_solve32<NP>(a, lu, float(b)));
-            if (sweeps <= 0) return x;
+        auto solve = [&](double bb) -> double {
+            const double b = iw * bb;
+            double x = double(wt_solve<NP, float>(F, s, lane, ord, float(b)));
+            if (sweeps <= 0) return w * x;
             double dprev = INFINITY;
-            for (int s = 0; s < sweeps; s++) {
-                const double r = b - (dg * x - jac_times(M, L, jr, x));
-                const double d = double(lu_solve32<NP>(a, lu, float(r)));
+            for (int k = 0; k < sweeps; k++) {
+                const double mx = wt_times<NP>(X, s, lane, x);     // every lane takes part
+                const double r = lane < NP ? b - mx : 0.0;
+                const double d = double(wt_solve<NP, float>(F, s, lane, ord, float(r)));
                 x += d;
-                const double dmax = wmax_abs(d), xmax = wmax_abs(x);
-                if (dmax <= 0x1p-48 * xmax) return x;
+                const double dmax = wmax_abs(w * d), xmax = wmax_abs(w * x);
+                if (dmax <= 0x1p-48 * xmax) return w * x;
                 if (!(dmax <= 0.5 * dprev)) break;      // stagnation (or not finite)
                 dprev = dmax;
             }
             conv = false;
-            return x;
+            return w * x;
         };
         const double ih = 1.0 / h;
         const double u1 = solve(f);
@@ -755,15 +610,7 @@ struct Ros4AdapterFD {
 };
 
 template <int NP>
-struct Ros4Adapter32 {
-    static constexpr int RPL = 1;
-    static constexpr int NSMAX = NP - 1;
-    static constexpr LdsKind LDS = kLdsWhole;
-    static constexpr int LDJ = NSMAX | 1;
-    static constexpr int kJc = Ros4Adapter<NP>::kJc;      // the FP64 step of a refactored solve
-    static constexpr bool PARK = WaveShape<NP>::PARK;
-    static constexpr int PARK_ROWS = NP;
-    static constexpr double qinv = 0.25;
+struct Ros4Adapter32 : Ros4Adapter<NP> {
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, const double (&y)[1], double P, double h,
                                 double (&yn)[1], double (&e)[1], const IntOpts &o, int &fb) {
         return Ros4Wave32<NP>::step(M, L, y[0], P, h, yn[0], e[0], o.refine_sweeps, fb);

@@ -25,12 +25,40 @@
 namespace ck {
 
 typedef double wd4 __attribute__((ext_vector_type(4)));
+typedef float wf4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double wt_readlane(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
     return __hiloint2double(hi, lo);
 }
+
+__device__ __forceinline__ float wt_readlane(float v, int src) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
+}
+
+// Element types of the tiles.  The FP32 instruction keeps its accumulator rows contiguous (row 4 g + v
+// on lane group g, register v) where the FP64 one interleaves them (g + 4 v); feeding its A operand
+// the columns in the order ucol(c) gives both the same tile layout.
+template <class T> struct WtType;
+template <> struct WtType<double> {
+    using V = wd4;
+    __device__ static __forceinline__ V mfma(double a, double b, V c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    __device__ static __forceinline__ int ucol(int c) { return c; }
+    __device__ static __forceinline__ unsigned key(double v) { return unsigned(__double2hiint(fabs(v))); }
+    __device__ static __forceinline__ double rcp(double v) { return __builtin_amdgcn_rcp(v); }
+};
+template <> struct WtType<float> {
+    using V = wf4;
+    __device__ static __forceinline__ V mfma(float a, float b, V c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    __device__ static __forceinline__ int ucol(int c) { return (c >> 2) + 4 * (c & 3); }
+    __device__ static __forceinline__ unsigned key(float v) { return __float_as_uint(fabsf(v)); }
+    __device__ static __forceinline__ float rcp(float v) { return __builtin_amdgcn_rcpf(v); }
+};
 
 // f(integral_constant<i>) for i in [B, E).
 template <int B, int E, class F>
@@ -42,21 +70,23 @@ __device__ __forceinline__ void wt_for(F &&f) {
 }
 
 // Search for the next pivot and its reciprocal, cut into short stages of one dependency chain.  The
-// pivot is the lane with the largest high word of |a| (ordered like |a|; values within a relative
-// 2^-20 of the largest may tie, and then the first lane is taken); key is 0 for rows already used.
+// pivot is the lane with the largest |a| (FP64: by the high word, which is ordered like |a|; values
+// within a relative 2^-20 of the largest may tie, and then the first lane is taken); key is 0 for rows
+// already used.
 // Stages 0..5: largest key (rows of 16 lanes, then each row's last lane into the next row and row 1's
 // into the upper half); 6, 7: lane; 8, 9: 1 / pivot estimate; 10..13: two Newton-Raphson steps.
+template <class E>
 struct PivotSearch {
     unsigned key, m;
     int src;
     bool any;
-    double piv, rp, t;
+    E piv, rp, t;
     template <int CTRL, int ROWS>
     __device__ __forceinline__ void fold() {
         m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), CTRL, ROWS, 0xf, true)));
     }
     template <int S>
-    __device__ __forceinline__ void stage(double col) {
+    __device__ __forceinline__ void stage(E col) {
         if constexpr (S == 0) fold<0x111, 0xf>();      // row_shr 1
         if constexpr (S == 1) fold<0x112, 0xf>();      // row_shr 2
         if constexpr (S == 2) fold<0x114, 0xf>();      // row_shr 4
@@ -69,8 +99,8 @@ struct PivotSearch {
         }
         if constexpr (S == 7) src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m));
         if constexpr (S == 8) piv = wt_readlane(col, src);
-        if constexpr (S == 9) rp = __builtin_amdgcn_rcp(piv);
-        if constexpr (S == 10 || S == 12) t = fma(-piv, rp, 1.0);
+        if constexpr (S == 9) rp = WtType<E>::rcp(piv);
+        if constexpr (S == 10 || S == 12) t = fma(-piv, rp, E(1));
         if constexpr (S == 11 || S == 13) rp = fma(t, rp, rp);
     }
 };
@@ -82,6 +112,14 @@ __device__ __forceinline__ double wt_fold32(double a, double b) {
     auto lo = __builtin_amdgcn_permlane32_swap(unsigned(__double2loint(a)), unsigned(__double2loint(b)), false, false);
     auto hi = __builtin_amdgcn_permlane32_swap(unsigned(__double2hiint(a)), unsigned(__double2hiint(b)), false, false);
     return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+}
+__device__ __forceinline__ float wt_fold32(float a, float b) {
+    auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
+__device__ __forceinline__ float wt_fold16(float a, float b) {
+    auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
 }
 __device__ __forceinline__ double wt_fold16(double a, double b) {
     auto lo = __builtin_amdgcn_permlane16_swap(unsigned(__double2loint(a)), unsigned(__double2loint(b)), false, false);
@@ -119,32 +157,35 @@ __device__ __forceinline__ WScratch wt_scratch(double *b) {
 // nonzero diagonal and the rest with zeros).  On return lane r holds in `ord` the pivot order of row
 // r: row r of the tiles is row ord of the inverse, its column 16 J + j the one that belongs to the
 // row of pivot order 16 J + j.  False if a pivot column was zero.
-template <int NP>
-__device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane, int &ord) {
+template <int NP, class T>
+__device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s,
+                                          int lane, int &ord) {
+    using TT = WtType<T>;
     constexpr int TR = WTile<NP>::TR, PLD = WTile<NP>::PLD;
     const int g = lane >> 4, c16 = lane & 15;
+    T *const PNL = reinterpret_cast<T *>(s.PNL);
     bool done = lane >= NP, ok = true;
     ord = NP;
 #pragma unroll 1
     for (int p = 0; p < TR; p++) {
         // the panel (tile column 0; tile columns rotate) with one row per lane
-        double R[16];
+        T R[16];
 #pragma unroll
         for (int I = 0; I < TR; I++)
 #pragma unroll
-            for (int v = 0; v < 4; v++) s.PNL[(g + 4 * v) * PLD + 16 * I + c16] = X[0][I][v];
+            for (int v = 0; v < 4; v++) PNL[(g + 4 * v) * PLD + 16 * I + c16] = X[0][I][v];
         __syncthreads();
         const int lr = TR == 4 ? lane : min(lane, 16 * TR - 1);
 #pragma unroll
-        for (int j = 0; j < 16; j++) R[j] = s.PNL[j * PLD + lr];
+        for (int j = 0; j < 16; j++) R[j] = PNL[j * PLD + lr];
         __syncthreads();
         // Gauss-Jordan in the panel, columns rotating so that the pivot column is R[0].  A pivot row
         // stays unscaled (its multiplier is 0, its own entry 1) and takes the factor 1 / pivot once
         // at the end: every later step is linear in the row.
         const int npv = (NP % 16 != 0 && p == TR - 1) ? NP % 16 : 16;
-        double scale = 1.0;
-        PivotSearch ps;
-        ps.key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
+        T scale = 1;
+        PivotSearch<T> ps;
+        ps.key = done ? 0u : TT::key(R[0]);
         ps.m = ps.key;
         wt_for<0, 14>([&](auto i) { ps.template stage<decltype(i)::value>(R[0]); });
 #pragma unroll 1
@@ -155,8 +196,8 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
                 ok = ok && ps.any;
                 const int src = ps.src;
                 const bool me = lane == src;
-                const double gm = me ? 0.0 : -R[0] * ps.rp;
-                const double last = me ? 1.0 : gm;
+                const T gm = me ? T(0) : -R[0] * ps.rp;
+                const T last = me ? T(1) : gm;
                 done = done || me;
                 scale = me ? ps.rp : scale;
                 ord = me ? 16 * p + c8 + c : ord;
@@ -166,16 +207,16 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
                 // left to itself the compiler puts most of the chain behind the last column.
                 // Each column's lane reads are issued one column early, which covers the wait between a
                 // lane read and the vector instruction that takes its scalar result.
-                PivotSearch nx;
-                double pj = wt_readlane(R[1], src);
+                PivotSearch<T> nx;
+                T pj = wt_readlane(R[1], src);
                 wt_for<1, 16>([&](auto i) {
                     constexpr int j = decltype(i)::value;
-                    const double pn = j < 15 ? wt_readlane(R[j < 15 ? j + 1 : 15], src) : 0.0;
+                    const T pn = j < 15 ? wt_readlane(R[j < 15 ? j + 1 : 15], src) : T(0);
                     __builtin_amdgcn_sched_barrier(0);
                     R[j - 1] = fma(gm, pj, R[j]);
                     pj = pn;
                     if (j == 2) {
-                        nx.key = done ? 0u : unsigned(__double2hiint(fabs(R[0])));
+                        nx.key = done ? 0u : TT::key(R[0]);
                         nx.m = nx.key;
                     }
                     if (j > 2) nx.template stage<(j > 2 ? j - 3 : 0)>(R[0]);
@@ -190,13 +231,13 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
         const int rot = npv & 15;
 #pragma unroll
         for (int j = 0; j < 16; j++)
-            if (lane < 16 * TR) s.PNL[((j + rot) & 15) * PLD + lane] = R[j] * scale;
+            if (lane < 16 * TR) PNL[((j + rot) & 15) * PLD + lane] = R[j] * scale;
         s.ORD[lane] = ord;
         __syncthreads();
 #pragma unroll
         for (int I = 0; I < TR; I++)
 #pragma unroll
-            for (int v = 0; v < 4; v++) X[0][I][v] = s.PNL[(g + 4 * v) * PLD + 16 * I + c16];
+            for (int v = 0; v < 4; v++) X[0][I][v] = PNL[(g + 4 * v) * PLD + 16 * I + c16];
         if (TR > 1) {
             int o[TR];
 #pragma unroll
@@ -211,8 +252,8 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
                     for (int J = 1; J < TR; J++)
 #pragma unroll
                         for (int v = 0; v < 4; v++) {
-                            s.PNL[o[I] * PLD + 16 * J + g + 4 * v] = X[J][I][v];
-                            X[J][I][v] = 0.0;
+                            PNL[o[I] * PLD + 16 * J + g + 4 * v] = X[J][I][v];
+                            X[J][I][v] = T(0);
                         }
                 }
             __syncthreads();
@@ -221,14 +262,14 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     if (NP % 16 != 0 && 4 * k >= npv) break;     // no pivots of these orders
-                    const double u = s.PNL[(4 * k + g) * PLD + 16 * J + c16];
+                    const T u = PNL[(4 * k + g) * PLD + 16 * J + TT::ucol(c16)];
 #pragma unroll
                     for (int I = 0; I < TR; I++)
-                        X[J][I] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, X[0][I][k], X[J][I], 0, 0, 0);
+                        X[J][I] = TT::mfma(u, X[0][I][k], X[J][I]);
                 }
             __syncthreads();
             // the next panel becomes tile column 0
-            wd4 t[TR];
+            typename TT::V t[TR];
 #pragma unroll
             for (int I = 0; I < TR; I++) t[I] = X[0][I];
 #pragma unroll
@@ -242,23 +283,20 @@ __device__ __forceinline__ bool wt_invert(wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR]
     return ok;
 }
 
-// x = A^-1 b from the inverted tiles; b and x one component per lane.
-template <int NP>
-__device__ __forceinline__ double wt_solve(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane,
-                                           int ord, double b) {
+// Rows of tiles times a vector given by column (BS holds column o at 16 (o % 4) + o / 4, so that the
+// values a lane needs are contiguous): row r on lane r.
+template <int NP, class T>
+__device__ __forceinline__ T wt_rows(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const T *BS,
+                                     int lane) {
     constexpr int TR = WTile<NP>::TR;
     const int g = lane >> 4;
-    // b by pivot order, permuted so that the values a lane needs (orders 16 J + g + 4 v) are contiguous:
-    // order o at 16 (o % 4) + o / 4
-    if (ord < NP) s.BS[16 * (ord & 3) + (ord >> 2)] = b;
-    __syncthreads();
-    double bs[4 * TR];
+    T bs[4 * TR];
 #pragma unroll
-    for (int k = 0; k < 4 * TR; k++) bs[k] = 4 * k < NP ? s.BS[16 * g + k] : 0.0;
-    double z[4];
+    for (int k = 0; k < 4 * TR; k++) bs[k] = 4 * k < NP ? BS[16 * g + k] : T(0);
+    T z[4];
 #pragma unroll
     for (int I = 0; I < TR; I++) {
-        double a = 0.0, b2 = 0.0;     // two chains
+        T a = 0, b2 = 0;     // two chains
 #pragma unroll
         for (int J = 0; J < TR; J++) {
             a = fma(X[J][I][0], bs[4 * J], a);
@@ -271,22 +309,38 @@ __device__ __forceinline__ double wt_solve(const wd4 (&X)[WTile<NP>::TR][WTile<N
         z[I] = a + b2;
     }
     // sum over the lane groups; group g keeps row block I = g
-    double r;
     if (TR == 1) {
-        const double h = wt_fold32(z[0], z[0]);
-        r = wt_fold16(h, h);
-    } else if (TR == 2) {
-        const double h0 = wt_fold32(z[0], z[0]), h1 = wt_fold32(z[1], z[1]);
-        r = wt_fold16(h0, h1);
-    } else {
-        const double h0 = wt_fold32(z[0], z[2]), h1 = wt_fold32(z[1], TR == 4 ? z[TR - 1] : z[1]);
-        r = wt_fold16(h0, h1);
+        const T h = wt_fold32(z[0], z[0]);
+        return wt_fold16(h, h);
     }
-    if (ord < NP) s.XS[ord] = r;
+    if (TR == 2) return wt_fold16(wt_fold32(z[0], z[0]), wt_fold32(z[1], z[1]));
+    return wt_fold16(wt_fold32(z[0], z[2]), wt_fold32(z[1], TR == 4 ? z[TR - 1] : z[1]));
+}
+
+// x = A^-1 b from the inverted tiles; b and x one component per lane.
+template <int NP, class T>
+__device__ __forceinline__ T wt_solve(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s,
+                                      int lane, int ord, T b) {
+    T *const BS = reinterpret_cast<T *>(s.BS), *const XS = reinterpret_cast<T *>(s.XS);
+    if (ord < NP) BS[16 * (ord & 3) + (ord >> 2)] = b;
     __syncthreads();
-    const double x = lane < NP ? s.XS[lane] : 0.0;
+    const T r = wt_rows<NP, T>(X, BS, lane);
+    if (ord < NP) XS[ord] = r;
+    __syncthreads();
+    const T x = lane < NP ? XS[lane] : T(0);
     __syncthreads();
     return x;
+}
+
+// A x from the tiles of A itself.
+template <int NP>
+__device__ __forceinline__ double wt_times(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane,
+                                           double x) {
+    if (lane < NP) s.BS[16 * (lane & 3) + (lane >> 2)] = x;
+    __syncthreads();
+    const double r = wt_rows<NP, double>(X, s.BS, lane);
+    __syncthreads();
+    return r;
 }
 
 }  // namespace ck
