@@ -59,7 +59,8 @@ enum {
 enum {
     CK_KERNEL_AUTO = 0,    /* ROS4: WAVE if N <= 64, else GROUP_TILE if N <= 128; RKF45: WAVE if N <= 128 */
     CK_KERNEL_LANE = 1,    /* one reactor per lane, all scratch in global memory (Algorithm 2 analogue) */
-    CK_KERNEL_WAVE = 2,    /* one reactor per 64-lane wavefront, persistent work queue, LU in registers */
+    CK_KERNEL_WAVE = 2,    /* one reactor per 64-lane wavefront, persistent work queue; ROS4: inverse in
+                              register tiles on the matrix cores */
     CK_KERNEL_GROUP = 3,   /* ROS4 only: one reactor per workgroup of 1 (N <= 64) or 4 (N <= 128, matrix
                               rows split over thread pairs) wavefronts, persistent work queue,
                               Gauss-Jordan inverse in registers.  With 4 wavefronts the reaction
@@ -67,11 +68,12 @@ enum {
                               between runs: results agree to rounding, not bit for bit.  Every other
                               kernel gives bitwise identical results for identical inputs, whatever
                               the batch a reactor is in */
-    CK_KERNEL_GROUP_TILE = 4 /* ROS4 only, 64 < N <= 128: the four-wavefront workgroup with the
-                              iteration matrix in 16x16 tiles and a blocked Gauss-Jordan inverse
-                              (panels of 16 columns, partial pivoting) whose rank-16 updates run on
-                              the FP64 matrix cores (MFMA).  Same pivots and results as GROUP up to
-                              rounding; the same summation caveat applies */
+    CK_KERNEL_GROUP_TILE = 4 /* ROS4 only, 64 < N <= 128: the iteration matrix in 16x16 register tiles
+                              and a blocked Gauss-Jordan inverse (panels of 16 columns, partial
+                              pivoting) whose rank-16 updates run on the FP64 matrix cores (MFMA).
+                              FP64 with N <= 112: the whole matrix in one wavefront, results bitwise
+                              identical between runs; otherwise the four-wavefront workgroup, to
+                              which the summation caveat of GROUP applies */
 };
 
 /* Reactor form (Section 3).  Constant pressure: p[] holds pressures (Pa); the density follows
@@ -93,11 +95,11 @@ enum {
 
 /* Precision of the Rosenbrock linear solves. */
 enum {
-    CK_PREC_FP64 = 0,      /* FP64 LU and triangular solves */
+    CK_PREC_FP64 = 0,      /* FP64 factorisation and solves */
     CK_PREC_FP32_REFINE = 1 /* FP32 factorisation with FP64 residual refinement (RHS, Jacobian, error
-                              norm and control stay FP64): FP32 LU in the wavefront kernel (N <= 64),
-                              FP32 matrix-core Gauss-Jordan in the tile workgroup kernel
-                              (64 < N <= 128).  Each solve: x = M32^-1 b, then up to refine_sweeps
+                              norm and control stay FP64): an FP32 matrix-core Gauss-Jordan inverse
+                              in the wavefront kernel (N <= 64) and in the four-wavefront tile
+                              kernel (64 < N <= 128).  Each solve: x = M32^-1 b, then up to refine_sweeps
                               corrections with FP64 residuals b - M x, done once the correction is
                               below 2^-48 of the solution; if a correction fails to halve or the
                               sweeps run out, that step is refactored in FP64 (counted in

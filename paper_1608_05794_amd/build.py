@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libck.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["mech.hip", "k_lane.hip", "k_wave.hip", "k_coop.hip", "api.hip"]
+SOURCES = ["mech.hip", "k_lane.hip", "k_wave.hip", "k_wide.hip", "k_coop.hip", "api.hip"]
 ARCH = os.environ.get("CK_OFFLOAD_ARCH", "gfx950")
 
 # -disable-machine-licm: keeps the backend from hoisting FP64 constants (the exp / log polynomial

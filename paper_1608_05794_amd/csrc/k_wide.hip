@@ -1,0 +1,27 @@
+// Wavefront-per-reactor ROS4 for 64 < N <= 112: the whole iteration matrix in one wavefront's tiles
+// (N = 112: 392 of its 512 registers, one wavefront per SIMD), two state components per lane.
+//
+// Against the four-wavefront workgroup (the matrix over four wavefronts, two workgroups per CU): no
+// barrier between the 16 pivots of a panel, whose search and broadcasts are a serial chain that the four
+// wavefronts ran together, and no panel exchange; four reactors per CU instead of two.  M111 x 4099
+// reactors to 1e-13 s: 405 ms with the workgroup, 308 ms here.  Of a step's 430 k cycles the inverse
+// takes 235 k (pivots 103 k, matrix cores 89 k), the Jacobian windows 110 k, the stage source terms 24 k.
+#include "wave.h"
+
+namespace ck {
+
+bool wide_supported(const DevMech &M) { return M.N > 64 && M.N <= 112; }
+
+int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
+                          double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
+                          int32_t *nrej, hipStream_t s) {
+    unsigned *q = static_cast<unsigned *>(ws);
+    switch ((M.N + 15) / 16 * 16) {
+        case 80: return launch_int<Ros4Adapter<80>>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+        case 96: return launch_int<Ros4Adapter<96>>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+        case 112: return launch_int<Ros4Adapter<112>>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+        default: return CK_EUNSUPPORTED;
+    }
+}
+
+}  // namespace ck

@@ -35,6 +35,12 @@ int launch_integrate_wave(int method, const DevMech &M, int64_t n, double *y, in
                           const double *t_end, double *t, double *h, const IntOpts &o, void *ws,
                           int32_t *status, int32_t *nacc, int32_t *nrej, hipStream_t s);
 
+// one wavefront per reactor for larger states (k_wide.hip): FP64 ROS4, constant pressure
+bool wide_supported(const DevMech &M);
+int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
+                          double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
+                          int32_t *nrej, hipStream_t s);
+
 // workgroup-cooperative ROS4 (k_coop.hip)
 bool coop_supported(const DevMech &M);
 size_t coop_ws_bytes(const DevMech &M, int cus);   // queue counter + parked inverse rows

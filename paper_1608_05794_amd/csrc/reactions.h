@@ -69,15 +69,82 @@ __device__ __forceinline__ PairRec first_pair(const DevMech &M, int tid) {
     return pair_rec(M, min(tid, max(M.nrxn - M.n_gen - 1, 0)));
 }
 
-// f(byte offset of the species, alpha - 1) for the third-body efficiencies of pair-form reaction i.
-template <class F>
-__device__ __forceinline__ void for_efficiencies(const DevMech &M, int i, F &&f) {
+// Third-body efficiencies of pair-form reaction i < n_fall: the first three in registers.
+struct Effs {
+    int4 e;             // species offsets; type | number << 2
+    double am1[3];
+    int begin;
+};
+__device__ __forceinline__ Effs pair_effs(const DevMech &M, int i) {
     const FactorBlock &fb = M.factor[i >> 6];
-    const int l = i & 63, n = fb.eff[l].w >> 2;
-    if (n > 0) f(fb.eff[l].x, fb.am1[0][l]);
-    if (n > 1) f(fb.eff[l].y, fb.am1[1][l]);
-    if (n > 2) f(fb.eff[l].z, fb.am1[2][l]);
-    for (int j = 3; j < n; j++) f(8 * M.eff[fb.eff_begin[l] + j].sp, M.eff[fb.eff_begin[l] + j].am1);
+    const int l = i & 63;
+    return Effs{fb.eff[l], {fb.am1[0][l], fb.am1[1][l], fb.am1[2][l]}, fb.eff_begin[l]};
+}
+// f(byte offset of the species, alpha - 1) for each of them.
+template <class F>
+__device__ __forceinline__ void for_efficiencies(const DevMech &M, const Effs &x, F &&f) {
+    const int n = x.e.w >> 2;
+    if (n > 0) f(x.e.x, x.am1[0]);
+    if (n > 1) f(x.e.y, x.am1[1]);
+    if (n > 2) f(x.e.z, x.am1[2]);
+    for (int j = 3; j < n; j++) f(8 * M.eff[x.begin + j].sp, M.eff[x.begin + j].am1);
+}
+
+// d wdot/dC of one pair-form reaction for the columns [c0, c0 + win): the four slots' columns, then
+// those of the third-body efficiencies.  Rows of the null species go to a row that is never read.
+__device__ __forceinline__ void pair_columns(const DevMech &M, const RxArrays &A, const int4 &o, double cA, double cB,
+                                             double cC, double cD, double ckf, double ckr, double rdm, const Effs &ef,
+                                             int c0, int win) {
+    const int rA = o.x * A.ldj, rB = o.y * A.ldj, rC = o.z * A.ldj, rD = o.w * A.ldj;
+    auto column = [&](int off, double dq) {
+        const int col = off - 8 * c0;
+        if (unsigned(col) < unsigned(8 * win)) {
+            lds_add(A.JC, rA + col, -dq);
+            lds_add(A.JC, rB + col, -dq);
+            lds_add(A.JC, rC + col, dq);
+            lds_add(A.JC, rD + col, dq);
+        }
+    };
+    column(o.x, ckf * cB);
+    column(o.y, ckf * cA);
+    column(o.z, -ckr * cD);
+    column(o.w, -ckr * cC);
+    if (rdm != 0.0) for_efficiencies(M, ef, [&](int off, double am1) { column(off, rdm * am1); });
+}
+
+// A later column window from the first window's scalars.  The pass is a chain of loads and LDS adds, so
+// the next block's offsets and scalars are requested while this one is scattered (windows 2..4 of M111:
+// 90 -> 74 k cycles a step; M53, one window more: 16.3 -> 15.2 k).
+template <int T>
+__device__ __forceinline__ void pair_scatter(const DevMech &M, const RxArrays &A, int c0, int win, const double *keep,
+                                             int tid) {
+    const int nf = M.nrxn - M.n_gen;
+    if (tid >= nf) return;
+    struct Kept {
+        int4 off;
+        double ckf, ckr, rdm;
+        Effs ef;
+    };
+    auto load = [&](int i, Kept &k) {
+        k.off = M.pair[i >> 6].off[i & 63];
+        k.ckf = keep[0];
+        k.ckr = keep[T];
+        k.rdm = 0.0;
+        if (i < M.n_fall) {
+            k.rdm = keep[2 * T];
+            k.ef = pair_effs(M, i);
+        }
+        keep += 3 * T;
+    };
+    Kept next;
+    load(tid, next);
+    for (int i = tid; i < nf; i += T) {
+        const Kept k = next;
+        if (i + T < nf) load(i + T, next);
+        const int4 o = k.off;
+        pair_columns(M, A, o, lds_at(A.C, o.x), lds_at(A.C, o.y), lds_at(A.C, o.z), lds_at(A.C, o.w), k.ckf, k.ckr, k.rdm,
+                     k.ef, c0, win);
+    }
 }
 
 // Pair-form reactions (at most two reactant and two product units, 2 A counting as A + A, and
@@ -99,109 +166,86 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
         const double cA = lds_at(A.C, o.x), cB = lds_at(A.C, o.y), cC = lds_at(A.C, o.z), cD = lds_at(A.C, o.w);
         const bool has1 = o.y != null_off, has3 = o.w != null_off;
         const bool factor = i < M.n_fall;        // third-body or fall-off (the leading reactions)
-        double ckf, ckr, rdm = 0.0;
-        if (JAC && mode == kScatterKept) {
-            ckf = keep[0];
-            ckr = keep[T];
-            if (factor) rdm = keep[2 * T];
-        } else {
-            const double lnkf = fma(-R.EaR, t.invT, fma(R.beta, t.lnT, R.lnA));
-            const double sg = (lds_at(A.G, o.z) + lds_at(A.G, o.w)) - (lds_at(A.G, o.x) + lds_at(A.G, o.y));
-            ckf = ck_exp(lnkf);
-            ckr = ck_exp(lnkf + sg);             // kr = kf / Kc, ln Kc = -sum_k nu_k g_k
-            const double pf = cA * cB, pr = cC * cD;
-            double dlnkf = 0.0, rdT = 0.0, rdMc = 0.0;
-            if (JAC) dlnkf = fma(R.EaR, t.invT, R.beta) * t.invT;
-            if (factor) {
-                const FactorBlock &fb = M.factor[i >> 6];
-                const int l = i & 63;
-                const int4 e = fb.eff[l];
-                const FactorIn in{e.w & 3,     fb.lnA0[l],  fb.beta0[l], fb.Ea0R[l],
-                                  fb.a[l],     fb.invT3[l], fb.invT1[l], fb.T2[l]};
-                double Mc = Ctot;
-                Mc = fma(fb.am1[0][l], lds_at(A.C, e.x), Mc);
-                Mc = fma(fb.am1[1][l], lds_at(A.C, e.y), Mc);
-                Mc = fma(fb.am1[2][l], lds_at(A.C, e.z), Mc);
-                for (int j = 3; j < e.w >> 2; j++) {
-                    const EffRec E = M.eff[fb.eff_begin[l] + j];
-                    Mc = fma(E.am1, A.C[E.sp], Mc);
-                }
-                Factor c;
-                rate_factor<JAC>(in, t, Mc, lnkf, dlnkf, c);
-                const double Rn = ckf * pf - ckr * pr;
-                ckf *= c.c;
-                ckr *= c.c;
-                if (JAC) {
-                    rdm = Rn * c.dcdM;
-                    rdT = Rn * c.dcdT;
-                    rdMc = rdm * c.Mc;
-                }
+        Effs ef;
+        if (factor) ef = pair_effs(M, i);
+        const double lnkf = fma(-R.EaR, t.invT, fma(R.beta, t.lnT, R.lnA));
+        const double sg = (lds_at(A.G, o.z) + lds_at(A.G, o.w)) - (lds_at(A.G, o.x) + lds_at(A.G, o.y));
+        double ckf = ck_exp(lnkf);
+        double ckr = ck_exp(lnkf + sg);             // kr = kf / Kc, ln Kc = -sum_k nu_k g_k
+        const double pf = cA * cB, pr = cC * cD;
+        double dlnkf = 0.0, rdm = 0.0, rdT = 0.0, rdMc = 0.0;
+        if (JAC) dlnkf = fma(R.EaR, t.invT, R.beta) * t.invT;
+        if (factor) {
+            const FactorBlock &fb = M.factor[i >> 6];
+            const int l = i & 63;
+            const FactorIn in{ef.e.w & 3,  fb.lnA0[l],  fb.beta0[l], fb.Ea0R[l],
+                              fb.a[l],     fb.invT3[l], fb.invT1[l], fb.T2[l]};
+            double Mc = Ctot;
+            Mc = fma(ef.am1[0], lds_at(A.C, ef.e.x), Mc);
+            Mc = fma(ef.am1[1], lds_at(A.C, ef.e.y), Mc);
+            Mc = fma(ef.am1[2], lds_at(A.C, ef.e.z), Mc);
+            for (int j = 3; j < ef.e.w >> 2; j++) {
+                const EffRec E = M.eff[ef.begin + j];
+                Mc = fma(E.am1, A.C[E.sp], Mc);
             }
-            const double qf = ckf * pf, qr = ckr * pr, q = qf - qr;
-            if (!JAC || mode != kScatter) {
-                double vT = 0.0, vB = 0.0, shx = 0.0;
-                if (JAC) {
-                    const double sh = (lds_at(A.H, o.z) + lds_at(A.H, o.w)) - (lds_at(A.H, o.x) + lds_at(A.H, o.y));
-                    const double d1 = has1 ? 1.0 : 0.0, d3 = has3 ? 1.0 : 0.0;
-                    const double r = fma(d3, qr, -fma(d1, qf, rdMc));
-                    vT = fma(sc.sT, r, fma(q, dlnkf, fma(qr * sh, t.invT, rdT)));
-                    vB = fma(sc.sB, r, rdm);
-                    shx = fma(sc.dh, d3 - d1, sh);
-                }
-                lds_add(A.WD, o.x, -q);
-                lds_add(A.WD, o.z, q);
-                if (JAC) {
-                    lds_add(A.DWT, o.x, -vT);
-                    lds_add(A.DWT, o.z, vT);
-                    lds_add(A.TB, o.x, -vB);
-                    lds_add(A.TB, o.z, vB);
-                    lds_add(A.HC, o.x, ckf * cB * shx);
-                    lds_add(A.HC, o.z, -ckr * cD * shx);
-                }
-                if (has1) {
-                    lds_add(A.WD, o.y, -q);
-                    if (JAC) {
-                        lds_add(A.DWT, o.y, -vT);
-                        lds_add(A.TB, o.y, -vB);
-                        lds_add(A.HC, o.y, ckf * cA * shx);
-                    }
-                }
-                if (has3) {
-                    lds_add(A.WD, o.w, q);
-                    if (JAC) {
-                        lds_add(A.DWT, o.w, vT);
-                        lds_add(A.TB, o.w, vB);
-                        lds_add(A.HC, o.w, -ckr * cC * shx);
-                    }
-                }
-                if (JAC && factor && rdm != 0.0)
-                    for_efficiencies(M, i, [&](int off, double am1) { lds_add(A.HC, off, rdm * am1 * shx); });
-            }
-            if (JAC && mode == kRatesKeep) {
-                keep[0] = ckf;
-                keep[T] = ckr;
-                if (factor) keep[2 * T] = rdm;
+            Factor c;
+            rate_factor<JAC>(in, t, Mc, lnkf, dlnkf, c);
+            const double Rn = ckf * pf - ckr * pr;
+            ckf *= c.c;
+            ckr *= c.c;
+            if (JAC) {
+                rdm = Rn * c.dcdM;
+                rdT = Rn * c.dcdT;
+                rdMc = rdm * c.Mc;
             }
         }
-        if (JAC) {
-            // rows of the null species go to a row that is never read
-            const int rA = o.x * A.ldj, rB = o.y * A.ldj, rC = o.z * A.ldj, rD = o.w * A.ldj;
-            auto column = [&](int off, double dq) {
-                const int col = off - 8 * c0;
-                if (unsigned(col) < unsigned(8 * win)) {
-                    lds_add(A.JC, rA + col, -dq);
-                    lds_add(A.JC, rB + col, -dq);
-                    lds_add(A.JC, rC + col, dq);
-                    lds_add(A.JC, rD + col, dq);
+        const double qf = ckf * pf, qr = ckr * pr, q = qf - qr;
+        if (!JAC || mode != kScatter) {
+            double vT = 0.0, vB = 0.0, shx = 0.0;
+            if (JAC) {
+                const double sh = (lds_at(A.H, o.z) + lds_at(A.H, o.w)) - (lds_at(A.H, o.x) + lds_at(A.H, o.y));
+                const double d1 = has1 ? 1.0 : 0.0, d3 = has3 ? 1.0 : 0.0;
+                const double r = fma(d3, qr, -fma(d1, qf, rdMc));
+                vT = fma(sc.sT, r, fma(q, dlnkf, fma(qr * sh, t.invT, rdT)));
+                vB = fma(sc.sB, r, rdm);
+                shx = fma(sc.dh, d3 - d1, sh);
+            }
+            lds_add(A.WD, o.x, -q);
+            lds_add(A.WD, o.z, q);
+            if (JAC) {
+                lds_add(A.DWT, o.x, -vT);
+                lds_add(A.DWT, o.z, vT);
+                lds_add(A.TB, o.x, -vB);
+                lds_add(A.TB, o.z, vB);
+                lds_add(A.HC, o.x, ckf * cB * shx);
+                lds_add(A.HC, o.z, -ckr * cD * shx);
+            }
+            if (has1) {
+                lds_add(A.WD, o.y, -q);
+                if (JAC) {
+                    lds_add(A.DWT, o.y, -vT);
+                    lds_add(A.TB, o.y, -vB);
+                    lds_add(A.HC, o.y, ckf * cA * shx);
                 }
-            };
-            column(o.x, ckf * cB);
-            column(o.y, ckf * cA);
-            column(o.z, -ckr * cD);
-            column(o.w, -ckr * cC);
-            if (factor && rdm != 0.0) for_efficiencies(M, i, [&](int off, double am1) { column(off, rdm * am1); });
-            if (mode == kRatesKeep || mode == kScatterKept) keep += 3 * T;
+            }
+            if (has3) {
+                lds_add(A.WD, o.w, q);
+                if (JAC) {
+                    lds_add(A.DWT, o.w, vT);
+                    lds_add(A.TB, o.w, vB);
+                    lds_add(A.HC, o.w, -ckr * cC * shx);
+                }
+            }
+            if (JAC && factor && rdm != 0.0)
+                for_efficiencies(M, ef, [&](int off, double am1) { lds_add(A.HC, off, rdm * am1 * shx); });
         }
+        if (JAC && mode == kRatesKeep) {
+            keep[0] = ckf;
+            keep[T] = ckr;
+            if (factor) keep[2 * T] = rdm;
+            keep += 3 * T;
+        }
+        if (JAC) pair_columns(M, A, o, cA, cB, cC, cD, ckf, ckr, rdm, ef, c0, win);
     }
 }
 
@@ -302,7 +346,8 @@ __device__ __forceinline__ void reaction_pass(const DevMech &M, const RxArrays &
         general_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
         if (JAC && (mode == kRatesKeep || mode == kScatterKept)) keep += 3 * T * ((M.n_gen + T - 1) / T);
     }
-    pair_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid, first);
+    if (JAC && mode == kScatterKept) pair_scatter<T>(M, A, c0, win, keep, tid);
+    else pair_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid, first);
 }
 
 // Chain rule from the accumulators to J = df/dy for the lane's species k, shared by the kernels.

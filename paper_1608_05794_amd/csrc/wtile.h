@@ -1,4 +1,4 @@
-// Dense linear algebra of one wavefront (N <= 64): the iteration matrix in 16 x 16 register tiles and
+// Dense linear algebra of one wavefront (N <= 112): the iteration matrix in 16 x 16 register tiles and
 // its inverse by blocked Gauss-Jordan elimination with partial pivoting, rank-16 updates on the FP64
 // matrix cores; stage solves are matrix-vector products.
 //
@@ -9,7 +9,7 @@
 // T[16 I + c][4 s + g]) is register s of the eliminated panel's own tile, so the panel is not loaded a
 // second time; the A operand is the panel's pivot rows, read from LDS.  A matrix-vector product is
 // 16 TR multiply-adds per lane and row block and a sum over the four lane groups that leaves row
-// 16 g + c on lane (g, c), i.e. one component per lane.
+// 16 g + c on lane (g, c), i.e. one component per lane (rows from 64 on in a second register).
 //
 // Why this form (measured at N = 54, M53, 16384 reactors to 1e-13 s): the register LU with one row per
 // lane spent about 6300 vector instructions on the factorisation (two lane reads and a hazard wait per
@@ -70,23 +70,28 @@ __device__ __forceinline__ void wt_for(F &&f) {
 }
 
 // Search for the next pivot and its reciprocal, cut into short stages of one dependency chain.  The
-// pivot is the lane with the largest |a| (FP64: by the high word, which is ordered like |a|; values
+// pivot is the row with the largest |a| (FP64: by the high word, which is ordered like |a|; values
 // within a relative 2^-20 of the largest may tie, and then the first lane is taken); key is 0 for rows
-// already used.
+// already used.  With two rows per lane (lane and lane + 64) sel tells which one it is.
 // Stages 0..5: largest key (rows of 16 lanes, then each row's last lane into the next row and row 1's
 // into the upper half); 6, 7: lane; 8, 9: 1 / pivot estimate; 10..13: two Newton-Raphson steps.
-template <class E>
+template <class E, int ROWS>
 struct PivotSearch {
-    unsigned key, m;
+    unsigned key[ROWS], m;
     int src;
-    bool any;
+    bool any, sel;
     E piv, rp, t;
-    template <int CTRL, int ROWS>
+    __device__ __forceinline__ void start(const E (&R)[ROWS][16], const bool (&done)[ROWS]) {
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) key[r] = done[r] ? 0u : WtType<E>::key(R[r][0]);
+        m = ROWS == 2 ? max(key[0], key[ROWS - 1]) : key[0];
+    }
+    template <int CTRL, int LANES>
     __device__ __forceinline__ void fold() {
-        m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), CTRL, ROWS, 0xf, true)));
+        m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), CTRL, LANES, 0xf, true)));
     }
     template <int S>
-    __device__ __forceinline__ void stage(E col) {
+    __device__ __forceinline__ void stage(const E (&R)[ROWS][16]) {
         if constexpr (S == 0) fold<0x111, 0xf>();      // row_shr 1
         if constexpr (S == 1) fold<0x112, 0xf>();      // row_shr 2
         if constexpr (S == 2) fold<0x114, 0xf>();      // row_shr 4
@@ -97,8 +102,23 @@ struct PivotSearch {
             m = unsigned(__builtin_amdgcn_readlane(int(m), 63));
             any = m != 0u;
         }
-        if constexpr (S == 7) src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m));
-        if constexpr (S == 8) piv = wt_readlane(col, src);
+        if constexpr (S == 7) {
+            if constexpr (ROWS == 1) {
+                src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key[0] == m));
+                sel = false;
+            } else {
+                const unsigned long long b0 = __builtin_amdgcn_ballot_w64(key[0] == m);
+                sel = b0 == 0ull;
+                src = __builtin_ctzll(sel ? __builtin_amdgcn_ballot_w64(key[ROWS - 1] == m) : b0);
+            }
+        }
+        if constexpr (S == 8) {
+            piv = wt_readlane(R[0][0], src);
+            if constexpr (ROWS == 2) {
+                const E p1 = wt_readlane(R[ROWS - 1][0], src);
+                piv = sel ? p1 : piv;
+            }
+        }
         if constexpr (S == 9) rp = WtType<E>::rcp(piv);
         if constexpr (S == 10 || S == 12) t = fma(-piv, rp, E(1));
         if constexpr (S == 11 || S == 13) rp = fma(t, rp, rp);
@@ -129,12 +149,13 @@ __device__ __forceinline__ double wt_fold16(double a, double b) {
 
 template <int NP>
 struct WTile {
-    static_assert(NP % 8 == 0 && NP <= 64, "one wavefront: up to 64 rows");
+    static_assert(NP % 8 == 0 && (NP <= 64 || (NP % 16 == 0 && NP <= 112)), "up to 112 rows, 392 tile registers");
     static constexpr int TR = (NP + 15) / 16;     // tiles per side
+    static constexpr int ROWS = NP > 64 ? 2 : 1;  // matrix rows per lane where rows lie one per lane
     // column stride of the panel buffer and row stride of the pivot rows (doubles): 4 over a multiple
     // of 16, so the four lane groups of an access start in different banks
     static constexpr int PLD = 16 * TR + 4;
-    static constexpr int kScratch = 16 * PLD + 64 + 64 + 32;   // panel / pivot rows, vectors, pivot orders
+    static constexpr int kScratch = 16 * PLD + 3 * 64 * ROWS;   // panel / pivot rows, vectors, pivot orders
     using Mat = wd4[TR][TR];
 };
 
@@ -148,46 +169,52 @@ __device__ __forceinline__ WScratch wt_scratch(double *b) {
     WScratch s;
     s.PNL = b;
     s.BS = b + 16 * WTile<NP>::PLD;
-    s.XS = s.BS + 64;
-    s.ORD = reinterpret_cast<int *>(s.XS + 64);
+    s.XS = s.BS + 64 * WTile<NP>::ROWS;
+    s.ORD = reinterpret_cast<int *>(s.XS + 64 * WTile<NP>::ROWS);
     return s;
 }
 
 // In-place inverse of the leading NP x NP block (the caller pads rows and columns N..NP-1 with a
-// nonzero diagonal and the rest with zeros).  On return lane r holds in `ord` the pivot order of row
-// r: row r of the tiles is row ord of the inverse, its column 16 J + j the one that belongs to the
-// row of pivot order 16 J + j.  False if a pivot column was zero.
+// nonzero diagonal and the rest with zeros).  On return lane l holds in ord[r] the pivot order of row
+// l + 64 r: that row of the tiles is row ord of the inverse, its column 16 J + j the one that belongs
+// to the row of pivot order 16 J + j.  False if a pivot column was zero.
 template <int NP, class T>
 __device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s,
-                                          int lane, int &ord) {
+                                          int lane, int (&ord)[WTile<NP>::ROWS]) {
     using TT = WtType<T>;
-    constexpr int TR = WTile<NP>::TR, PLD = WTile<NP>::PLD;
+    constexpr int TR = WTile<NP>::TR, PLD = WTile<NP>::PLD, ROWS = WTile<NP>::ROWS;
     const int g = lane >> 4, c16 = lane & 15;
     T *const PNL = reinterpret_cast<T *>(s.PNL);
-    bool done = lane >= NP, ok = true;
-    ord = NP;
+    bool done[ROWS], ok = true;
+#pragma unroll
+    for (int r = 0; r < ROWS; r++) {
+        done[r] = lane + 64 * r >= NP;
+        ord[r] = NP;
+    }
 #pragma unroll 1
     for (int p = 0; p < TR; p++) {
-        // the panel (tile column 0; tile columns rotate) with one row per lane
-        T R[16];
+        // the panel (tile column 0; tile columns rotate) with one or two rows per lane
+        T R[ROWS][16];
 #pragma unroll
         for (int I = 0; I < TR; I++)
 #pragma unroll
             for (int v = 0; v < 4; v++) PNL[(g + 4 * v) * PLD + 16 * I + c16] = X[0][I][v];
         __syncthreads();
-        const int lr = TR == 4 ? lane : min(lane, 16 * TR - 1);
 #pragma unroll
-        for (int j = 0; j < 16; j++) R[j] = PNL[j * PLD + lr];
+        for (int r = 0; r < ROWS; r++)
+#pragma unroll
+            for (int j = 0; j < 16; j++) R[r][j] = PNL[j * PLD + min(lane + 64 * r, 16 * TR - 1)];
         __syncthreads();
-        // Gauss-Jordan in the panel, columns rotating so that the pivot column is R[0].  A pivot row
+        // Gauss-Jordan in the panel, columns rotating so that the pivot column is R[.][0].  A pivot row
         // stays unscaled (its multiplier is 0, its own entry 1) and takes the factor 1 / pivot once
         // at the end: every later step is linear in the row.
         const int npv = (NP % 16 != 0 && p == TR - 1) ? NP % 16 : 16;
-        T scale = 1;
-        PivotSearch<T> ps;
-        ps.key = done ? 0u : TT::key(R[0]);
-        ps.m = ps.key;
-        wt_for<0, 14>([&](auto i) { ps.template stage<decltype(i)::value>(R[0]); });
+        T scale[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) scale[r] = T(1);
+        PivotSearch<T, ROWS> ps;
+        ps.start(R, done);
+        wt_for<0, 14>([&](auto i) { ps.template stage<decltype(i)::value>(R); });
 #pragma unroll 1
         for (int c8 = 0; c8 < npv; c8 += 8) {
             // eight pivots of straight-line code, so that the rotation is register renaming
@@ -195,44 +222,60 @@ __device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::
             for (int c = 0; c < 8; c++) {
                 ok = ok && ps.any;
                 const int src = ps.src;
-                const bool me = lane == src;
-                const T gm = me ? T(0) : -R[0] * ps.rp;
-                const T last = me ? T(1) : gm;
-                done = done || me;
-                scale = me ? ps.rp : scale;
-                ord = me ? 16 * p + c8 + c : ord;
-                // the next pivot's column first, then its search and reciprocal (a chain of about 20
+                T gm[ROWS], last[ROWS];
+#pragma unroll
+                for (int r = 0; r < ROWS; r++) {
+                    const bool me = lane == src && (ROWS == 1 || ps.sel == (r == 1));
+                    gm[r] = me ? T(0) : -R[r][0] * ps.rp;
+                    last[r] = me ? T(1) : gm[r];
+                    done[r] = done[r] || me;
+                    scale[r] = me ? ps.rp : scale[r];
+                    ord[r] = me ? 16 * p + c8 + c : ord[r];
+                }
+                // The next pivot's column first, then its search and reciprocal (a chain of about 20
                 // dependent instructions) one stage per updated column: the chain's latency is spent
                 // on the other columns' lane reads and multiply-adds.  The order is fixed by hand;
                 // left to itself the compiler puts most of the chain behind the last column.
                 // Each column's lane reads are issued one column early, which covers the wait between a
                 // lane read and the vector instruction that takes its scalar result.
-                PivotSearch<T> nx;
-                T pj = wt_readlane(R[1], src);
-                wt_for<1, 16>([&](auto i) {
-                    constexpr int j = decltype(i)::value;
-                    const T pn = j < 15 ? wt_readlane(R[j < 15 ? j + 1 : 15], src) : T(0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    R[j - 1] = fma(gm, pj, R[j]);
-                    pj = pn;
-                    if (j == 2) {
-                        nx.key = done ? 0u : TT::key(R[0]);
-                        nx.m = nx.key;
-                    }
-                    if (j > 2) nx.template stage<(j > 2 ? j - 3 : 0)>(R[0]);
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-                nx.template stage<13>(R[0]);
-                R[15] = last;
+                PivotSearch<T, ROWS> nx;
+                auto columns = [&](auto which) {
+                    constexpr int Q = decltype(which)::value;       // the pivot row's register
+                    T pj = wt_readlane(R[Q][1], src);
+                    wt_for<1, 16>([&](auto i) {
+                        constexpr int j = decltype(i)::value;
+                        const T pn = j < 15 ? wt_readlane(R[Q][j < 15 ? j + 1 : 15], src) : T(0);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int r = 0; r < ROWS; r++) R[r][j - 1] = fma(gm[r], pj, R[r][j]);
+                        pj = pn;
+                        if (j == 2) nx.start(R, done);
+                        if (j > 2) nx.template stage<(j > 2 ? j - 3 : 0)>(R);
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                };
+                if constexpr (ROWS == 1) {
+                    columns(std::integral_constant<int, 0>{});
+                } else {
+                    if (ps.sel) columns(std::integral_constant<int, ROWS - 1>{});
+                    else columns(std::integral_constant<int, 0>{});
+                }
+                nx.template stage<13>(R);
+#pragma unroll
+                for (int r = 0; r < ROWS; r++) R[r][15] = last[r];
                 ps = nx;
             }
         }
-        // npv rotations leave column j in R[(j - npv) mod 16]
+        // npv rotations leave column j in R[.][(j - npv) mod 16]
         const int rot = npv & 15;
 #pragma unroll
-        for (int j = 0; j < 16; j++)
-            if (lane < 16 * TR) PNL[((j + rot) & 15) * PLD + lane] = R[j] * scale;
-        s.ORD[lane] = ord;
+        for (int r = 0; r < ROWS; r++)
+            if (lane + 64 * r < 16 * TR) {
+#pragma unroll
+                for (int j = 0; j < 16; j++) PNL[((j + rot) & 15) * PLD + lane + 64 * r] = R[r][j] * scale[r];
+            }
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) s.ORD[lane + 64 * r] = ord[r];
         __syncthreads();
 #pragma unroll
         for (int I = 0; I < TR; I++)
@@ -264,8 +307,7 @@ __device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::
                     if (NP % 16 != 0 && 4 * k >= npv) break;     // no pivots of these orders
                     const T u = PNL[(4 * k + g) * PLD + 16 * J + TT::ucol(c16)];
 #pragma unroll
-                    for (int I = 0; I < TR; I++)
-                        X[J][I] = TT::mfma(u, X[0][I][k], X[J][I]);
+                    for (int I = 0; I < TR; I++) X[J][I] = TT::mfma(u, X[0][I][k], X[J][I]);
                 }
             __syncthreads();
             // the next panel becomes tile column 0
@@ -283,17 +325,19 @@ __device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::
     return ok;
 }
 
-// Rows of tiles times a vector given by column (BS holds column o at 16 (o % 4) + o / 4, so that the
-// values a lane needs are contiguous): row r on lane r.
+// Rows of tiles times a vector given by column (BS holds column o at 4 TR (o % 4) + o / 4, so that the
+// values a lane needs are contiguous): row l + 64 r on lane l, register r.
+template <int NP>
+__device__ __forceinline__ int wt_slot(int o) { return 4 * WTile<NP>::TR * (o & 3) + (o >> 2); }
 template <int NP, class T>
-__device__ __forceinline__ T wt_rows(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const T *BS,
-                                     int lane) {
+__device__ __forceinline__ void wt_rows(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const T *BS,
+                                        int lane, T (&out)[WTile<NP>::ROWS]) {
     constexpr int TR = WTile<NP>::TR;
     const int g = lane >> 4;
     T bs[4 * TR];
 #pragma unroll
-    for (int k = 0; k < 4 * TR; k++) bs[k] = 4 * k < NP ? BS[16 * g + k] : T(0);
-    T z[4];
+    for (int k = 0; k < 4 * TR; k++) bs[k] = 4 * k < NP ? BS[4 * TR * g + k] : T(0);
+    T z[8];
 #pragma unroll
     for (int I = 0; I < TR; I++) {
         T a = 0, b2 = 0;     // two chains
@@ -308,39 +352,51 @@ __device__ __forceinline__ T wt_rows(const typename WtType<T>::V (&X)[WTile<NP>:
         }
         z[I] = a + b2;
     }
-    // sum over the lane groups; group g keeps row block I = g
-    if (TR == 1) {
-        const T h = wt_fold32(z[0], z[0]);
-        return wt_fold16(h, h);
-    }
-    if (TR == 2) return wt_fold16(wt_fold32(z[0], z[0]), wt_fold32(z[1], z[1]));
-    return wt_fold16(wt_fold32(z[0], z[2]), wt_fold32(z[1], TR == 4 ? z[TR - 1] : z[1]));
+    // sum over the lane groups; group g keeps row block I = g (and 4 + g)
+    auto fold = [&](int I0, int count) {
+        if (count == 1) {
+            const T h = wt_fold32(z[I0], z[I0]);
+            return wt_fold16(h, h);
+        }
+        if (count == 2) return wt_fold16(wt_fold32(z[I0], z[I0]), wt_fold32(z[I0 + 1], z[I0 + 1]));
+        return wt_fold16(wt_fold32(z[I0], z[I0 + 2]), wt_fold32(z[I0 + 1], count == 4 ? z[I0 + 3] : z[I0 + 1]));
+    };
+    out[0] = fold(0, TR < 4 ? TR : 4);
+    if constexpr (WTile<NP>::ROWS == 2) out[1] = fold(4, TR - 4);
 }
 
-// x = A^-1 b from the inverted tiles; b and x one component per lane.
+// x = A^-1 b from the inverted tiles; component l + 64 r of b and x on lane l, register r.
 template <int NP, class T>
-__device__ __forceinline__ T wt_solve(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s,
-                                      int lane, int ord, T b) {
+__device__ __forceinline__ void wt_solve(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR],
+                                         const WScratch &s, int lane, const int (&ord)[WTile<NP>::ROWS],
+                                         const T (&b)[WTile<NP>::ROWS], T (&x)[WTile<NP>::ROWS]) {
+    constexpr int ROWS = WTile<NP>::ROWS;
     T *const BS = reinterpret_cast<T *>(s.BS), *const XS = reinterpret_cast<T *>(s.XS);
-    if (ord < NP) BS[16 * (ord & 3) + (ord >> 2)] = b;
+#pragma unroll
+    for (int r = 0; r < ROWS; r++)
+        if (ord[r] < NP) BS[wt_slot<NP>(ord[r])] = b[r];
     __syncthreads();
-    const T r = wt_rows<NP, T>(X, BS, lane);
-    if (ord < NP) XS[ord] = r;
+    T z[ROWS];
+    wt_rows<NP, T>(X, BS, lane, z);
+#pragma unroll
+    for (int r = 0; r < ROWS; r++)
+        if (ord[r] < NP) XS[ord[r]] = z[r];
     __syncthreads();
-    const T x = lane < NP ? XS[lane] : T(0);
+#pragma unroll
+    for (int r = 0; r < ROWS; r++) x[r] = lane + 64 * r < NP ? XS[lane + 64 * r] : T(0);
     __syncthreads();
-    return x;
 }
 
 // A x from the tiles of A itself.
 template <int NP>
-__device__ __forceinline__ double wt_times(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane,
-                                           double x) {
-    if (lane < NP) s.BS[16 * (lane & 3) + (lane >> 2)] = x;
+__device__ __forceinline__ void wt_times(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s, int lane,
+                                         const double (&x)[WTile<NP>::ROWS], double (&z)[WTile<NP>::ROWS]) {
+#pragma unroll
+    for (int r = 0; r < WTile<NP>::ROWS; r++)
+        if (lane + 64 * r < NP) s.BS[wt_slot<NP>(lane + 64 * r)] = x[r];
     __syncthreads();
-    const double r = wt_rows<NP, double>(X, s.BS, lane);
+    wt_rows<NP, double>(X, s.BS, lane, z);
     __syncthreads();
-    return r;
 }
 
 }  // namespace ck
