@@ -408,15 +408,15 @@ __device__ __forceinline__ void ros4_stages(const DevMech &M, const Lds &L, cons
 }
 
 // Solve with the inverted tiles of M in the variables z = y / w: iw scales a right-hand side, w a solution.
-template <int NP>
+template <int NP, int PJ = 0>
 __device__ __forceinline__ bool tile_solve(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], const WScratch &s,
                                            const int (&ord)[WTile<NP>::ROWS], const double (&iw)[WTile<NP>::ROWS],
                                            const double (&w)[WTile<NP>::ROWS], const double (&b)[WTile<NP>::ROWS],
-                                           double (&u)[WTile<NP>::ROWS]) {
+                                           double (&u)[WTile<NP>::ROWS], const double *park = nullptr) {
     double bz[WTile<NP>::ROWS], z[WTile<NP>::ROWS];
 #pragma unroll
     for (int c = 0; c < WTile<NP>::ROWS; c++) bz[c] = iw[c] * b[c];
-    wt_solve<NP, double>(X, s, lane_fresh(), ord, bz, z);
+    wt_solve<NP, double, PJ>(X, s, lane_fresh(), ord, bz, z, park);
 #pragma unroll
     for (int c = 0; c < WTile<NP>::ROWS; c++) u[c] = w[c] * z[c];
     return true;
@@ -433,11 +433,27 @@ struct Ros4Wave {
         const WScratch s = wt_scratch<NP>(L.JC);
         int ord[RPL];
         const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord);
-        ros4_stages<RPL>(M, L, y, P, h, f,
-                         [&](const double (&b)[RPL], double (&u)[RPL]) {
-                             return tile_solve<NP>(X, s, ord, iw, w, b, u);
-                         },
-                         ynew, e);
+        constexpr int PJ = WTile<NP>::PJ;
+        if constexpr (PJ > 0) {
+            // the solves' vectors move to the Jacobian's per-species sums, the tiles to the staging area
+            static_assert(WTile<NP>::kPark <= WaveShape<NP>::kJc && 2 * 64 * RPL <= 3 * NP);
+            __syncthreads();
+            wt_park<NP>(X, L.JC, lane_fresh());
+            WScratch sv = s;
+            sv.BS = L.TB;
+            sv.XS = L.TB + 64 * RPL;
+            ros4_stages<RPL>(M, L, y, P, h, f,
+                             [&](const double (&b)[RPL], double (&u)[RPL]) {
+                                 return tile_solve<NP, PJ>(X, sv, ord, iw, w, b, u, L.JC);
+                             },
+                             ynew, e);
+        } else {
+            ros4_stages<RPL>(M, L, y, P, h, f,
+                             [&](const double (&b)[RPL], double (&u)[RPL]) {
+                                 return tile_solve<NP>(X, s, ord, iw, w, b, u);
+                             },
+                             ynew, e);
+        }
         return ok;
     }
 };

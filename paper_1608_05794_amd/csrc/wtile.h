@@ -156,6 +156,11 @@ struct WTile {
     // of 16, so the four lane groups of an access start in different banks
     static constexpr int PLD = 16 * TR + 4;
     static constexpr int kScratch = 16 * PLD + 3 * 64 * ROWS;   // panel / pivot rows, vectors, pivot orders
+    // Tile columns of the inverse that wait in LDS while the stages run (kPark doubles).  At 112 rows
+    // the tiles leave 120 registers where a source term takes about 130; left to itself the compiler
+    // spills tiles and reloads them one by one inside the solves (M111: a solve 15 k cycles; ROS4 x 4099 302 -> 291 ms).
+    static constexpr int PJ = TR == 7 ? 2 : 0;
+    static constexpr int kPark = PJ * TR * 4 * 64;
     using Mat = wd4[TR][TR];
 };
 
@@ -329,9 +334,10 @@ __device__ __forceinline__ bool wt_invert(typename WtType<T>::V (&X)[WTile<NP>::
 // values a lane needs are contiguous): row l + 64 r on lane l, register r.
 template <int NP>
 __device__ __forceinline__ int wt_slot(int o) { return 4 * WTile<NP>::TR * (o & 3) + (o >> 2); }
-template <int NP, class T>
+// PJ: the last PJ tile columns are in LDS (wt_park).
+template <int NP, class T, int PJ = 0>
 __device__ __forceinline__ void wt_rows(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR], const T *BS,
-                                        int lane, T (&out)[WTile<NP>::ROWS]) {
+                                        int lane, T (&out)[WTile<NP>::ROWS], const T *park = nullptr) {
     constexpr int TR = WTile<NP>::TR;
     const int g = lane >> 4;
     T bs[4 * TR];
@@ -343,11 +349,14 @@ __device__ __forceinline__ void wt_rows(const typename WtType<T>::V (&X)[WTile<N
         T a = 0, b2 = 0;     // two chains
 #pragma unroll
         for (int J = 0; J < TR; J++) {
-            a = fma(X[J][I][0], bs[4 * J], a);
-            b2 = fma(X[J][I][1], bs[4 * J + 1], b2);
+            auto x = [&](int v) {
+                return J < TR - PJ ? X[J][I][v] : park[(4 * ((J - (TR - PJ)) * TR + I) + v) * 64 + lane];
+            };
+            a = fma(x(0), bs[4 * J], a);
+            b2 = fma(x(1), bs[4 * J + 1], b2);
             if (16 * J + 8 < NP) {
-                a = fma(X[J][I][2], bs[4 * J + 2], a);
-                b2 = fma(X[J][I][3], bs[4 * J + 3], b2);
+                a = fma(x(2), bs[4 * J + 2], a);
+                b2 = fma(x(3), bs[4 * J + 3], b2);
             }
         }
         z[I] = a + b2;
@@ -365,11 +374,24 @@ __device__ __forceinline__ void wt_rows(const typename WtType<T>::V (&X)[WTile<N
     if constexpr (WTile<NP>::ROWS == 2) out[1] = fold(4, TR - 4);
 }
 
+// The last WTile::PJ tile columns to LDS.
+template <int NP>
+__device__ __forceinline__ void wt_park(const wd4 (&X)[WTile<NP>::TR][WTile<NP>::TR], double *park, int lane) {
+    constexpr int TR = WTile<NP>::TR, PJ = WTile<NP>::PJ;
+#pragma unroll
+    for (int J = TR - PJ; J < TR; J++)
+#pragma unroll
+        for (int I = 0; I < TR; I++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) park[(4 * ((J - (TR - PJ)) * TR + I) + v) * 64 + lane] = X[J][I][v];
+}
+
 // x = A^-1 b from the inverted tiles; component l + 64 r of b and x on lane l, register r.
-template <int NP, class T>
+template <int NP, class T, int PJ = 0>
 __device__ __forceinline__ void wt_solve(const typename WtType<T>::V (&X)[WTile<NP>::TR][WTile<NP>::TR],
                                          const WScratch &s, int lane, const int (&ord)[WTile<NP>::ROWS],
-                                         const T (&b)[WTile<NP>::ROWS], T (&x)[WTile<NP>::ROWS]) {
+                                         const T (&b)[WTile<NP>::ROWS], T (&x)[WTile<NP>::ROWS],
+                                         const T *park = nullptr) {
     constexpr int ROWS = WTile<NP>::ROWS;
     T *const BS = reinterpret_cast<T *>(s.BS), *const XS = reinterpret_cast<T *>(s.XS);
 #pragma unroll
@@ -377,7 +399,7 @@ __device__ __forceinline__ void wt_solve(const typename WtType<T>::V (&X)[WTile<
         if (ord[r] < NP) BS[wt_slot<NP>(ord[r])] = b[r];
     __syncthreads();
     T z[ROWS];
-    wt_rows<NP, T>(X, BS, lane, z);
+    wt_rows<NP, T, PJ>(X, BS, lane, z, park);
 #pragma unroll
     for (int r = 0; r < ROWS; r++)
         if (ord[r] < NP) XS[ord[r]] = z[r];
