@@ -432,7 +432,7 @@ struct Ros4Wave {
         jac_tiles<NP>(M, L, y, P, 1.0 / (Ros4::gamma * h), X, f, iw, w);
         const WScratch s = wt_scratch<NP>(L.JC);
         int ord[RPL];
-        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord);
+        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord, M.N);
         constexpr int PJ = WTile<NP>::PJ;
         if constexpr (PJ > 0) {
             // the solves' vectors move to the Jacobian's per-species sums, the tiles to the staging area
@@ -506,7 +506,7 @@ struct Ros4WaveFD {
                 }
         const WScratch s = wt_scratch<NP>(L.JC);
         int ord[1];
-        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord);
+        const bool ok = wt_invert<NP, double>(X, s, lane_fresh(), ord, M.N);
         const double one[1] = {1.0};
         ros4_stages<1>(M, L, yy, P, h, f0,
                        [&](const double (&b)[1], double (&u)[1]) { return tile_solve<NP>(X, s, ord, one, one, b, u); },
@@ -546,7 +546,7 @@ struct Ros4Wave32 {
         const WScratch s = wt_scratch<NP>(L.JC);
         const int lane = lane_fresh();
         int ord[1];
-        const bool ok = wt_invert<NP, float>(F, s, lane, ord);
+        const bool ok = wt_invert<NP, float>(F, s, lane, ord, M.N);
         conv = true;
         auto inverse = [&](double b) {
             const float bf[1] = {float(b)};
