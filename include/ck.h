@@ -116,7 +116,9 @@ typedef struct {
     int32_t precision;     /* CK_PREC_* (ROS4 only) */
     int32_t refine_sweeps; /* FP32 mode: maximum FP64 refinement sweeps, 0..3 */
     int32_t blocks_per_cu; /* persistent kernels (WAVE, GROUP): resident workgroups per compute unit;
-                              0 = as many as registers and LDS allow (larger values are clamped) */
+                              0 = as many as registers and LDS allow (larger values are clamped).
+                              GROUP_TILE: counted in four-wavefront workgroups; the one-wavefront
+                              form keeps two reactors resident for each */
     int32_t jacobian;      /* CK_JAC_* (ROS4 only) */
     int32_t reactor;       /* CK_REACTOR_*: with CK_REACTOR_CONST_V the p array holds densities */
     int32_t *n_fallback;   /* CK_PREC_FP32_REFINE only, optional (NULL: not reported): device array

@@ -13,9 +13,12 @@ namespace ck {
 bool wide_supported(const DevMech &M) { return M.N > 64 && M.N <= 112; }
 
 int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
-                          double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
+                          double *t, double *h, const IntOpts &opts, void *ws, int32_t *status, int32_t *nacc,
                           int32_t *nrej, hipStream_t s) {
     unsigned *q = static_cast<unsigned *>(ws);
+    IntOpts o = opts;
+    // counted in workgroups of the four-wavefront form, of which two fill a CU as four of these do
+    if (o.blocks_per_cu > 0) o.blocks_per_cu = o.blocks_per_cu < 2 ? 2 : 4;
     switch ((M.N + 15) / 16 * 16) {
         case 80: return launch_int<Ros4Adapter<80>>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
         case 96: return launch_int<Ros4Adapter<96>>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
