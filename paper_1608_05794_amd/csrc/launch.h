@@ -26,7 +26,7 @@ int launch_integrate_lane(int method, const DevMech &M, int64_t n, double *y, in
 
 // wavefront-per-reactor family (k_wave.hip)
 bool wave_supported(const DevMech &M, int method, int precision);
-size_t wave_ws_bytes(const DevMech &M, int cus);   // queue counter + parked LU rows
+size_t wave_ws_bytes(const DevMech &M, int cus);   // queue counter + a parking slice per resident wavefront
 int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *dydt,
                     int cv, hipStream_t s);
 int launch_jac_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac,
@@ -47,7 +47,7 @@ size_t coop_ws_bytes(const DevMech &M, int cus);   // queue counter + parked inv
 int launch_integrate_coop(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
                           int32_t *nrej, hipStream_t s);
-// tile form of the four-wavefront ROS4 (64 < N <= 128): blocked Gauss-Jordan on the matrix cores
+// tile form of the four-wavefront ROS4 (FP64: 112 < N <= 128, FP32-refined: 64 < N): blocked Gauss-Jordan on the matrix cores
 bool tile_supported(const DevMech &M);
 int launch_integrate_tile(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
