@@ -39,14 +39,15 @@ PEAK_FP64_VECTOR = 78.6e12         # FLOP/s, MI355X FP64 vector (VALU)
 # WRITE_SIZE all of them).  Valid only for the default workload and for kernel sources whose hash
 # matches; otherwise the traffic is reported as null.
 TRAFFIC_REF = {
-    "sources": ["paper_1608_05794_amd/csrc/k_wave.hip", "paper_1608_05794_amd/csrc/kinetics.h",
-                "paper_1608_05794_amd/csrc/ck_internal.h", "paper_1608_05794_amd/csrc/launch.h",
-                "paper_1608_05794_amd/csrc/mech.hip"],
-    "sha256": "45bf3512875cebbad468a548f6952454bb4ab27ef01445e2dea2656d3ee155d1",
+    "sources": ["paper_1608_05794_amd/csrc/k_wave.hip", "paper_1608_05794_amd/csrc/wave.h",
+                "paper_1608_05794_amd/csrc/wtile.h", "paper_1608_05794_amd/csrc/reactions.h",
+                "paper_1608_05794_amd/csrc/kinetics.h", "paper_1608_05794_amd/csrc/ck_internal.h",
+                "paper_1608_05794_amd/csrc/launch.h", "paper_1608_05794_amd/csrc/mech.hip"],
+    "sha256": "80414f27af41fda0e80d6735269e1acba0c09d3ef819cdcb9151c6497a493aa7",
     "args": {"mech": "M53", "reactors": 131072, "t_end": 1e-3, "kernel": "wave", "precision": "fp64",
              "launch_steps": 2000},
-    "fetch_kib_per_launch": 7323296.37, "fetch_factor": 1048576.0 / 524302.31,
-    "write_kib_per_launch": 832079207.05, "write_factor": 1.0,
+    "fetch_kib_per_launch": 196553.66, "fetch_factor": 1048576.0 / 524302.31,
+    "write_kib_per_launch": 112193282.53, "write_factor": 1.0,
 }
 TRANSCENDENTAL_FLOPS = 20           # FP64 operations charged per exp / log / log10 / exp10
 
@@ -787,7 +788,8 @@ def main():
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_VECTOR, "traffic": measured_traffic(a),
                      "traffic_unit": "bytes per launch",
                      "kernel": (KERNEL_NAMES[a.kernel].replace("Adapter", "Adapter32").replace("CoopTile", "CoopTile32")
-                                if a.precision != "fp64" else KERNEL_NAMES[a.kernel]),
+                                if a.precision != "fp64" else
+                                KERNEL_NAMES["wave" if a.kernel == "tile" and info["n_species"] < 112 else a.kernel]),
                      "launches": launches,
                      "avg_launch_ms": 1e3 * kernel_s / launches,
                      "flops_per_step_of_batch": flops_launch, "kernel_s": kernel_s,
