@@ -43,7 +43,7 @@ TRAFFIC_REF = {
                 "paper_1608_05794_amd/csrc/wtile.h", "paper_1608_05794_amd/csrc/reactions.h",
                 "paper_1608_05794_amd/csrc/kinetics.h", "paper_1608_05794_amd/csrc/ck_internal.h",
                 "paper_1608_05794_amd/csrc/launch.h", "paper_1608_05794_amd/csrc/mech.hip"],
-    "sha256": "80414f27af41fda0e80d6735269e1acba0c09d3ef819cdcb9151c6497a493aa7",
+    "sha256": "1fa1625098adbb7d05e7741091133b52a76161e0db23c1d463147ffe97789d41",
     "args": {"mech": "M53", "reactors": 131072, "t_end": 1e-3, "kernel": "wave", "precision": "fp64",
              "launch_steps": 2000},
     "fetch_kib_per_launch": 196553.66, "fetch_factor": 1048576.0 / 524302.31,

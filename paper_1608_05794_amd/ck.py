@@ -79,12 +79,11 @@ def _check(rc):
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None      # the argument types make it a pointer
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
 
 
 def _state(y, N):
@@ -161,7 +160,7 @@ class Mechanism:
 def rhs(mech, y, p, out=None, kernel=None, stream=None, reactor="cp"):
     """dy/dt for every reactor (ck_rhs_eval / ck_rhs_eval_ex); y [N, n] float64, p [n]: pressures (Pa)
     for reactor="cp", densities (kg/m^3) for "cv"."""
-    _state(y, mech.N)
+    ld = _state(y, mech.N)
     n = y.shape[1]
     _vec(p, n, y.device, "p")
     if out is None:
@@ -169,9 +168,11 @@ def rhs(mech, y, p, out=None, kernel=None, stream=None, reactor="cp"):
         # so that a fresh compact output matches it
         y = y.contiguous()
         out = torch.empty_like(y)
-    ld = _state(y, mech.N)
-    if out.dtype != torch.float64 or out.device != y.device or out.shape != y.shape or \
-            out.stride(0) != ld or out.stride(1) != 1:
+        ld = y.stride(0)
+        fits = True
+    else:
+        fits = out.dtype == torch.float64 and out.device == y.device and out.shape == y.shape
+    if not fits or out.stride(0) != ld or out.stride(1) != 1:
         raise CkError("output must be a float64 tensor with the state's shape, device and strides")
     if kernel is None and reactor == "cp":
         _check(lib().ck_rhs_eval(mech.handle, n, _ptr(y), ld, _ptr(p), _ptr(out), _stream(stream)))

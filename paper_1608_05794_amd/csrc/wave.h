@@ -21,7 +21,6 @@
 #include "wtile.h"
 
 extern "C" __device__ unsigned long long __ockl_wfred_max_u64(unsigned long long);
-extern "C" __device__ unsigned __ockl_wfred_max_u32(unsigned);
 
 namespace ck {
 namespace {
