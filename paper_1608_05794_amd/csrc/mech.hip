@@ -161,51 +161,89 @@ struct PairUnits {
 // 8.4 cycles for 64 lanes without a conflict, 16.5 / 32 / 129 with 2 / 4 / 16 lanes per bank, 30 for
 // random species).  The cost is the largest bank load, summed over the accesses of a ROS4 step: six
 // per slot to the per-species arrays (four in the Jacobian pass, one in each stage source term) and
-// the d wdot/dC entries of the two column windows of width `win`.
-int bank_cost(const PairUnits *r, int n, int nsp, int win) {
-    auto heaviest = [](const int *bank, int k) {
-        unsigned char load[16] = {0};
-        int m = 0;
-        for (int i = 0; i < k; i++) m = std::max(m, int(++load[bank[i] & 15]));
-        return m;
-    };
-    int cost = 0, bank[16], id[16];
+// the d wdot/dC entries of two column windows of width `win`: those of the wavefront kernels for N <= 56
+// and of the workgroup kernels.  (The one-wavefront ROS4 for 64 < N <= 112 stages three or four windows of
+// 32 columns, for which this order is not the best one.)
+//
+// One load is sixteen counters in a vector, so that an exchange of one reaction is two additions per
+// access and the maxima of sixteen accesses are taken together.
+typedef uint8_t BankLoad __attribute__((vector_size(16)));
+constexpr int kNoBank = 16;             // no access
+constexpr int kAccesses = 36;           // 0..3: species of slot b; 4 + 16 w + 4 b + a: window w, slot b, row of slot a
+
+struct BankOf {
+    uint8_t at[kAccesses];
+};
+
+BankOf banks_of(const PairUnits &r, int nsp, int win) {
+    BankOf o;
+    std::fill(o.at, o.at + kAccesses, uint8_t(kNoBank));
     for (int b = 0; b < 4; b++) {
-        int k = 0;
-        for (int i = 0; i < n; i++)
-            if (r[i].sp[b] != nsp) bank[k++] = r[i].sp[b];
-        cost += 6 * heaviest(bank, k);
-        for (int w = 0; w < 2; w++) {
-            k = 0;
-            for (int i = 0; i < n; i++) {
-                const int col = r[i].sp[b] + 1;
-                if (r[i].sp[b] != nsp && col / win == w) id[k++] = i;
-            }
-            if (k < 2) {
-                cost += 4 * k;
-                continue;
-            }
-            for (int a = 0; a < 4; a++) {
-                for (int j = 0; j < k; j++) bank[j] = r[id[j]].sp[a] * (win | 1) + r[id[j]].sp[b] + 1 - win * w;
-                cost += heaviest(bank, k);
-            }
-        }
+        if (r.sp[b] == nsp) continue;
+        const int col = r.sp[b] + 1, w = col / win;
+        o.at[b] = uint8_t(r.sp[b] & 15);
+        for (int a = 0; a < 4; a++) o.at[4 + 16 * w + 4 * b + a] = uint8_t((r.sp[a] * (win | 1) + col - win * w) & 15);
     }
-    return cost;
+    return o;
+}
+
+struct LaneGroup {
+    BankLoad load[kAccesses] = {};
+    int cost = 0;
+};
+
+// Both vectors' entries i and i + 8 folded: after four levels one entry of each of sixteen is left.
+BankLoad fold_max(BankLoad a, BankLoad b) {
+    return __builtin_elementwise_max(
+        __builtin_shufflevector(a, b, 0, 16, 1, 17, 2, 18, 3, 19, 4, 20, 5, 21, 6, 22, 7, 23),
+        __builtin_shufflevector(a, b, 8, 24, 9, 25, 10, 26, 11, 27, 12, 28, 13, 29, 14, 30, 15, 31));
+}
+BankLoad fold4(const BankLoad *v) { return fold_max(fold_max(v[0], v[1]), fold_max(v[2], v[3])); }
+int sum_bytes(BankLoad v) {             // entries up to 16: the bytes of half a vector add up to 128
+    uint64_t h[2];
+    std::memcpy(h, &v, sizeof h);
+    return int((h[0] * 0x0101010101010101u) >> 56) + int((h[1] * 0x0101010101010101u) >> 56);
+}
+
+struct OneHot {
+    BankLoad v[kNoBank + 1] = {};
+    OneHot() {
+        for (int i = 0; i < 16; i++) v[i][i] = 1;
+    }
+};
+
+// Group g after reaction `out` has given its lane to `in`.
+void exchange(const LaneGroup &g, const BankOf &out, const BankOf &in, const OneHot &one, LaneGroup &o) {
+    for (int i = 0; i < kAccesses; i++) o.load[i] = g.load[i] - one.v[out.at[i]] + one.v[in.at[i]];
+    const BankLoad s = fold4(o.load);   // four accesses, each of whose maxima ends up in four entries
+    o.cost = 6 * (sum_bytes(fold_max(fold_max(s, s), fold_max(s, s))) / 4);
+    for (int w = 0; w < 2; w++) {
+        const BankLoad *x = o.load + 4 + 16 * w;
+        o.cost += sum_bytes(fold_max(fold_max(fold4(x), fold4(x + 4)), fold_max(fold4(x + 8), fold4(x + 12))));
+    }
 }
 
 // Rearranges pair-form reactions over the lanes (within their type, so that the leading blocks keep
 // the fall-off reactions) and the two species of a side over their slots, to keep the lanes of a
 // group apart in the LDS banks: first-improvement descent over random exchanges, 60 per reaction
-// (M53: largest bank load 3.1 -> 2.0 per species access, 2.1 -> 1.6 per Jacobian entry; 30 ms, once
-// per loaded mechanism).
+// (M53: largest bank load 3.1 -> 2.0 per species access, 2.1 -> 1.6 per Jacobian entry).  Once per
+// loaded mechanism, linear in the reactions: 325 of them 1.3 ms, 784 3.4 ms (24 and 77 ms while every
+// exchange counted its groups anew).
 void spread_over_banks(std::vector<PairUnits> &v, int nsp) {
     const int n = int(v.size()), N = nsp + 1;
     if (n < 2) return;
     const int win = N > 64 ? (N + 15) / 16 * 8 : (N > 32 ? 32 : (N + 15) / 16 * 16);
-    auto count = [&](int g) { return std::min(16, n - 16 * g); };
-    std::vector<int> cost((n + 15) / 16);
-    for (size_t g = 0; g < cost.size(); g++) cost[g] = bank_cost(&v[16 * g], count(int(g)), nsp, win);
+    const OneHot one;
+    BankOf none;
+    std::fill(none.at, none.at + kAccesses, uint8_t(kNoBank));
+    std::vector<BankOf> bank(n);
+    std::vector<LaneGroup> group((n + 15) / 16);
+    LaneGroup ti, tj;
+    for (int i = 0; i < n; i++) {
+        bank[i] = banks_of(v[i], nsp, win);
+        LaneGroup &g = group[i / 16];
+        exchange(g, none, bank[i], one, g);
+    }
     uint32_t seed = 12345;
     auto draw = [&](int m) {
         seed = seed * 1664525u + 1013904223u;
@@ -217,19 +255,24 @@ void spread_over_banks(std::vector<PairUnits> &v, int nsp) {
             int &a = v[i].sp[2 * kind], &b = v[i].sp[2 * kind + 1];
             if (a == b || b == nsp) continue;
             std::swap(a, b);
-            const int c = bank_cost(&v[16 * gi], count(gi), nsp, win);
-            if (c <= cost[gi]) cost[gi] = c;
-            else std::swap(a, b);
+            const BankOf turned = banks_of(v[i], nsp, win);
+            exchange(group[gi], bank[i], turned, one, ti);
+            if (ti.cost <= group[gi].cost) {
+                group[gi] = ti;
+                bank[i] = turned;
+            } else {
+                std::swap(a, b);
+            }
         } else {
             const int j = draw(n), gj = j / 16;
             if (gi == gj || v[i].type != v[j].type) continue;
-            std::swap(v[i], v[j]);
-            const int ci = bank_cost(&v[16 * gi], count(gi), nsp, win), cj = bank_cost(&v[16 * gj], count(gj), nsp, win);
-            if (ci + cj <= cost[gi] + cost[gj]) {
-                cost[gi] = ci;
-                cost[gj] = cj;
-            } else {
+            exchange(group[gi], bank[i], bank[j], one, ti);
+            exchange(group[gj], bank[j], bank[i], one, tj);
+            if (ti.cost + tj.cost <= group[gi].cost + group[gj].cost) {
+                group[gi] = ti;
+                group[gj] = tj;
                 std::swap(v[i], v[j]);
+                std::swap(bank[i], bank[j]);
             }
         }
     }
