@@ -31,7 +31,7 @@ struct RxnRec {
     int sp[3];                  // species of slots 0..5, two 16-bit indices per int (reactants first)
     int nu;                     // stoichiometric coefficient of slot s in bits 2s..2s+1 (1..3)
     int fall;                   // index into the fall-off table, or -1
-    int pad;
+    int blk_slots;              // largest slot count among the general-form reactions of this one's block of 64
 };
 
 struct FallRec {                // fall-off parameters (Lindemann / Troe)

@@ -308,10 +308,12 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     // kernels hand consecutive blocks of 64 reactions to the lanes of a wavefront, and a block pays
     // for the most complex type it holds, so the few third-body and fall-off reactions share the
     // leading blocks and the ragged last block holds elementary ones only.  Within a type the lanes
-    // of pair-form reactions are chosen by their LDS banks.
+    // of pair-form reactions are chosen by their LDS banks, and general reactions with few species go
+    // first (a block of 64 can skip the slots that none of its reactions uses).
     std::vector<int> order(nr);
     std::iota(order.begin(), order.end(), 0);
     auto units = [](const std::vector<int> &nu) { return std::accumulate(nu.begin(), nu.end(), 0); };
+    auto slots = [&](int i) { return hm.rx[i].rsp.size() + hm.rx[i].psp.size(); };
     auto pair_form = [&](int i) {
         const auto &x = hm.rx[i];
         const int r = units(x.rnu), p = units(x.pnu);
@@ -319,7 +321,8 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         if (pair_form(a) != pair_form(b)) return !pair_form(a);
-        return hm.rx[a].type > hm.rx[b].type;
+        if (hm.rx[a].type != hm.rx[b].type) return hm.rx[a].type > hm.rx[b].type;
+        return !pair_form(a) && slots(a) < slots(b);
     });
     int n_gen = 0, n_fall = 0;
     for (int i = 0; i < nr; i++) {
@@ -427,6 +430,12 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
             E.sp = e.first;
             eff.push_back(E);
         }
+    }
+    for (int b0 = 0; b0 < n_gen; b0 += 64) {
+        const int b1 = std::min(n_gen, b0 + 64);
+        int most = 0;
+        for (int i = b0; i < b1; i++) most = std::max(most, rx_nslot(rx[i].meta));
+        for (int i = b0; i < b1; i++) rx[i].blk_slots = most;
     }
     if (fall.empty()) fall.resize(1);
     if (eff.empty()) eff.resize(1);

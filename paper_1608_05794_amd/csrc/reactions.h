@@ -250,7 +250,11 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
 }
 
 // Reactions of any form: up to three species per side with coefficients 1..3, irreversible ones.
-template <int T, bool JAC>
+// BOUND: slots that no reaction of the wavefront's block uses are skipped by scalar branches, which
+// takes 22 registers off a Jacobian pass and lets another wavefront reside (N = 32, 155 reactions, a
+// third of them general, 30000 Jacobians: 351 us with, 426 us without).  The source term is better off
+// without the branches (N = 32 as above: 98 us with, 93 us without).
+template <int T, bool JAC, bool BOUND>
 __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                                   const RxScale &sc, int c0, int win, RxMode mode, double *keep,
                                                   int tid) {
@@ -259,8 +263,9 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
     auto Hg = [&](int k) { return A.H[k]; };
     for (int i = tid; i < M.n_gen; i += T) {
         const RxnRec R = M.rx[i];
+        const int nmax = BOUND ? __builtin_amdgcn_readfirstlane(R.blk_slots) : kMaxSlots;
         Slots S;
-        load_slots(R, Cg, S, kMaxSlots);
+        load_slots(R, Cg, S, nmax);
         double ckf, ckr, rdm;
         if (JAC && mode == kScatterKept) {
             ckf = keep[0];
@@ -268,7 +273,7 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
             rdm = keep[2 * T];
         } else {
             Rate q;
-            reaction_rate<JAC>(M, R, S, kMaxSlots, t, Ctot, Cg, Gg, Hg, q);
+            reaction_rate<JAC>(M, R, S, nmax, t, Ctot, Cg, Gg, Hg, q);
             const double Rn = q.kf * q.pf - q.kr * q.pr;
             ckf = q.c * q.kf;
             ckr = q.c * q.kr;
@@ -280,6 +285,7 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
                     double of = 0.0, orr = 0.0;
 #pragma unroll
                     for (int s = 0; s < kMaxSlots; s++) {
+                        if (s >= nmax) break;
                         of += S.sgn[s] < 0 ? double(S.nu[s]) : 0.0;
                         orr += S.sgn[s] > 0 ? double(S.nu[s]) : 0.0;
                         shx += S.sgn[s] != 0 ? (S.sgn[s] * S.nu[s]) * (Hg(S.sp[s]) + sc.dh) : 0.0;
@@ -291,13 +297,14 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
                 }
 #pragma unroll
                 for (int s = 0; s < kMaxSlots; s++) {
+                    if (s >= nmax) break;
                     if (S.sgn[s] == 0) continue;
                     const double v = S.sgn[s] * S.nu[s];
                     atomicAdd(&A.WD[S.sp[s]], v * qi);
                     if (JAC) {
                         atomicAdd(&A.DWT[S.sp[s]], v * vT);
                         atomicAdd(&A.TB[S.sp[s]], v * vB);
-                        const double d = dprod_slot(S, s, kMaxSlots);
+                        const double d = dprod_slot(S, s, nmax);
                         atomicAdd(&A.HC[S.sp[s]], (S.sgn[s] < 0 ? ckf * d : -ckr * d) * shx);
                     }
                 }
@@ -317,13 +324,16 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
                 const int col = sp - c0;
                 if (unsigned(col) >= unsigned(win)) return;
 #pragma unroll
-                for (int a = 0; a < kMaxSlots; a++)
+                for (int a = 0; a < kMaxSlots; a++) {
+                    if (a >= nmax) break;
                     if (S.sgn[a] != 0) atomicAdd(&A.JC[S.sp[a] * A.ldj + col], (S.sgn[a] * S.nu[a]) * dq);
+                }
             };
 #pragma unroll
             for (int b = 0; b < kMaxSlots; b++) {
+                if (b >= nmax) break;
                 if (S.sgn[b] == 0) continue;
-                const double d = dprod_slot(S, b, kMaxSlots);
+                const double d = dprod_slot(S, b, nmax);
                 column(S.sp[b], S.sgn[b] < 0 ? ckf * d : -ckr * d);
             }
             if (rdm != 0.0) {
@@ -337,13 +347,13 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
 
 // Every reaction of the mechanism.  Window: columns [c0, c0 + win) of JC, win already cut to the
 // species count.  first: first_pair(M, tid).  The caller synchronises before and after.  GEN = false
-// leaves the general form out (the caller knows that the mechanism has none).
-template <int T, bool JAC, bool GEN = true>
+// leaves the general form out (the caller knows that the mechanism has none); BOUND: general_reactions.
+template <int T, bool JAC, bool GEN = true, bool BOUND = (T > 64)>
 __device__ __forceinline__ void reaction_pass(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                               const RxScale &sc, int c0, int win, RxMode mode, double *keep,
                                               int tid, const PairRec &first) {
     if (GEN && M.n_gen > 0) {
-        general_reactions<T, JAC>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
+        general_reactions<T, JAC, BOUND>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
         if (JAC && (mode == kRatesKeep || mode == kScatterKept)) keep += 3 * T * ((M.n_gen + T - 1) / T);
     }
     if (JAC && mode == kScatterKept) pair_scatter<T>(M, A, c0, win, keep, tid);
