@@ -38,25 +38,34 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
     }
 }
 
-// Standalone Jacobian for N <= 64: workgroups of eight wavefronts, one reactor each, d wdot/dC staged
-// in windows of WIN matrix columns (the temperature column is column 0).  Bound by the stores: an entry
-// of a reactor is eight bytes of a line that it shares with fifteen neighbours, so the eight staged
-// windows are written out together, eight neighbouring reactors by one store (64 bytes), instead of
-// one reactor at a time (a line per lane): M53 x 8192 380 -> 140 us.  Rates are evaluated again for a later window.
-template <int NSMAX, int WIN>
+// Standalone Jacobian for N <= 64: workgroups of one or eight wavefronts, one reactor each, d wdot/dC
+// staged in windows of WIN matrix columns (the temperature column is column 0).
+//
+// Eight: bound by the stores: an entry of a reactor is eight bytes of a line that it shares with fifteen
+// neighbours, so the eight staged windows are written out together, eight neighbouring reactors by one
+// store (64 bytes), instead of one reactor at a time (a line per lane): M53 x 8192 233 -> 155 us.  The
+// windows of eight reactors fill a CU's LDS, so rates are evaluated again for a later window.
+//
+// One: the whole matrix in one window.  A call on few reactors is a latency: here every reactor has a
+// SIMD to itself and its rates are evaluated once (M53 x 64 45 us with eight, 31 us with one; N = 64
+// 56 and 28 us).  launch_jac_wave has the rule.
+template <int NSMAX, int WIN, int RW>
 struct JacShape {
-    static constexpr int R = 8;                     // reactors of a workgroup
+    static constexpr int R = RW;                    // reactors of a workgroup
     static constexpr int LDJ = WIN | 1;
     static constexpr int NWIN = (NSMAX + 1 + WIN - 1) / WIN;
     static constexpr int kSlab0 = 8 * (NSMAX + 1) + (NSMAX + 1) * LDJ;
     // slab stride 8 modulo 32 doubles: the eight reactors of a store read different banks
-    static constexpr int kSlab = kSlab0 + (8 - kSlab0 % 32 + 32) % 32;
+    static constexpr int kSlab = R == 1 ? kSlab0 : kSlab0 + (8 - kSlab0 % 32 + 32) % 32;
     static constexpr size_t kLds = size_t(R) * kSlab + 2 * (NSMAX + 1);
+    // general reactions: where more wavefronts than two a SIMD fit the LDS, registers limit them
+    static constexpr bool BOUND = R == 1 && NSMAX < 32;
 };
-template <int NSMAX, int WIN>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) jac_wave_kernel(DevMech M, int64_t n, const double *y,
-                                                       int64_t ld, const double *p, double *jac, int cv) {
-    using SH = JacShape<NSMAX, WIN>;
+// WPE: resident wavefronts per SIMD that the registers have to allow
+template <int NSMAX, int WIN, int RW, int WPE>
+__global__ void __launch_bounds__(64 * RW) __attribute__((amdgpu_waves_per_eu(WPE, 4)))
+jac_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld, const double *p, double *jac, int cv) {
+    using SH = JacShape<NSMAX, WIN, RW>;
     extern __shared__ double lds_raw[];
     const int N = M.N, ns = M.nsp, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int64_t r0 = xcd_reactor(blockIdx.x, int64_t(gridDim.x)) * SH::R;
@@ -79,7 +88,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))
     L.ldj = SH::LDJ;
     L.cv = cv;
     init_lds<1>(M, L, kLdsRhs);
-    for (int e = int(threadIdx.x); e < N; e += 512) {
+    for (int e = int(threadIdx.x); e < N; e += 64 * SH::R) {
         W[e] = e == 0 ? 1.0 : M.W()[e - 1];
         IW[e] = e == 0 ? 1.0 : M.invW()[e - 1];
     }
@@ -92,7 +101,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))
     zero_jc(L, ns);
     species_pass<1, true>(M, yy, p[r], L, x);
     const RxScale sc = rx_scale<1>(L, x);
-    reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, -1, min(WIN, N), kRates, nullptr, lane, first);
+    reaction_pass<64, true, true, SH::BOUND>(M, L, x.t, x.Ctot, sc, -1, min(WIN, N), kRates, nullptr, lane, first);
     __syncthreads();
     finish_rhs<1>(M, L, x, ff);
     const Chain<1> c = chain_rule<1>(M, L, x, yy, bcast(ff[0], 0));
@@ -111,15 +120,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))
             zero_jc(L, ns);
             __syncthreads();
             const PairRec again = first_pair<64>(M, lane);
-            reaction_pass<64, true>(M, L, x.t, x.Ctot, sc, w * WIN - 1, min(WIN, N - w * WIN), kScatter, nullptr, lane,
-                                    again);
+            reaction_pass<64, true, true, SH::BOUND>(M, L, x.t, x.Ctot, sc, w * WIN - 1, min(WIN, N - w * WIN), kScatter,
+                                                     nullptr, lane, again);
         }
         __syncthreads();
-        const int s = int(threadIdx.x) & 7;
+        const int s = int(threadIdx.x) % SH::R;
         const double *slab = lds_raw + s * SH::kSlab;
         const int cols = min(WIN, N - w * WIN);
         if (r0 + s < n)
-            for (int e = int(threadIdx.x) >> 3; e < N * WIN; e += 64) {
+            for (int e = int(threadIdx.x) / SH::R; e < N * WIN; e += 64) {
                 const int i = e / WIN, jj = e % WIN, j = w * WIN + jj;
                 if (jj >= cols) continue;
                 double v;
@@ -140,18 +149,18 @@ int pad_np(int N) { return ((N + 7) / 8) * 8; }
 }  // namespace
 
 namespace {
-template <int NSMAX, int WIN>
+template <int NSMAX, int WIN, int RW, int WPE>
 int launch_jac(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac, int cv,
                hipStream_t s) {
-    using SH = JacShape<NSMAX, WIN>;
+    using SH = JacShape<NSMAX, WIN, RW>;
     if (M.nsp > NSMAX) return CK_EUNSUPPORTED;
     const size_t lds = SH::kLds * sizeof(double);
-    auto kern = jac_wave_kernel<NSMAX, WIN>;
+    auto kern = jac_wave_kernel<NSMAX, WIN, RW, WPE>;
     if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
         return CK_EHIP;
     const int64_t groups = (n + SH::R - 1) / SH::R;
-    kern<<<dim3(unsigned((groups + 7) / 8 * 8)), dim3(512), lds, s>>>(M, n, y, ld, p, jac, cv);
+    kern<<<dim3(unsigned((groups + 7) / 8 * 8)), dim3(64 * RW), lds, s>>>(M, n, y, ld, p, jac, cv);
     return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
 }
 }  // namespace
@@ -182,10 +191,32 @@ int launch_rhs_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, co
 int launch_jac_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, const double *p, double *jac,
                     int cv, hipStream_t s) {
     if (M.N > 64) return cv ? CK_EUNSUPPORTED : launch_jac_coop(M, n, y, ld, p, jac, s);
-    if (M.N <= 16) return launch_jac<15, 16>(M, n, y, ld, p, jac, cv, s);
-    if (M.N <= 32) return launch_jac<31, 32>(M, n, y, ld, p, jac, cv, s);
-    if (M.N <= 56) return launch_jac<55, 32>(M, n, y, ld, p, jac, cv, s);
-    return launch_jac<63, 24>(M, n, y, ld, p, jac, cv, s);      // eight windows of 32 columns exceed the LDS
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return CK_EHIP;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return CK_EHIP;
+    // One reactor a workgroup while all of them are resident at once, one a SIMD: M53 x 1024 42 us (eight:
+    // 48), x 1536 68 us (49).  With N <= 16 a matrix is small enough for that at any size (M13 x 30000 92 us,
+    // 130 with eight).  With general reactions, whose registers keep eight-reactor workgroups to one a CU,
+    // it pays again when those need more than two rounds (N = 32, a third of 155 reactions general:
+    // x 4096 78 us, 73 with eight; x 30000 348 us, 435).
+    const int64_t few = 4 * int64_t(cus);
+    const bool general = M.n_gen > 0;
+    if (M.N <= 16) {
+        // the general pass takes spills for a fourth wavefront once three do not hold the batch (N = 14,
+        // all 65 reactions general: x 2048 41 us, 37 with three; x 30000 235 us, 256)
+        if (general && n > 3 * few) return launch_jac<15, 16, 1, 4>(M, n, y, ld, p, jac, cv, s);
+        return launch_jac<15, 16, 1, 3>(M, n, y, ld, p, jac, cv, s);
+    }
+    if (M.N <= 32) {
+        if (n <= few || (general && n > 4 * few)) return launch_jac<31, 32, 1, 3>(M, n, y, ld, p, jac, cv, s);
+        return launch_jac<31, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
+    }
+    if (M.N <= 56) {
+        if (n <= few) return launch_jac<55, 56, 1, 1>(M, n, y, ld, p, jac, cv, s);
+        return launch_jac<55, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
+    }
+    if (n <= few) return launch_jac<63, 64, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    return launch_jac<63, 24, 8, 2>(M, n, y, ld, p, jac, cv, s);      // eight windows of 32 columns exceed the LDS
 }
 
 int launch_integrate_wave(int method, const DevMech &M, int64_t n, double *y, int64_t ld, const double *p,
