@@ -1374,10 +1374,22 @@ int launch(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, 
                                                                          status, nacc, nrej, s);
 }
 
+// Half-row form.  Up to 104 rows two workgroups fit a CU by themselves.  The registers of 112 and 120 rows
+// pass 256 by a few; a build held to 256 spills them and is the better one once a CU has a second reactor to
+// take (M111 x 1024, 10 steps: 6.1 ms with two workgroups a CU, 8.8 ms with one), the other one before
+// (M111 x 64: 2.2 ms, 2.8 ms held to 256).  128 rows leave LDS for one workgroup.
 template <int NP>
 int launch_half(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end, double *t,
                 double *h, const IntOpts &o, unsigned *queue, int32_t *status, int32_t *nacc, int32_t *nrej,
                 hipStream_t s) {
+    if constexpr (NP == 112 || NP == 120) {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return CK_EHIP;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return CK_EHIP;
+        if (n > cus && o.blocks_per_cu != 1)
+            return launch_kernel<4, Ros4CoopHalf<NP>, NP / 2, true, 2>(M, n, y, ld, p, t_end, t, h, o, queue, status,
+                                                                       nacc, nrej, s);
+    }
     return launch_kernel<4, Ros4CoopHalf<NP>, NP / 2, true>(M, n, y, ld, p, t_end, t, h, o, queue, status, nacc,
                                                             nrej, s);
 }

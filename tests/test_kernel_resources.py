@@ -60,7 +60,7 @@ def kernels():
     return _kernels(ck.LIB_PATH)
 
 
-@pytest.mark.parametrize("np", [72, 80, 88, 96, 104])
+@pytest.mark.parametrize("np", [72, 80, 88, 96, 104, 112, 120])
 def test_two_half_row_workgroups_per_cu(kernels, np):
     fit = [k[".vgpr_count"] for name, k in kernels.items() if f"Ros4CoopHalfILi{np}E" in name]
     print(np, fit)
