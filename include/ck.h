@@ -72,8 +72,11 @@ enum {
                               and a blocked Gauss-Jordan inverse (panels of 16 columns, partial
                               pivoting) whose rank-16 updates run on the FP64 matrix cores (MFMA).
                               FP64 with N <= 112: the whole matrix in one wavefront, results bitwise
-                              identical between runs; otherwise the four-wavefront workgroup, to
-                              which the summation caveat of GROUP applies */
+                              identical between runs, except that calls on at most two reactors per
+                              compute unit take the four-wavefront workgroup where that is quicker
+                              (N > 96, or reactions that are irreversible or have more than two units a
+                              side).  The workgroup (also for N > 112 and the refined precision) has the
+                              summation caveat of GROUP */
 };
 
 /* Reactor form (Section 3).  Constant pressure: p[] holds pressures (Pa); the density follows
@@ -223,7 +226,7 @@ int ck_integrate_rkf45(const ck_mech *m, int64_t n, double *y, int64_t ld, const
  *   replays  optional out: graph replays run.
  *   workspace  device buffer of ck_graph_workspace_bytes(), or NULL (library-owned, per stream).
  * Synchronous: returns after the last replay has completed.  Results equal those of the same
- * launches issued one by one (bitwise for every kernel but CK_KERNEL_GROUP at N > 64).
+ * launches issued one by one (bitwise for every kernel but the four-wavefront workgroups at N > 64).
  * launch_steps >= 1, 1 <= launches_per_graph <= 64.
  */
 int ck_integrate_graph(const ck_mech *m, int32_t method, int64_t n, double *y, int64_t ld, const double *p,

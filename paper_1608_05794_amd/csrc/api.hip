@@ -147,7 +147,7 @@ int integrate(int method, const ck_mech *mc, int64_t n, double *y, int64_t ld, c
         return launch_integrate_wave(method, m->dev, n, y, ld, p, t_end, t, h, io, ws, status, nacc, nrej, s);
     if (kern == CK_KERNEL_GROUP)
         return launch_integrate_coop(m->dev, n, y, ld, p, t_end, t, h, io, ws, status, nacc, nrej, s);
-    if (kern == CK_KERNEL_GROUP_TILE && io.precision == CK_PREC_FP64 && wide_supported(m->dev))
+    if (kern == CK_KERNEL_GROUP_TILE && io.precision == CK_PREC_FP64 && wide_preferred(m->dev, n, io))
         return launch_integrate_wide(m->dev, n, y, ld, p, t_end, t, h, io, ws, status, nacc, nrej, s);
     if (kern == CK_KERNEL_GROUP_TILE)
         return launch_integrate_tile(m->dev, n, y, ld, p, t_end, t, h, io, ws, status, nacc, nrej, s);

@@ -1428,9 +1428,13 @@ int launch_integrate_tile(const DevMech &M, int64_t n, double *y, int64_t ld, co
             default: return CK_EUNSUPPORTED;
         }
     }
-    // FP64: N <= 112 fits one wavefront (launch_integrate_wide)
-    if (M.N <= 112) return CK_EUNSUPPORTED;
-    return coop::launch_tile<128>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+    switch (((M.N + 15) / 16) * 16) {
+#define CK_TILE(NPV) \
+    case NPV: return coop::launch_tile<NPV>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+        CK_TILE(80) CK_TILE(96) CK_TILE(112) CK_TILE(128)
+#undef CK_TILE
+        default: return CK_EUNSUPPORTED;
+    }
 }
 
 namespace coop {

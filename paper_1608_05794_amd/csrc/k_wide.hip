@@ -10,7 +10,20 @@
 
 namespace ck {
 
-bool wide_supported(const DevMech &M) { return M.N > 64 && M.N <= 112; }
+// Few reactors are a latency, which four wavefronts on one reactor make shorter: as long as their
+// workgroups are all resident at once (two a CU) they finish first where a step is long for one wavefront,
+// that is with more than 96 rows (M111 x 256, 20 steps: 2.3 ms, one wavefront 3.4) or with general
+// reactions (N = 96, all of 475 general, x 256: 2.2 and 4.3 ms).  Beyond two a CU one wavefront a reactor
+// is ahead (M111 x 768: 5.0 and 3.6 ms), with up to 96 rows and pair-form reactions it was never behind.
+bool wide_preferred(const DevMech &M, int64_t n, const IntOpts &o) {
+    if (M.N <= 64 || M.N > 112) return false;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return true;
+    const int64_t resident = int64_t(cus) * (o.blocks_per_cu == 1 ? 1 : 2);
+    return n > resident || (M.N <= 96 && M.n_gen == 0);
+}
 
 int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &opts, void *ws, int32_t *status, int32_t *nacc,

@@ -36,7 +36,7 @@ int launch_integrate_wave(int method, const DevMech &M, int64_t n, double *y, in
                           int32_t *status, int32_t *nacc, int32_t *nrej, hipStream_t s);
 
 // one wavefront per reactor for larger states (k_wide.hip): FP64 ROS4, constant pressure
-bool wide_supported(const DevMech &M);
+bool wide_preferred(const DevMech &M, int64_t n, const IntOpts &o);     // rather than the four-wavefront tile form
 int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
                           int32_t *nrej, hipStream_t s);
@@ -47,7 +47,7 @@ size_t coop_ws_bytes(const DevMech &M, int cus);   // queue counter + parked inv
 int launch_integrate_coop(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
                           int32_t *nrej, hipStream_t s);
-// tile form of the four-wavefront ROS4 (FP64: 112 < N <= 128, FP32-refined: 64 < N): blocked Gauss-Jordan on the matrix cores
+// tile form of the four-wavefront ROS4 (64 < N <= 128): blocked Gauss-Jordan on the matrix cores
 bool tile_supported(const DevMech &M);
 int launch_integrate_tile(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,

@@ -64,3 +64,44 @@ def test_jacobian_of_one_reactor_is_quicker(tmp_path):
     one, many = medians([lambda: ck.jac(g, y1, P1), lambda: ck.jac(g, y, P)])
     print(f"N = 64: one reactor {1e3 * one:.1f} us, 2048 reactors {1e3 * many:.1f} us", flush=True)
     assert one <= 0.8 * many
+
+
+# sizes at the edges of the tile forms; n_gen > 0 for the mixed ones
+@pytest.mark.parametrize("nsp,forms", [(64, "mixed"), (79, "mixed"), (80, "all"), (95, "mixed"), (96, "pair"), (111, "pair")])
+def test_ros4_tile_forms(tmp_path, nsp, forms):
+    """Two reactors per compute unit (one workgroup each) and three more (one wavefront each): both within
+    the shape tests' 1e-6 of the oracle, in T and in the solver's weights, after eight fixed steps."""
+    from oracle import oracle as O
+
+    from .parity_util import state_rel_error, weighted_error
+    edge = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    ck, g, y, P = setup(tmp_path, nsp, forms, edge + 3)
+    om = O.Mechanism(str(tmp_path / "m.ckm"))
+    k = 9
+    y0, P0 = y[:, :k].cpu().numpy(), P[:k].cpu().numpy()
+    for h in 10.0 ** np.arange(-8, -20, -1):
+        o = om.integrate(y0, P0, 8 * h, "ros4", h_fixed=h)
+        if np.all(np.isfinite(o["y"])) and np.abs(o["y"][0] - y0[0]).max() < 100.0:
+            break
+    for n in (k, edge, edge + 3):
+        r = ck.integrate(g, y[:, :n].contiguous(), P[:n].contiguous(), 8 * h, kernel="tile", h_fixed=h)
+        a = r["y"][:, :k].cpu().numpy()
+        eT, ew = state_rel_error(a, o["y"])[0], weighted_error(a, o["y"])
+        print(f"{nsp} {forms} x {n}: T {eT:.1e} weighted {ew:.1e}", flush=True)
+        assert (r["status"][:k].cpu().numpy() == 0).all() and eT <= 1e-6 and ew <= 1e-6
+
+
+@pytest.mark.parametrize("nsp,forms", [(111, "pair"), (95, "all")])
+def test_ros4_of_few_reactors_is_quicker(tmp_path, nsp, forms):
+    """Nine reactors against four per compute unit, one round of the one-wavefront form.  With that form for
+    both the times are 0.93 of each other (measured at N = 96 and 112); with a workgroup for each of the nine
+    0.63 and 0.5.  The calls alternate, bound 0.8."""
+    ck, g, y, P = setup(tmp_path, nsp, forms, 4 * torch.cuda.get_device_properties(0).multi_processor_count)
+    y9, P9 = y[:, :9].contiguous(), P[:9].contiguous()
+
+    def call(y, p):
+        return lambda: ck.integrate(g, y, p, 8e-14, kernel="tile", h_fixed=1e-14)
+
+    few, many = medians([call(y9, P9), call(y, P)], 11)
+    print(f"{nsp} {forms}: nine reactors {few:.3f} ms, {y.shape[1]} reactors {many:.3f} ms", flush=True)
+    assert few <= 0.8 * many
