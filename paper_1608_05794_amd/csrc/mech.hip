@@ -351,14 +351,17 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
     std::vector<FallRec> fall;
     std::vector<EffRec> eff;
     std::vector<int> orig(std::max(nr, 1));
+    // Rate parameters within the range of the kernels' exp: a rate constant with |E| / R beyond 2e14 K or
+    // |beta| beyond 2e11 is 0 or inf at every temperature from 1 K to 1e11 K, and stays that with the bound.
+    auto bound = [](double v, double b) { return std::min(std::max(v, -b), b); };
     for (int ii = 0; ii < nr; ii++) {
         const auto &x = hm.rx[order[ii]];
         RxnRec &R = rx[ii];
         std::memset(&R, 0, sizeof(R));
         orig[ii] = order[ii];
         R.lnA = std::log(x.A);
-        R.beta = x.beta;
-        R.EaR = x.Ea / hm.R;
+        R.beta = bound(x.beta, 2e11);
+        R.EaR = bound(x.Ea / hm.R, 2e14);
         int s = 0, nu = 0, sp[6] = {0, 0, 0, 0, 0, 0};
         double d = 0;
         for (size_t j = 0; j < x.rsp.size(); j++, s++) {
@@ -381,13 +384,11 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
         if (x.type >= 2) {
             FallRec F{};
             F.lnA0 = std::log(x.A0);
-            F.beta0 = x.beta0;
-            F.Ea0R = x.Ea0 / hm.R;
+            F.beta0 = bound(x.beta0, 2e11);
+            F.Ea0R = bound(x.Ea0 / hm.R, 2e14);
             if (x.type == 3) {
                 F.a = x.ta;
-                // exp(-T / T***) and its like are 0 (or inf) long before these bounds, which keep the
-                // arguments within the range of the kernels' exp
-                auto bound = [](double v, double b) { return std::min(std::max(v, -b), b); };
+                // exp(-T / T***) and its like are 0 (or inf) long before these bounds
                 F.invT3 = bound(1.0 / x.T3, 1e10);
                 F.invT1 = bound(1.0 / x.T1, 1e10);
                 F.T2 = bound(x.T2, 1e12);
