@@ -193,7 +193,9 @@ __device__ __forceinline__ void rate_factor(const FactorIn &F, const TPow &t, do
         const double nn = 0.75 - 1.27 * L;
         const double x = fma(kLog10e, ck_log(fmax(Pr, 1e-300)), cc);
         const double d = nn - 0.14 * x;
-        const double id = ck_rcp(d != 0.0 ? d : 1e-150);     // d = 0: f1 beyond any bound, F = 1
+        // d = 0: f1 beyond any bound and F = 1; any other d is unchanged (a select instead: Jacobian M53 x 8192
+        // 142.3 us, 139.7 with the addition)
+        const double id = ck_rcp(d + 0x1p-500);
         const double f1 = x * id;
         const double iu = ck_rcp(fma(f1, f1, 1.0));
         Fb = ck_exp(kLn10 * L * iu);
