@@ -357,7 +357,7 @@ def suite_batching(a):
 
 def suite_precision(a):
     """FP32 factorisation with FP64 refinement against the all-FP64 solver, at 53 species (wavefront
-    kernel, FP32 LU) and 111 species (tile workgroup kernel, FP32 matrix-core Gauss-Jordan): step
+    kernel, FP32 inverse in matrix-core tiles) and 111 species (tile workgroup kernel, FP32 matrix-core Gauss-Jordan): step
     counts, FP64 refactorings (steps whose refinement stagnated), the largest relative differences of
     T and Y (Y > 1e-12) between the two over the batch, and throughput."""
     import torch

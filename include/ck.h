@@ -175,11 +175,11 @@ int ck_jacobian_eval(const ck_mech *m, int64_t n, const double *y, int64_t ld, c
  * the mechanism is called on, kept (and grown when a call needs more, which
  * waits for the device) until ck_mechanism_free.
  * Lane kernel: per-reactor scratch, linear in n.  Wavefront kernel: a
- * 256-byte queue counter, plus for 32 < N' <= 64 (N' = N rounded up to a
- * multiple of 8) a parking slice of 64 N' doubles per resident wavefront (8
- * per compute unit of the mechanism's device).  Workgroup kernel with N > 64:
- * the counter plus a parking slice of 128 N' doubles per resident workgroup
- * (2 per compute unit).  Independent of n except for the lane kernel.
+ * 256-byte queue counter, plus for N <= 64 a slice of 64 N' doubles (N' = N
+ * rounded up to a multiple of 8) for each of 8 wavefronts per compute unit of
+ * the mechanism's device.  Workgroup and tile kernels with N > 64: the counter
+ * plus 2 slices of 128 N' doubles (N' = N rounded up to a multiple of 16) per
+ * compute unit.  Independent of n except for the lane kernel.
  * Returns 0 on a device query error.
  */
 size_t ck_workspace_bytes(const ck_mech *m, int64_t n, const ck_opts *o);

@@ -1,6 +1,6 @@
 // C-ABI entry points: argument validation, workspace management and kernel
 // selection.  Every compute step runs in the kernels of k_lane.hip,
-// k_wave.hip and k_coop.hip.
+// k_wave.hip, k_wide.hip and k_coop.hip.
 #include <climits>
 #include <cmath>
 

@@ -20,11 +20,10 @@ constexpr int kMaxN = 128;        // largest state size (T + 127 species)
 // wavefront mostly take the same branch.
 enum RxnType { kElementary = 0, kThirdBody = 1, kLindemann = 2, kTroe = 3 };
 
-// One reaction, packed into 64 bytes so a lane fetches it with four 16-byte loads.
+// One reaction in 64 bytes, so that a lane fetches it with 16-byte loads.
 // Reactions are stored sorted by type so lanes of one wavefront mostly share a branch.
-struct RxnRec {
+struct alignas(64) RxnRec {
     double lnA, beta, EaR;      // ln A, temperature exponent, E/R (high-pressure limit for fall-off)
-    double dnu;                 // net mole change sum_j (nu''_j - nu'_j)
     int meta;                   // bits 0-1 type, bit 2 reversible, bits 3-5 slots, bits 6-8 reactant slots,
                                 // bits 9-31 number of third-body efficiencies
     int eff_begin;              // first entry in the efficiency table

@@ -279,7 +279,6 @@ __device__ __forceinline__ Row chain_rule(const DevMech &M, const Lds &L, const 
     const double TBk = valid ? L.TB[k] : 0.0, WDk = valid ? L.WD[k] : 0.0, DWTk = valid ? L.DWT[k] : 0.0;
     ChainIn c;
     c.rho = x.rho;
-    c.invrho = x.invrho;
     c.Wbar = x.Wbar;
     c.invT = x.t.invT;
     c.R = M.R;
@@ -384,45 +383,28 @@ __device__ __forceinline__ double gj_apply(const double (&a)[NP], const Lds &L, 
     return x;
 }
 
-template <int W, int NP, int NWIN, int WIN, bool PARK>
+// One wavefront, one matrix row per lane (N <= 64).
+template <int NP>
 struct Ros4Coop {
     static constexpr double qinv = 0.25;
-    static constexpr size_t kRows = size_t(NP) * 64 * W;   // parked doubles per workgroup
+    static constexpr size_t kRows = 0;      // nothing parked
     static constexpr bool kHalf = false;
     static constexpr size_t kJcMin = 0;
-    // the inverse rows go to the workspace while the stage source terms are evaluated and come
-    // back as one batch of independent loads before the next products
-    __device__ static __forceinline__ void park(const Lds &L, const double (&a)[NP]) {
-        if (!PARK) return;
-        double *r = L.rows + opaque(Grp<W>::tid());
-#pragma unroll
-        for (int j = 0; j < NP; j++) r[j * Grp<W>::T] = a[j];
-    }
-    __device__ static __forceinline__ void unpark(const Lds &L, double (&a)[NP]) {
-        if (!PARK) return;
-        const double *r = L.rows + opaque(Grp<W>::tid());
-#pragma unroll
-        for (int j = 0; j < NP; j++) a[j] = r[j * Grp<W>::T];
-    }
     __device__ static __forceinline__ bool step(const DevMech &M, const Lds &L, double y, double P, double h, double &ynew,
                                 double &e, const IntOpts &, int &) {
         double a[NP];
         double f;
         const double dg = 1.0 / (Ros4::gamma * h);
-        static_assert(W == 1, "larger states take the half-row or the tile form");
         iteration_rows<NP>(M, L, y, P, dg, a, f);
         int ord;
-        const bool ok = gj_invert<W, NP>(a, L, ord);
+        const bool ok = gj_invert<1, NP>(a, L, ord);
         const double ih = 1.0 / h;
-        const double u1 = gj_apply<W, NP>(a, L, ord, f);
-        park(L, a);
-        double ft = rhs<W>(M, L, y + Ros4::a21 * u1, P);
-        unpark(L, a);
-        const double u2 = gj_apply<W, NP>(a, L, ord, ft + (Ros4::c21 * u1) * ih);
-        ft = rhs<W>(M, L, y + Ros4::a31 * u1 + Ros4::a32 * u2, P);
-        unpark(L, a);
-        const double u3 = gj_apply<W, NP>(a, L, ord, ft + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih);
-        const double u4 = gj_apply<W, NP>(a, L, ord, ft + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih);
+        const double u1 = gj_apply<1, NP>(a, L, ord, f);
+        double ft = rhs<1>(M, L, y + Ros4::a21 * u1, P);
+        const double u2 = gj_apply<1, NP>(a, L, ord, ft + (Ros4::c21 * u1) * ih);
+        ft = rhs<1>(M, L, y + Ros4::a31 * u1 + Ros4::a32 * u2, P);
+        const double u3 = gj_apply<1, NP>(a, L, ord, ft + (Ros4::c31 * u1 + Ros4::c32 * u2) * ih);
+        const double u4 = gj_apply<1, NP>(a, L, ord, ft + (Ros4::c41 * u1 + Ros4::c42 * u2 + Ros4::c43 * u3) * ih);
         ynew = y + Ros4::m1 * u1 + Ros4::m2 * u2 + Ros4::m3 * u3 + Ros4::m4 * u4;
         e = Ros4::e1 * u1 + Ros4::e2 * u2 + Ros4::e3 * u3 + Ros4::e4 * u4;
         return ok;
@@ -1337,7 +1319,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 __global__ void zero_queue_kernel(unsigned *q) { *q = 0u; }
 
-// Workgroups per CU of a parking kernel are capped so that the parked rows fit the workspace.
+// Workgroups per CU of a kernel with park slices are capped so that the slices fit the workspace.
 constexpr int kParkBlocksPerCu = 2;
 
 template <int W, class S, int WIN, bool PARK, int WPE = 0>
@@ -1365,13 +1347,11 @@ int launch_kernel(const DevMech &M, int64_t n, double *y, int64_t ld, const doub
     return hipGetLastError() == hipSuccess ? CK_OK : CK_EHIP;
 }
 
-template <int W, int NP, int NWIN, int WIN>
+template <int NP>
 int launch(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end, double *t,
            double *h, const IntOpts &o, unsigned *queue, int32_t *status, int32_t *nacc, int32_t *nrej,
            hipStream_t s) {
-    constexpr bool PARK = W > 1;
-    return launch_kernel<W, Ros4Coop<W, NP, NWIN, WIN, PARK>, WIN, PARK>(M, n, y, ld, p, t_end, t, h, o, queue,
-                                                                         status, nacc, nrej, s);
+    return launch_kernel<1, Ros4Coop<NP>, NP, false>(M, n, y, ld, p, t_end, t, h, o, queue, status, nacc, nrej, s);
 }
 
 // Half-row form.  Up to 104 rows two workgroups fit a CU by themselves.  The registers of 112 and 120 rows
@@ -1483,7 +1463,7 @@ int launch_integrate_coop(const DevMech &M, int64_t n, double *y, int64_t ld, co
     unsigned *q = static_cast<unsigned *>(ws);
     const int np = ((M.N + 7) / 8) * 8;
 #define CK_COOP1(NPV) \
-    case NPV: return coop::launch<1, NPV, 1, NPV>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
+    case NPV: return coop::launch<NPV>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
 #define CK_COOP2(NPV) \
     case NPV: return coop::launch_half<NPV>(M, n, y, ld, p, t_end, t, h, o, q, status, nacc, nrej, s);
     switch (np) {

@@ -171,8 +171,8 @@ bool wave_supported(const DevMech &M, int method, int precision) {
 }
 
 size_t wave_ws_bytes(const DevMech &M, int cus) {
-    // parked FP64 rows of every resident wavefront (FP64 ROS4 with NP > 32, or any NP <= 64 with
-    // the forward-difference Jacobian)
+    // a slice of NP rows of 64 doubles for every resident wavefront: the first Jacobian window's rate
+    // scalars (analytic ROS4, NP > 32), or the matrix (forward differences)
     const int np = pad_np(M.N);
     if (np > 64) return 256;
     return 256 + size_t(cus) * kWaveMaxPerCu * size_t(np) * 64 * sizeof(double);

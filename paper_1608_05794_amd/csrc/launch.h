@@ -43,7 +43,7 @@ int launch_integrate_wide(const DevMech &M, int64_t n, double *y, int64_t ld, co
 
 // workgroup-cooperative ROS4 (k_coop.hip)
 bool coop_supported(const DevMech &M);
-size_t coop_ws_bytes(const DevMech &M, int cus);   // queue counter + parked inverse rows
+size_t coop_ws_bytes(const DevMech &M, int cus);   // queue counter + park slices
 int launch_integrate_coop(const DevMech &M, int64_t n, double *y, int64_t ld, const double *p, const double *t_end,
                           double *t, double *h, const IntOpts &o, void *ws, int32_t *status, int32_t *nacc,
                           int32_t *nrej, hipStream_t s);

@@ -363,19 +363,15 @@ extern "C" int ck_mechanism_load(const char *path, int device, ck_mech **out) {
         R.beta = bound(x.beta, 2e11);
         R.EaR = bound(x.Ea / hm.R, 2e14);
         int s = 0, nu = 0, sp[6] = {0, 0, 0, 0, 0, 0};
-        double d = 0;
         for (size_t j = 0; j < x.rsp.size(); j++, s++) {
             sp[s] = x.rsp[j];
             nu |= x.rnu[j] << (2 * s);
-            d -= x.rnu[j];
         }
         const int nre = s;
         for (size_t j = 0; j < x.psp.size(); j++, s++) {
             sp[s] = x.psp[j];
             nu |= x.pnu[j] << (2 * s);
-            d += x.pnu[j];
         }
-        R.dnu = d;
         R.meta = (x.type & 3) | ((x.rev ? 1 : 0) << 2) | (s << 3) | (nre << 6) | (int(x.eff.size()) << 9);
         R.eff_begin = int(eff.size());
         for (int j = 0; j < 3; j++) R.sp[j] = sp[2 * j] | (sp[2 * j + 1] << 16);

@@ -368,7 +368,7 @@ __device__ __forceinline__ void reaction_pass(const DevMech &M, const RxArrays &
 //   sHB = sum H TB, sHW = sum H wdot, dQT = sum [R cp wdot + H (DWT - wdot / T)]   (H: J/mol)
 // at constant pressure, and U = H - RT, c_v, no wdot/T term at constant volume.
 struct ChainIn {
-    double rho, invrho, Wbar, invT, RT, R, cpm, fT, sHB, sHW, dQT, sdcp;
+    double rho, Wbar, invT, RT, R, cpm, fT, sHB, sHW, dQT, sdcp;
 };
 __device__ __forceinline__ double chain_trow(const ChainIn &c, bool cv, double HC, double cp) {
     // dQ / dz_j - (dT/dt) d(rho c)/dz_j over rho c (per mole: times W_j against Y_j)
