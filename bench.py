@@ -43,11 +43,11 @@ TRAFFIC_REF = {
                 "paper_1608_05794_amd/csrc/wtile.h", "paper_1608_05794_amd/csrc/reactions.h",
                 "paper_1608_05794_amd/csrc/kinetics.h", "paper_1608_05794_amd/csrc/ck_internal.h",
                 "paper_1608_05794_amd/csrc/launch.h", "paper_1608_05794_amd/csrc/mech.hip"],
-    "sha256": "1fa1625098adbb7d05e7741091133b52a76161e0db23c1d463147ffe97789d41",
+    "sha256": "c336005473757e0922c1a620f4beac193553d0d2d6e8f5e72ad3c3ed89fef821",
     "args": {"mech": "M53", "reactors": 131072, "t_end": 1e-3, "kernel": "wave", "precision": "fp64",
              "launch_steps": 2000},
-    "fetch_kib_per_launch": 196553.66, "fetch_factor": 1048576.0 / 524302.31,
-    "write_kib_per_launch": 112193282.53, "write_factor": 1.0,
+    "fetch_kib_per_launch": 179311.45, "fetch_factor": 1048576.0 / 524302.31,
+    "write_kib_per_launch": 108898834.45, "write_factor": 1.0,
 }
 TRANSCENDENTAL_FLOPS = 20           # FP64 operations charged per exp / log / log10 / exp10
 
@@ -789,7 +789,8 @@ def main():
                      "traffic_unit": "bytes per launch",
                      "kernel": (KERNEL_NAMES[a.kernel].replace("Adapter", "Adapter32").replace("CoopTile", "CoopTile32")
                                 if a.precision != "fp64" else
-                                KERNEL_NAMES["wave" if a.kernel == "tile" and info["n_species"] < 112 else a.kernel]),
+                                KERNEL_NAMES["wave" if a.kernel == "tile" and info["n_species"] < 112 and
+                                                  a.reactors > 512 else a.kernel]),
                      "launches": launches,
                      "avg_launch_ms": 1e3 * kernel_s / launches,
                      "flops_per_step_of_batch": flops_launch, "kernel_s": kernel_s,

@@ -7,11 +7,11 @@ namespace ck {
 // ---------------------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------------------
-// Source term.  Bound by vector issue: 926 instructions a reactor at M53 (2291 before the pair form), 86 %
-// of the issue slots busy with four wavefronts per SIMD, LDS 50 %: M53 x 131072 465 -> 240 us,
-// M111 x 30011 205 -> 115 us.  One workgroup per reactor: workgroups that stride through the batch,
-// with the next state requested ahead, take 254 us instead of 230; a line of memory per lane costs
-// 2 % against contiguous states.
+// Source term.  Bound by vector issue: 905 instructions a reactor at M53 (2291 before the pair form), 92 %
+// of the issue slots busy with four wavefronts per SIMD, LDS 54 %: M53 x 131072 466 -> 247 us,
+// M111 x 30011 205 -> 107 us.  One workgroup per reactor: workgroups that stride through the batch,
+// with the next state requested ahead, were a tenth slower (254 against 230 us of the kernel alone); a
+// line of memory per lane costs 2 % against contiguous states.
 template <int RPL, bool GEN>
 __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld,
                                                       const double *p, double *dydt, int cv) {
@@ -43,7 +43,7 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
 //
 // Eight: bound by the stores: an entry of a reactor is eight bytes of a line that it shares with fifteen
 // neighbours, so the eight staged windows are written out together, eight neighbouring reactors by one
-// store (64 bytes), instead of one reactor at a time (a line per lane): M53 x 8192 233 -> 155 us.  The
+// store (64 bytes), instead of one reactor at a time (a line per lane): M53 x 8192 141 us, 233 us with one.  The
 // windows of eight reactors fill a CU's LDS, so rates are evaluated again for a later window.
 //
 // One: the whole matrix in one window.  A call on few reactors is a latency: here every reactor has a

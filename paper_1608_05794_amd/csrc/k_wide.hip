@@ -4,8 +4,9 @@
 // Against the four-wavefront workgroup (the matrix over four wavefronts, two workgroups per CU): no
 // barrier between the 16 pivots of a panel, whose search and broadcasts are a serial chain that the four
 // wavefronts ran together, and no panel exchange; four reactors per CU instead of two.  M111 x 4099
-// reactors to 1e-13 s: 405 ms with the workgroup, 308 ms here.  Of a step's 430 k cycles the inverse
-// takes 235 k (pivots 103 k, matrix cores 89 k), the Jacobian windows 110 k, the stage source terms 24 k.
+// reactors to 1e-13 s: 489 ms with the workgroup, 295 ms here.  Of a step's 472 k cycles in an instrumented
+// build the inverse takes 266 k, the Jacobian windows 110 k with 16 k of species and chain rule, the two
+// stage source terms 45 k, the four solves 21 k, the controller 6 k.
 #include "wave.h"
 
 namespace ck {
