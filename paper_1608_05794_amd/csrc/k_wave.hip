@@ -47,8 +47,8 @@ __global__ void __launch_bounds__(64) rhs_wave_kernel(DevMech M, int64_t n, cons
 // windows of eight reactors fill a CU's LDS, so rates are evaluated again for a later window.
 //
 // One: the whole matrix in one window.  A call on few reactors is a latency: here every reactor has a
-// SIMD to itself and its rates are evaluated once (M53 x 64 45 us with eight, 31 us with one; N = 64
-// 56 and 28 us).  launch_jac_wave has the rule.
+// SIMD to itself and its rates are evaluated once (M53 x 64 45 us with eight, 25 us with one; N = 64
+// 56 and 26 us).  launch_jac_wave has the rule.
 template <int NSMAX, int WIN, int RW>
 struct JacShape {
     static constexpr int R = RW;                    // reactors of a workgroup
@@ -59,7 +59,7 @@ struct JacShape {
     static constexpr int kSlab = R == 1 ? kSlab0 : kSlab0 + (8 - kSlab0 % 32 + 32) % 32;
     static constexpr size_t kLds = size_t(R) * kSlab + 2 * (NSMAX + 1);
     // general reactions: where more wavefronts than two a SIMD fit the LDS, registers limit them
-    static constexpr bool BOUND = R == 1 && NSMAX < 32;
+    static constexpr bool BOUND = R == 1 && NSMAX < 32, POWERS = R == 1 && NSMAX > 16;
 };
 // WPE: resident wavefronts per SIMD that the registers have to allow
 template <int NSMAX, int WIN, int RW, int WPE>
@@ -101,7 +101,8 @@ jac_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld, const double 
     zero_jc(L, ns);
     species_pass<1, true>(M, yy, p[r], L, x);
     const RxScale sc = rx_scale<1>(L, x);
-    reaction_pass<64, true, true, SH::BOUND>(M, L, x.t, x.Ctot, sc, -1, min(WIN, N), kRates, nullptr, lane, first);
+    reaction_pass<64, true, true, SH::BOUND, SH::POWERS>(M, L, x.t, x.Ctot, sc, -1, min(WIN, N), kRates, nullptr,
+                                                         lane, first);
     __syncthreads();
     finish_rhs<1>(M, L, x, ff);
     const Chain<1> c = chain_rule<1>(M, L, x, yy, bcast(ff[0], 0));
@@ -120,10 +121,26 @@ jac_wave_kernel(DevMech M, int64_t n, const double *y, int64_t ld, const double 
             zero_jc(L, ns);
             __syncthreads();
             const PairRec again = first_pair<64>(M, lane);
-            reaction_pass<64, true, true, SH::BOUND>(M, L, x.t, x.Ctot, sc, w * WIN - 1, min(WIN, N - w * WIN), kScatter,
-                                                     nullptr, lane, again);
+            reaction_pass<64, true, true, SH::BOUND, SH::POWERS>(M, L, x.t, x.Ctot, sc, w * WIN - 1,
+                                                                 min(WIN, N - w * WIN), kScatter, nullptr, lane, again);
         }
         __syncthreads();
+        if constexpr (SH::R == 1 && NSMAX >= 32) {
+            // one window, a matrix column per lane: no divisions, and the rows' loads go out together, eight at
+            // a time (M53 x 1 30 us with the loop below, 24 so)
+            if (lane < N) {
+                const bool t = lane == 0;      // the temperature column is staged whole: 1 x - 0
+                const double iw = IW[lane];
+                const double *a = t ? L.DWT : L.JC + lane;
+                double *out = jac + int64_t(lane) * ld + r0;
+                out[0] = iw * L.TROW[lane];
+#pragma unroll 8
+                for (int i = 1; i < N; i++)
+                    out[int64_t(i) * N * ld] =
+                        iw * fma(t ? 1.0 : W[i], a[(i - 1) * (t ? 1 : SH::LDJ)], t ? -0.0 : L.TB[i - 1]);
+            }
+            break;
+        }
         const int s = int(threadIdx.x) % SH::R;
         const double *slab = lds_raw + s * SH::kSlab;
         const int cols = min(WIN, N - w * WIN);

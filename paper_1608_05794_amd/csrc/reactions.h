@@ -254,7 +254,9 @@ __device__ __forceinline__ void pair_reactions(const DevMech &M, const RxArrays 
 // takes 22 registers off a Jacobian pass and lets another wavefront reside (N = 32, 155 reactions, a
 // third of them general, 30000 Jacobians: 351 us with, 426 us without).  The source term is better off
 // without the branches (N = 32 as above: 98 us with, 93 us without).
-template <int T, bool JAC, bool BOUND>
+// POWERS: derivatives by dprod_powers, for kernels with the registers for it (Jacobian of N = 64, 315 general
+// reactions, one reactor: 52 -> 43 us; the ROS4 kernels of pair-form mechanisms would lose 1 to 2 %).
+template <int T, bool JAC, bool BOUND, bool POWERS>
 __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                                   const RxScale &sc, int c0, int win, RxMode mode, double *keep,
                                                   int tid) {
@@ -266,6 +268,9 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
         const int nmax = BOUND ? __builtin_amdgcn_readfirstlane(R.blk_slots) : kMaxSlots;
         Slots S;
         load_slots(R, Cg, S, nmax);
+        SlotPowers w;
+        if (JAC && POWERS) slot_powers(S, nmax, w);
+        auto dprod = [&](int s) { return POWERS ? dprod_powers(S, w, s, nmax) : dprod_slot(S, s, nmax); };
         double ckf, ckr, rdm;
         if (JAC && mode == kScatterKept) {
             ckf = keep[0];
@@ -304,7 +309,7 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
                     if (JAC) {
                         atomicAdd(&A.DWT[S.sp[s]], v * vT);
                         atomicAdd(&A.TB[S.sp[s]], v * vB);
-                        const double d = dprod_slot(S, s, nmax);
+                        const double d = dprod(s);
                         atomicAdd(&A.HC[S.sp[s]], (S.sgn[s] < 0 ? ckf * d : -ckr * d) * shx);
                     }
                 }
@@ -333,7 +338,7 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
             for (int b = 0; b < kMaxSlots; b++) {
                 if (b >= nmax) break;
                 if (S.sgn[b] == 0) continue;
-                const double d = dprod_slot(S, b, nmax);
+                const double d = dprod(b);
                 column(S.sp[b], S.sgn[b] < 0 ? ckf * d : -ckr * d);
             }
             if (rdm != 0.0) {
@@ -347,13 +352,14 @@ __device__ __forceinline__ void general_reactions(const DevMech &M, const RxArra
 
 // Every reaction of the mechanism.  Window: columns [c0, c0 + win) of JC, win already cut to the
 // species count.  first: first_pair(M, tid).  The caller synchronises before and after.  GEN = false
-// leaves the general form out (the caller knows that the mechanism has none); BOUND: general_reactions.
-template <int T, bool JAC, bool GEN = true, bool BOUND = (T > 64)>
+// leaves the general form out (the caller knows that the mechanism has none); BOUND, POWERS:
+// general_reactions.
+template <int T, bool JAC, bool GEN = true, bool BOUND = (T > 64), bool POWERS = false>
 __device__ __forceinline__ void reaction_pass(const DevMech &M, const RxArrays &A, const TPow &t, double Ctot,
                                               const RxScale &sc, int c0, int win, RxMode mode, double *keep,
                                               int tid, const PairRec &first) {
     if (GEN && M.n_gen > 0) {
-        general_reactions<T, JAC, BOUND>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
+        general_reactions<T, JAC, BOUND, POWERS>(M, A, t, Ctot, sc, c0, win, mode, keep, tid);
         if (JAC && (mode == kRatesKeep || mode == kScatterKept)) keep += 3 * T * ((M.n_gen + T - 1) / T);
     }
     if (JAC && mode == kScatterKept) pair_scatter<T>(M, A, c0, win, keep, tid);
