@@ -59,7 +59,7 @@ struct JacShape {
     static constexpr int kSlab = R == 1 ? kSlab0 : kSlab0 + (8 - kSlab0 % 32 + 32) % 32;
     static constexpr size_t kLds = size_t(R) * kSlab + 2 * (NSMAX + 1);
     // general reactions: where more wavefronts than two a SIMD fit the LDS, registers limit them
-    static constexpr bool BOUND = R == 1 && NSMAX < 32, POWERS = R == 1 && NSMAX > 16;
+    static constexpr bool BOUND = R == 1 && NSMAX < 36, POWERS = R == 1 && NSMAX > 16;
 };
 // WPE: resident wavefronts per SIMD that the registers have to allow
 template <int NSMAX, int WIN, int RW, int WPE>
@@ -211,28 +211,45 @@ int launch_jac_wave(const DevMech &M, int64_t n, const double *y, int64_t ld, co
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return CK_EHIP;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return CK_EHIP;
-    // One reactor a workgroup while all of them are resident at once, one a SIMD: M53 x 1024 42 us (eight:
-    // 48), x 1536 68 us (49).  With N <= 16 a matrix is small enough for that at any size (M13 x 30000 92 us,
-    // 130 with eight).  With general reactions, whose registers keep eight-reactor workgroups to one a CU,
-    // it pays again when those need more than two rounds (N = 32, a third of 155 reactions general:
-    // x 4096 78 us, 73 with eight; x 30000 348 us, 435).
-    const int64_t few = 4 * int64_t(cus);
+    // Workgroups of eight: one a CU at a time (LDS), so they take rounds of 8 CUs reactors, and an idle part
+    // of the last round costs as much as a full one.  One reactor a workgroup takes a time in proportion to n,
+    // is a SIMD's alone in a small batch and has the better occupancy at small N; its stores are narrow, which
+    // costs most where ld is a multiple of 4 KiB and a reactor's entries share their channels.  So: one by one
+    // where the rounds of eight are poorly filled (M53 x 1200 46 us, eight 49; x 2100 67, 84; x 8192 270, 157),
+    // and general reactions, which keep eight reactors from overlapping, more often (N = 64, all 315 general:
+    // x 2100 137 us, eight 207; x 16384, ld a multiple of 4 KiB, N = 54: 675 us, eight 460).
     const bool general = M.n_gen > 0;
+    const int64_t round = 8 * int64_t(cus), rounds = (n + round - 1) / round;
+    auto filled_to = [&](int eighths) { return n <= eighths * rounds * cus; };
     if (M.N <= 16) {
         // the general pass takes spills for a fourth wavefront once three do not hold the batch (N = 14,
         // all 65 reactions general: x 2048 41 us, 37 with three; x 30000 235 us, 256)
-        if (general && n > 3 * few) return launch_jac<15, 16, 1, 4>(M, n, y, ld, p, jac, cv, s);
+        if (general && n > 12 * int64_t(cus)) return launch_jac<15, 16, 1, 4>(M, n, y, ld, p, jac, cv, s);
         return launch_jac<15, 16, 1, 3>(M, n, y, ld, p, jac, cv, s);
     }
     if (M.N <= 32) {
-        if (n <= few || (general && n > 4 * few)) return launch_jac<31, 32, 1, 3>(M, n, y, ld, p, jac, cv, s);
-        return launch_jac<31, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
+        // N = 32, pair form: x 2048 33 us, eight 29; x 2100 36, 43; x 16384 133, 138.  N = 18 is better off one by
+        // one at every n (x 30000 129 us, eight 190), N = 25 too (151, 213).
+        if (M.N > 24 && !filled_to(7) && rounds <= (general ? 2 : 4))
+            return launch_jac<31, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
+        return launch_jac<31, 32, 1, 3>(M, n, y, ld, p, jac, cv, s);
     }
-    if (M.N <= 56) {
-        if (n <= few) return launch_jac<55, 56, 1, 1>(M, n, y, ld, p, jac, cv, s);
-        return launch_jac<55, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
-    }
-    if (n <= few) return launch_jac<63, 64, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    // three wavefronts a SIMD (N = 34, all 165 reactions general: x 30000 381 us, eight 708)
+    if (M.N <= 36) return launch_jac<35, 36, 1, 3>(M, n, y, ld, p, jac, cv, s);
+    bool one;
+    if (general)
+        // N = 40: one by one always (x 8192 177 us, eight 253).  Full rounds of eight pay from N = 45 on (N = 54,
+        // irreversible, x 8192 237 us, one by one 315) while they are few or ld is that multiple.
+        one = M.N <= 40 || filled_to(M.N <= 48 || rounds > 1 ? 7 : 5) ||
+              (rounds > 1 && (M.N <= 44 || (rounds >= 5 && ld % 512 != 0)));
+    else
+        one = filled_to(M.N <= 48 ? 6 : 5);
+    // the fewer columns staged, the more workgroups a CU holds: ten, seven, five and four
+    if (one && M.N <= 40) return launch_jac<39, 40, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    if (one && M.N <= 48) return launch_jac<47, 48, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    if (one && M.N <= 56) return launch_jac<55, 56, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    if (one) return launch_jac<63, 64, 1, 1>(M, n, y, ld, p, jac, cv, s);
+    if (M.N <= 56) return launch_jac<55, 32, 8, 2>(M, n, y, ld, p, jac, cv, s);
     return launch_jac<63, 24, 8, 2>(M, n, y, ld, p, jac, cv, s);      // eight windows of 32 columns exceed the LDS
 }
 

@@ -1,9 +1,11 @@
 """Calls on few reactors, which take kernels of their own, against the same call on many.
 
-A Jacobian is evaluated with one reactor per workgroup up to four per compute unit and with eight beyond
-that (N <= 16: with one always, general reactions in another build from twelve per compute unit on; general
-reactions and N <= 32: with one again from sixteen on).  All forms run the same operations in the same order,
-so a reactor's matrix is the same bits in each.
+A Jacobian is evaluated with one reactor per workgroup where the rounds of eight per compute unit, which
+workgroups of eight reactors take, are poorly filled, and with eight per workgroup elsewhere (N <= 16: with one
+always, general reactions in another build from twelve per compute unit on; N <= 24 and 33 to 36, and general
+reactions of 37 to 40 rows: with one always).  All forms run the same operations in the same order, so a
+reactor's matrix is the same bits in each.  The edges: the size at which the form changes, in reactors per
+compute unit, or one within a form.
 
 Timing: one reactor's call occupies one SIMD, a call on 2048 gives every SIMD two.  The form for few
 reactors evaluates the rates once and stages the matrix whole, the other evaluates them for each of its
@@ -47,7 +49,9 @@ def setup(tmp_path, nsp, forms, n):
 
 @pytest.mark.parametrize("nsp,forms,per_cu", [(15, "mixed", 12), (16, "pair", 4), (31, "pair", 4), (31, "mixed", 4),
                                               (31, "all", 16), (32, "mixed", 4), (55, "pair", 4), (56, "pair", 4),
-                                              (63, "all", 4)])
+                                              (63, "all", 4), (31, "pair", 7), (39, "pair", 6), (44, "all", 7),
+                                              (47, "pair", 6), (55, "pair", 5), (56, "pair", 5), (55, "mixed", 14),
+                                              (63, "all", 14)])
 def test_jacobian_forms_agree(tmp_path, nsp, forms, per_cu):
     edge = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
     ck, g, y, P = setup(tmp_path, nsp, forms, edge + 3)
