@@ -43,7 +43,7 @@ TRAFFIC_REF = {
                 "paper_1608_05794_amd/csrc/wtile.h", "paper_1608_05794_amd/csrc/reactions.h",
                 "paper_1608_05794_amd/csrc/kinetics.h", "paper_1608_05794_amd/csrc/ck_internal.h",
                 "paper_1608_05794_amd/csrc/launch.h", "paper_1608_05794_amd/csrc/mech.hip"],
-    "sha256": "c336005473757e0922c1a620f4beac193553d0d2d6e8f5e72ad3c3ed89fef821",
+    "sha256": "93ca4942749fc76433687957647e8703f37400945e6b22cdcdff38007666e1f4",
     "args": {"mech": "M53", "reactors": 131072, "t_end": 1e-3, "kernel": "wave", "precision": "fp64",
              "launch_steps": 2000},
     "fetch_kib_per_launch": 179311.45, "fetch_factor": 1048576.0 / 524302.31,
